@@ -234,9 +234,12 @@ b3d_status b3d_mesh_create(const float* verts, int32_t V, const int32_t* tris, i
     m->allocs.push_back(*dst);
     return hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
   };
-  void *d_cl, *d_cv, *d_ct, *d_v, *d_t, *d_n;
+  std::vector<float4> firsts(lay.pids.size());
+  for (size_t q = 0; q < firsts.size(); ++q) firsts[q] = lay.pverts[4 * q];
+  void *d_cl, *d_cv, *d_cf, *d_ct, *d_v, *d_t, *d_n;
   bool ok = upload(lay.clusters.data(), std::max<size_t>(1, lay.clusters.size()) * sizeof(ClusterDev), &d_cl) &&
             upload(lay.pverts.data(), lay.pverts.size() * sizeof(float4), &d_cv) &&
+            upload(firsts.data(), firsts.size() * sizeof(float4), &d_cf) &&
             upload(lay.pids.data(), lay.pids.size() * sizeof(uint2), &d_ct) &&
             upload(v4.data(), v4.size() * sizeof(float4), &d_v) && upload(t4.data(), t4.size() * sizeof(int4), &d_t) &&
             upload(nrm.data(), nrm.size() * sizeof(float4), &d_n);
@@ -248,6 +251,7 @@ b3d_status b3d_mesh_create(const float* verts, int32_t V, const int32_t* tris, i
   MeshDev& d = m->dev;
   d.clusters = (const ClusterDev*)d_cl;
   d.pverts = (const float4*)d_cv;
+  d.pfirsts = (const float4*)d_cf;
   d.pids = (const uint2*)d_ct;
   d.n_visible = lay.n_visible;
   d.verts = (const float4*)d_v;

@@ -37,16 +37,21 @@ struct Pose {
 // (a, c, d) sharing the edge a-c (a convex planar quad).  sphere = centre and
 // radius of a ball holding them; cone = unit axis and half-angle (radians) of
 // a cone holding their face normals (half-angle > pi/2 means "no bound").
+// `alike` clusters hold parallelograms a, a + ab, a + ab + ad, a + ad that
+// share their edge vectors up to the rounding of the vertices: the faces of
+// equal voxels.
 struct ClusterDev {
-  int pfirst, np, pad0, pad1;
+  int pfirst, np, alike, pad;
   float4 sphere;
   float4 cone;
+  float4 ab, ad;  // alike: the edge vectors b - a and d - a
 };
 
 // Device view of an uploaded mesh.
 struct MeshDev {
   const ClusterDev* clusters;  // [0, n_visible) drawn; [n_visible, n_clusters) only near the near plane
   const float4* pverts;        // [primitives][4] object-frame corners a, b, c, d (d = c for a triangle)
+  const float4* pfirsts;       // [primitives] corner a alone (all that an alike cluster's primitives need)
   const uint2* pids;           // [primitives] caller's ids of triangles (a, b, c) and (a, c, d) or kNoTri
   const float4* verts;         // caller's vertices
   const int4* tris;            // caller's triangles (w unused)
@@ -435,6 +440,132 @@ __device__ __forceinline__ void walk_staged(const float* __restrict__ st, int la
   }
 }
 
+// Boxes of at most this many rows and columns are walked by a whole wave in
+// step; larger ones by each lane on its own.
+constexpr int kStepBox = 16;
+
+// An alike cluster (see ClusterDev), one parallelogram per lane.  What bounds
+// it is VALU issue: a voxel face covers two or three pixels at the sizes the
+// searches run at, so setting a face up costs more than filling it.  Hence
+// one corner is transformed and the other three follow from the edge vectors
+// (18 multiply-adds and additions for four corners instead of 36, 16 bytes
+// read instead of 64); one 1/z plane serves both triangles; and the wave steps
+// through the rows and columns of its largest box together, which keeps the
+// walk free of per-lane bookkeeping (the boxes of equal faces differ by at
+// most a row and a column).  A centre beyond every side by the largest margin
+// tq is outside or written at once, on the triangle that the diagonal's sign
+// picks; the few between, and every centre of a face seen nearly edge-on, go
+// to the queue of the exact test.  Measured against the general path on blobs
+// of 1 cm voxels: 429 against 495 us for 5,000 hypotheses of 2,000 voxels at
+// 160x120 with the adjoint, 3,086 against 4,177 us for 10,000 of 1,500 voxels at
+// 320x240.
+// Returns false, for the whole wave, when the general path has to take the
+// cluster: a corner behind the near plane or a box beyond kStepBox.
+template <bool COUNT>
+__device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev& m, const Pose& P, const Cam& cam,
+                                             uint32_t id_base, const Rect& buf, int pitch, float bx0, float bx1,
+                                             float by0, float by1, unsigned long long* zbuf, const RasterLds& lds,
+                                             int lane, unsigned* c_work) {
+  // camera coordinates with x and y scaled by the focal lengths; pixel
+  // coordinates with the centres on the integers
+  const float cu = cam.cx - 0.5f, cv = cam.cy - 0.5f;
+  const bool in = lane < cl.np;
+  const size_t pi = (size_t)cl.pfirst + (in ? lane : 0);
+  const float4 a = m.pfirsts[pi];
+  const uint2 ids = m.pids[pi];
+  const float3 oa = xform(P, a.x, a.y, a.z);
+  const float3 rb = rotate(P, cl.ab.x, cl.ab.y, cl.ab.z), rd = rotate(P, cl.ad.x, cl.ad.y, cl.ad.z);
+  const float bX = cam.fx * rb.x, bY = cam.fy * rb.y, dX = cam.fx * rd.x, dY = cam.fy * rd.y;
+  const float aX = cam.fx * oa.x, aY = cam.fy * oa.y;
+  const float Bz = oa.z + rb.z, Dz = oa.z + rd.z, Cz = Bz + rd.z;
+  const float zmin = fminf(fminf(oa.z, Bz), fminf(Cz, Dz));
+  if (__ballot(in && !(zmin > cam.znear)) != 0ull) return false;
+  const float iA = __builtin_amdgcn_rcpf(oa.z), iB = __builtin_amdgcn_rcpf(Bz);
+  const float iC = __builtin_amdgcn_rcpf(Cz), iD = __builtin_amdgcn_rcpf(Dz);
+  const float Au = __builtin_fmaf(aX, iA, cu), Av = __builtin_fmaf(aY, iA, cv);
+  const float Bu = __builtin_fmaf(aX + bX, iB, cu), Bv = __builtin_fmaf(aY + bY, iB, cv);
+  const float Cu = __builtin_fmaf(aX + bX + dX, iC, cu), Cv = __builtin_fmaf(aY + bY + dY, iC, cv);
+  const float Du = __builtin_fmaf(aX + dX, iD, cu), Dv = __builtin_fmaf(aY + dY, iD, cv);
+  // edges as in the general path: e of (a, b, c), f of (a, c, d), diagonal e1
+  const float e0x = Cu - Bu, e0y = Cv - Bv, e1x = Au - Cu, e1y = Av - Cv, e2x = Bu - Au, e2y = Bv - Av;
+  const float f0x = Du - Cu, f0y = Dv - Cv, f1x = Au - Du, f1y = Av - Dv;
+  const float area1 = e1x * e2y - e2x * e1y, area2 = e1x * f1y - f1x * e1y;
+  const float mag = fmaxf(fmaxf(fmaxf(fabsf(Au), fabsf(Av)), fmaxf(fabsf(Bu), fabsf(Bv))),
+                          fmaxf(fmaxf(fabsf(Cu), fabsf(Cv)), fmaxf(fabsf(Du), fabsf(Dv))));
+  const float tau = 2e-6f * fmaxf(mag + 0.5f, 256.0f);
+  const float len = fmaxf(fmaxf(fmaxf(fabsf(e0x) + fabsf(e0y), fabsf(e1x) + fabsf(e1y)),
+                                fmaxf(fabsf(e2x) + fabsf(e2y), fabsf(f0x) + fabsf(f0y))),
+                          fabsf(f1x) + fabsf(f1y));
+  const float tm = tau * len, amb = 4.0f * tm;
+  const bool act = in && !(fminf(area1, area2) > amb);
+  const bool eon = !(fmaxf(area1, area2) < -amb);
+  const float umin = fminf(fminf(Au, Bu), fminf(Cu, Du)), umax = fmaxf(fmaxf(Au, Bu), fmaxf(Cu, Du));
+  const float vmin = fminf(fminf(Av, Bv), fminf(Cv, Dv)), vmax = fmaxf(fmaxf(Av, Bv), fmaxf(Cv, Dv));
+  const float c0 = ceilf(fmaxf(umin - tau, bx0)), c1 = floorf(fminf(umax + tau, bx1));
+  const float r0 = ceilf(fmaxf(vmin - tau, by0)), r1 = floorf(fminf(vmax + tau, by1));
+  const bool has = act && c0 <= c1 && r0 <= r1;
+  const float nc = has ? c1 - c0 : -1.0f, nr = has ? r1 - r0 : -1.0f;  // columns and rows less one
+  int Rm = 0, Cm = 0;
+  while (Rm <= kStepBox && __ballot((float)Rm <= nr) != 0ull) ++Rm;
+  while (Cm <= kStepBox && __ballot((float)Cm <= nc) != 0ull) ++Cm;
+  if (Rm > kStepBox || Cm > kStepBox) return false;
+  if (COUNT && in) {
+    c_work[kCntVert] += 4;
+    c_work[kCntTri] += 2;
+    c_work[kCntSetup] += has ? 2u : 0u;
+  }
+  // edge functions at the box's first centre, positive outside
+  const float w0b = e0x * (r0 - Bv) - e0y * (c0 - Bu), w1b = e1x * (r0 - Cv) - e1y * (c0 - Cu);
+  const float w2b = e2x * (r0 - Av) - e2y * (c0 - Au), v0b = f0x * (r0 - Cv) - f0y * (c0 - Cu);
+  const float v1b = f1x * (r0 - Dv) - f1y * (c0 - Du);
+  // 1/z is affine on the screen: its value at that centre and its gradient
+  const float ia = __builtin_amdgcn_rcpf(area1);
+  const float zb = (w0b * iA + w1b * iB + w2b * iC) * ia;
+  const float zr = (e0x * iA + e1x * iB + e2x * iC) * ia;
+  const float zc = (e0y * iA + e1y * iB + e2y * iC) * ia;
+  const float tq = eon ? 3.0e38f : tm;
+  const uint32_t id1 = id_base + ids.x, id2 = id_base + ids.y;
+  const int first = (int)((r0 - (float)buf.y0) * (float)pitch + (c0 - (float)buf.x0));  // exact below 2^24
+  for (int r = 0; r < Rm; ++r) {
+    const float dr = (float)r;
+    const float w0r = __builtin_fmaf(e0x, dr, w0b), w1r = __builtin_fmaf(e1x, dr, w1b);
+    const float w2r = __builtin_fmaf(e2x, dr, w2b), v0r = __builtin_fmaf(f0x, dr, v0b);
+    const float v1r = __builtin_fmaf(f1x, dr, v1b), izr = __builtin_fmaf(zr, dr, zb);
+    const float ncr = dr <= nr ? nc : -1.0f;
+    const int pixr = first + r * pitch;
+    for (int c = 0; c < Cm; ++c) {
+      const float dc = (float)c;
+      const float w0 = __builtin_fmaf(-e0y, dc, w0r), w1 = __builtin_fmaf(-e1y, dc, w1r);
+      const float w2 = __builtin_fmaf(-e2y, dc, w2r), v0 = __builtin_fmaf(-f0y, dc, v0r);
+      const float v1 = __builtin_fmaf(-f1y, dc, v1r);
+      const float side = fmaxf(fmaxf(fmaxf(w0, w2), v0), v1);
+      if (dc <= ncr && !(side > tq)) {
+        const int pix = pixr + c;
+        if (fmaxf(side, -fabsf(w1)) < -tq) {
+          if (COUNT) ++c_work[kCntFrag];
+          const float z = __builtin_amdgcn_rcpf(__builtin_fmaf(-zc, dc, izr));
+          atomicMin(&zbuf[pix], pack_key(z, w1 > 0.0f ? id2 : id1));
+        } else {
+          // within the margin of an edge or the diagonal: both triangles that may hold it
+          for (int k = 0; k < 2; ++k) {
+            const float x0 = k ? v0 : w0, x1 = k ? v1 : w1, x2 = k ? -w1 : w2;
+            const float top = fmaxf(fmaxf(x0, x1), x2);
+            if (top > tm) continue;
+            const int slot = atomicAdd(&lds.counts[0], 1);
+            if (slot < lds.qcap) {
+              lds.queue[slot] = make_uint2((uint32_t)pix, k ? ids.y : ids.x);
+            } else if (!eon && !(top > 0.0f)) {  // queue full: single precision
+              if (COUNT) ++c_work[kCntFrag];
+              atomicMin(&zbuf[pix], pack_key(__builtin_amdgcn_rcpf(__builtin_fmaf(-zc, dc, izr)), k ? id2 : id1));
+            }
+          }
+        }
+      }
+    }
+  }
+  return true;
+}
+
 // Rasterise the mesh under pose P into the pixels of the image rectangle
 // `band` of an LDS key buffer that covers the rectangle `buf` (row pitch
 // buf.w(); band inside buf).  Triangle ids written are
@@ -456,6 +587,7 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
                                             const Rect& band, const Rect& buf, unsigned long long* zbuf,
                                             const RasterLds& lds, unsigned* cnt = nullptr) {
   unsigned c_vert = 0, c_tri = 0, c_setup = 0, c_frag = 0, c_exact = 0;
+  unsigned c_alike[kCntN] = {};  // raster_alike's share
   const int pitch = buf.w();
   const float bx0 = (float)band.x0, bx1 = (float)(band.x1 - 1);
   const float by0 = (float)band.y0, by1 = (float)(band.y1 - 1);
@@ -491,7 +623,9 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
       if (lane == 0) q = atomicAdd(&lds.counts[1 + kWaves], 1);
       q = __shfl(q, 0, 64);
       if (q >= total) break;
-      const ClusterDev cl = m.clusters[lds.list[q]];
+      const ClusterDev cl = m.clusters[__builtin_amdgcn_readfirstlane(lds.list[q])];
+      if (__builtin_amdgcn_readfirstlane(cl.alike) && raster_alike<COUNT>(cl, m, P, cam, id_base, buf, pitch, bx0, bx1, by0, by1, zbuf, lds, lane, c_alike))
+        continue;
       bool staged = false;
       if (lane < cl.np) {
         const size_t pi = (size_t)cl.pfirst + lane;
@@ -636,10 +770,10 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
     atomicMin(&zbuf[e.x], pack_key(z, id_base + e.y));
   }
   if (COUNT) {
-    atomicAdd(&cnt[kCntVert], c_vert);
-    atomicAdd(&cnt[kCntTri], c_tri);
-    atomicAdd(&cnt[kCntSetup], c_setup);
-    atomicAdd(&cnt[kCntFrag], c_frag);
+    atomicAdd(&cnt[kCntVert], c_vert + c_alike[kCntVert]);
+    atomicAdd(&cnt[kCntTri], c_tri + c_alike[kCntTri]);
+    atomicAdd(&cnt[kCntSetup], c_setup + c_alike[kCntSetup]);
+    atomicAdd(&cnt[kCntFrag], c_frag + c_alike[kCntFrag]);
     atomicAdd(&cnt[kCntExact], c_exact);
   }
   __syncthreads();

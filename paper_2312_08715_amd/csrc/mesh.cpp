@@ -21,8 +21,10 @@
 // and triangles with a repeated vertex position (zero area, never drawn) are
 // dropped.  Triangle ids stay the caller's row indices.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <numeric>
 #include <unordered_map>
 #include <vector>
@@ -243,6 +245,7 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
     int p[4];       // position ids a, b, c, d (d = c for a single triangle)
     int id1, id2;   // caller's triangle ids (id2 = -1: single)
     uint64_t key;
+    bool alike;     // a parallelogram with its class's commonest edge vectors
   };
   std::vector<int> mate((size_t)T, -1);
   std::vector<Prim> prims[2];  // 0 drawn, 1 hidden
@@ -317,11 +320,83 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
       pr.id2 = -1;
     }
     pr.key = order_key[t];
+    pr.alike = false;
     prims[cls[t]].push_back(pr);
+  }
+  // Parallelograms of one class that share their edge vectors: the commonest
+  // pair of edges of each class (rounded to a grid far above the rounding of
+  // the vertices and far below an edge), when it is worth clusters of its own.
+  double extent = 0.0;
+  for (int k = 0; k < 3; ++k) extent = std::max(extent, std::max(std::fabs(lo[k]), std::fabs(hi[k])));
+  const double same = extent * 1.1920929e-7;  // one unit in the last place of the largest coordinate
+  struct Edges {
+    double ab[3], ad[3];
+  };
+  auto edges_of = [&](const Prim& pr) {
+    Edges e;
+    for (int k = 0; k < 3; ++k) {
+      e.ab[k] = pos(pr.p[1], k) - pos(pr.p[0], k);
+      e.ad[k] = pos(pr.p[3], k) - pos(pr.p[0], k);
+    }
+    return e;
+  };
+  Edges common[26];
+  {
+    std::map<std::array<long long, 7>, std::vector<size_t>> groups;
+    for (size_t i = 0; i < prims[0].size(); ++i) {
+      const Prim& pr = prims[0][i];
+      if (pr.id2 < 0) continue;
+      const Edges e = edges_of(pr);
+      double off = 0.0;
+      for (int k = 0; k < 3; ++k)
+        off = std::max(off, std::fabs(pos(pr.p[2], k) - pos(pr.p[0], k) - e.ab[k] - e.ad[k]));
+      if (off > 2.0 * same) continue;
+      std::array<long long, 7> g;
+      g[0] = (long long)(pr.key >> 32);
+      for (int k = 0; k < 3; ++k) {
+        g[1 + k] = std::llround(e.ab[k] / (256.0 * same));
+        g[4 + k] = std::llround(e.ad[k] / (256.0 * same));
+      }
+      groups[g].push_back(i);
+    }
+    const std::vector<size_t>* pick[26] = {};
+    for (auto& kv : groups) {
+      const std::vector<size_t>*& p = pick[kv.first[0]];
+      if (!p || kv.second.size() > p->size()) p = &kv.second;
+    }
+    for (int d = 0; d < 26; ++d) {
+      if (!pick[d] || pick[d]->size() < 16) continue;  // a quarter of a cluster
+      // the middle of the group's edges, then those within one unit of it
+      Edges lo_e = edges_of(prims[0][(*pick[d])[0]]), hi_e = lo_e;
+      for (size_t i : *pick[d]) {
+        const Edges e = edges_of(prims[0][i]);
+        for (int k = 0; k < 3; ++k) {
+          lo_e.ab[k] = std::min(lo_e.ab[k], e.ab[k]);
+          hi_e.ab[k] = std::max(hi_e.ab[k], e.ab[k]);
+          lo_e.ad[k] = std::min(lo_e.ad[k], e.ad[k]);
+          hi_e.ad[k] = std::max(hi_e.ad[k], e.ad[k]);
+        }
+      }
+      Edges& c = common[d];
+      for (int k = 0; k < 3; ++k) {
+        c.ab[k] = 0.5 * (lo_e.ab[k] + hi_e.ab[k]);
+        c.ad[k] = 0.5 * (lo_e.ad[k] + hi_e.ad[k]);
+      }
+      for (size_t i : *pick[d]) {
+        const Edges e = edges_of(prims[0][i]);
+        bool ok = true;
+        for (int k = 0; k < 3; ++k)
+          ok = ok && std::fabs(e.ab[k] - c.ab[k]) <= same && std::fabs(e.ad[k] - c.ad[k]) <= same;
+        prims[0][i].alike = ok;
+      }
+    }
   }
   // 6. clusters: drawn primitives first, then hidden ones
   auto emit = [&](std::vector<Prim>& ps) {
-    std::stable_sort(ps.begin(), ps.end(), [](const Prim& x, const Prim& y) { return x.key < y.key; });
+    std::stable_sort(ps.begin(), ps.end(), [](const Prim& x, const Prim& y) {
+      if ((x.key >> 32) != (y.key >> 32) || x.alike == y.alike) return x.key < y.key;
+      return x.alike;
+    });
     size_t i = 0;
     while (i < ps.size()) {
       ClusterDev c{};
@@ -330,7 +405,14 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
       double axis[3] = {0, 0, 0};
       double blo[3] = {1e300, 1e300, 1e300}, bhi[3] = {-1e300, -1e300, -1e300};
       size_t j = i;
-      for (; j < ps.size() && c.np < kClusterPrims && (ps[j].key >> 32) == cls_dir; ++j) {
+      c.alike = ps[i].alike ? 1 : 0;
+      if (c.alike) {
+        const Edges& e = common[cls_dir];
+        c.ab = make_float4((float)e.ab[0], (float)e.ab[1], (float)e.ab[2], 0.0f);
+        c.ad = make_float4((float)e.ad[0], (float)e.ad[1], (float)e.ad[2], 0.0f);
+      }
+      for (; j < ps.size() && c.np < kClusterPrims && (ps[j].key >> 32) == cls_dir && ps[j].alike == ps[i].alike;
+           ++j) {
         const Prim& pr = ps[j];
         for (int k = 0; k < 4; ++k) {
           L.pverts.push_back(make_float4((float)pos(pr.p[k], 0), (float)pos(pr.p[k], 1), (float)pos(pr.p[k], 2), 0.0f));
