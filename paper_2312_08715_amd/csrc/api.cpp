@@ -194,6 +194,7 @@ b3d_status b3d_mesh_create(const float* verts, int32_t V, const int32_t* tris, i
   if (lay.pids.empty()) lay.pids.push_back(make_uint2(0, kNoTri));
   std::vector<float4> v4((size_t)V), nrm((size_t)T);
   std::vector<int4> t4((size_t)T);
+  std::vector<double4> pl((size_t)T);
   double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
   for (int i = 0; i < V; ++i) {
     v4[i] = make_float4(verts[3 * i], verts[3 * i + 1], verts[3 * i + 2], 0.0f);
@@ -212,6 +213,9 @@ b3d_status b3d_mesh_create(const float* verts, int32_t V, const int32_t* tris, i
     }
     nrm[t] = make_float4((float)(e1[1] * e2[2] - e1[2] * e2[1]), (float)(e1[2] * e2[0] - e1[0] * e2[2]),
                          (float)(e1[0] * e2[1] - e1[1] * e2[0]), 0.0f);
+    const double n[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
+    pl[t] = make_double4(n[0], n[1], n[2],
+                         n[0] * verts[3 * a] + n[1] * verts[3 * a + 1] + n[2] * verts[3 * a + 2]);
   }
   double ctr[3], rad = 0.0;
   for (int k = 0; k < 3; ++k) ctr[k] = 0.5 * (lo[k] + hi[k]);
@@ -236,13 +240,14 @@ b3d_status b3d_mesh_create(const float* verts, int32_t V, const int32_t* tris, i
   };
   std::vector<float4> firsts(lay.pids.size());
   for (size_t q = 0; q < firsts.size(); ++q) firsts[q] = lay.pverts[4 * q];
-  void *d_cl, *d_cv, *d_cf, *d_ct, *d_v, *d_t, *d_n;
+  void *d_cl, *d_cv, *d_cf, *d_ct, *d_v, *d_t, *d_n, *d_p;
   bool ok = upload(lay.clusters.data(), std::max<size_t>(1, lay.clusters.size()) * sizeof(ClusterDev), &d_cl) &&
             upload(lay.pverts.data(), lay.pverts.size() * sizeof(float4), &d_cv) &&
             upload(firsts.data(), firsts.size() * sizeof(float4), &d_cf) &&
             upload(lay.pids.data(), lay.pids.size() * sizeof(uint2), &d_ct) &&
             upload(v4.data(), v4.size() * sizeof(float4), &d_v) && upload(t4.data(), t4.size() * sizeof(int4), &d_t) &&
-            upload(nrm.data(), nrm.size() * sizeof(float4), &d_n);
+            upload(nrm.data(), nrm.size() * sizeof(float4), &d_n) &&
+            upload(pl.data(), pl.size() * sizeof(double4), &d_p);
   if (!ok) {
     for (void* p : m->allocs) (void)hipFree(p);
     delete m;
@@ -257,6 +262,7 @@ b3d_status b3d_mesh_create(const float* verts, int32_t V, const int32_t* tris, i
   d.verts = (const float4*)d_v;
   d.tris = (const int4*)d_t;
   d.normals = (const float4*)d_n;
+  d.planes = (const double4*)d_p;
   d.n_clusters = m->n_clusters;
   m->n_drawn = lay.n_drawn;
   m->n_hidden = lay.n_hidden;

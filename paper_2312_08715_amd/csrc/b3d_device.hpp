@@ -35,8 +35,8 @@ struct Pose {
 // are close in space: primitives [pfirst, pfirst + np).  A primitive is the
 // triangle (a, b, c) and, when its second id is not kNoTri, the triangle
 // (a, c, d) sharing the edge a-c (a convex planar quad).  sphere = centre and
-// radius of a ball holding them; cone = unit axis and half-angle (radians) of
-// a cone holding their face normals (half-angle > pi/2 means "no bound").
+// radius of a ball holding them; cone = unit axis of a cone holding their face
+// normals and the sine of its half-angle plus a margin (above 1: no bound).
 // `alike` clusters hold parallelograms a, a + ab, a + ab + ad, a + ad that
 // share their edge vectors up to the rounding of the vertices: the faces of
 // equal voxels.
@@ -56,6 +56,7 @@ struct MeshDev {
   const float4* verts;         // caller's vertices
   const int4* tris;            // caller's triangles (w unused)
   const float4* normals;       // object-frame (v1 - v0) x (v2 - v0)
+  const double4* planes;       // the same in double, and its product with v0
   int n_clusters, n_visible;
   int has_big;                 // some primitive spans over 1/8 of the bounds' diagonal (table tops, walls)
   int T;                       // triangles
@@ -124,31 +125,23 @@ __device__ __forceinline__ Rect grow_clip(const Rect& r, int m, int W, int H) {
   return o;
 }
 
-// Bounds of the projections of the 8 corners of the box [lo, hi] (camera
-// frame after pose P when `posed`, else already camera-frame corners).
-// Returns false when a corner is not in front of the near plane.
-__device__ __forceinline__ bool project_box(const Pose& P, const float* lo, const float* hi, bool posed, const Cam& cam,
-                                            float* b) {
-  bool ok = true;
-  b[0] = 3.0e38f;
-  b[1] = -3.0e38f;
-  b[2] = 3.0e38f;
-  b[3] = -3.0e38f;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float x = (k & 1) ? hi[0] : lo[0];
-    const float y = (k & 2) ? hi[1] : lo[1];
-    const float z = (k & 4) ? hi[2] : lo[2];
-    const float3 c = posed ? xform(P, x, y, z) : make_float3(x, y, z);
-    ok = ok && (c.z > cam.znear);
-    const float iz = 1.0f / c.z;
-    const float u = cam.fx * c.x * iz + cam.cx, v = cam.fy * c.y * iz + cam.cy;
-    b[0] = fminf(b[0], u);
-    b[1] = fmaxf(b[1], u);
-    b[2] = fminf(b[2], v);
-    b[3] = fmaxf(b[3], v);
-  }
-  return ok;
+// Minimum and maximum of v over the lanes of each group of eight, in all of them.
+template <int CTRL>
+__device__ __forceinline__ float lane_swap(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float min8(float v) {
+  v = fminf(v, lane_swap<0xB1>(v));     // lanes 1 apart
+  v = fminf(v, lane_swap<0x4E>(v));     // lanes 2 apart
+  return fminf(v, lane_swap<0x141>(v));  // the other quad of the eight
+}
+__device__ __forceinline__ float max8(float v) {
+  v = fmaxf(v, lane_swap<0xB1>(v));
+  v = fmaxf(v, lane_swap<0x4E>(v));
+  return fmaxf(v, lane_swap<0x141>(v));
+}
+__device__ __forceinline__ float uniform(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 // Range of x/z over a sphere (centre c, radius r) in front of the camera:
@@ -156,10 +149,10 @@ __device__ __forceinline__ bool project_box(const Pose& P, const float* lo, cons
 // (c_x - k c_z)^2 = r^2 (1 + k^2), i.e.
 // k = (c_x c_z -+ r sqrt(c_x^2 + c_z^2 - r^2)) / (c_z^2 - r^2).
 __device__ __forceinline__ void sphere_slopes(float cx, float cz, float r, float& k0, float& k1) {
-  const float den = cz * cz - r * r;
-  const float root = r * sqrtf(fmaxf(cx * cx + cz * cz - r * r, 0.0f));
-  k0 = (cx * cz - root) / den;
-  k1 = (cx * cz + root) / den;
+  const float iden = __builtin_amdgcn_rcpf(cz * cz - r * r);
+  const float root = r * __builtin_amdgcn_sqrtf(fmaxf(cx * cx + cz * cz - r * r, 0.0f));
+  k0 = (cx * cz - root) * iden;
+  k1 = (cx * cz + root) * iden;
 }
 
 // Conservative pixel rectangle of the object under pose P: the projection of
@@ -167,9 +160,15 @@ __device__ __forceinline__ void sphere_slopes(float cx, float cz, float r, float
 // of its bounding sphere (slightly enlarged against rounding), widened by one
 // pixel, clipped to the image.  The whole image when neither bound applies
 // (the box reaches the near plane and the sphere reaches the camera plane).
+// Every wave computes it with all lanes, eight of them sharing the box's
+// corners; the result is uniform.
 __device__ __forceinline__ Rect object_rect(const MeshDev& m, const Pose& P, const Cam& cam) {
-  float a[4], b[4];
-  const bool aok = project_box(P, m.lo, m.hi, true, cam, a);
+  const int k8 = threadIdx.x & 7;
+  const float3 q = xform(P, (k8 & 1) ? m.hi[0] : m.lo[0], (k8 & 2) ? m.hi[1] : m.lo[1], (k8 & 4) ? m.hi[2] : m.lo[2]);
+  const bool aok = __ballot(!(q.z > cam.znear)) == 0ull;
+  const float iz = __builtin_amdgcn_rcpf(q.z);
+  const float u = cam.fx * q.x * iz + cam.cx, v = cam.fy * q.y * iz + cam.cy;
+  const float a[4] = {min8(u), max8(u), min8(v), max8(v)};
   const float3 c = xform(P, m.sphere[0], m.sphere[1], m.sphere[2]);
   const float rad = m.sphere[3] * 1.0001f + 1e-6f;
   const bool sok = c.z - rad > cam.znear;
@@ -181,6 +180,7 @@ __device__ __forceinline__ Rect object_rect(const MeshDev& m, const Pose& P, con
     r.y1 = cam.H;
     return r;
   }
+  float b[4];
   if (sok) {
     float k0, k1;
     sphere_slopes(c.x, c.z, rad, k0, k1);
@@ -203,91 +203,98 @@ __device__ __forceinline__ Rect object_rect(const MeshDev& m, const Pose& P, con
   const float fx1 = fminf(floorf(b[1] - 0.5f) + 2.0f, (float)cam.W);
   const float fy0 = fmaxf(ceilf(b[2] - 0.5f) - 1.0f, 0.0f);
   const float fy1 = fminf(floorf(b[3] - 0.5f) + 2.0f, (float)cam.H);
-  r.x0 = (int)fminf(fx0, (float)cam.W);
-  r.x1 = (int)fmaxf(fx1, fx0);
-  r.y0 = (int)fminf(fy0, (float)cam.H);
-  r.y1 = (int)fmaxf(fy1, fy0);
+  r.x0 = __builtin_amdgcn_readfirstlane((int)fminf(fx0, (float)cam.W));
+  r.x1 = __builtin_amdgcn_readfirstlane((int)fmaxf(fx1, fx0));
+  r.y0 = __builtin_amdgcn_readfirstlane((int)fminf(fy0, (float)cam.H));
+  r.y1 = __builtin_amdgcn_readfirstlane((int)fmaxf(fy1, fy0));
   if (r.x1 > cam.W) r.x1 = cam.W;
   if (r.y1 > cam.H) r.y1 = cam.H;
   return r;
 }
 
-// Depth of pixel (r, c) on the plane of triangle `id` under pose P: the ray
-// z d meets the plane n.(x - c0) = 0 at z = (n.c0)/(n.d), with
-// c_k = R v_k + t and n = (c1 - c0) x (c2 - c0), all in double precision.
-// The rasteriser's interpolated 1/z decides visibility; this value is the
-// depth reported and scored.  (For a triangle seen nearly edge-on the depth
-// is ill-conditioned in the vertex coordinates, and single precision would
-// put errors of several micrometres into the point and its gradient.)
-__device__ __forceinline__ float plane_depth(const MeshDev& m, const Pose& P, const Cam& cam, uint32_t id, int r,
-                                             int c) {
-  const int4 tr = m.tris[id];
-  const float4 v[3] = {m.verts[tr.x], m.verts[tr.y], m.verts[tr.z]};
-  double q[3][3];
+// What the plane depth of a pixel needs of a pose and a camera, in double:
+// the cofactors of R (normals turn with them, whatever R's rounding), det R,
+// t, and the reciprocal focal lengths.  The kernels that rasterise keep it in
+// LDS (kPlaneViewBytes): 34 registers less across the rasteriser.
+struct PlaneView {
+  double c[9], det, t[3], ifx, ify, cx, cy;
+};
+constexpr size_t kPlaneViewBytes = sizeof(PlaneView);
+
+__device__ __forceinline__ PlaneView plane_view(const Pose& P, const Cam& cam) {
+  PlaneView v;
+  const double r[9] = {P.r[0], P.r[1], P.r[2], P.r[3], P.r[4], P.r[5], P.r[6], P.r[7], P.r[8]};
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-      q[k][i] = (double)P.r[3 * i] * v[k].x + (double)P.r[3 * i + 1] * v[k].y + (double)P.r[3 * i + 2] * v[k].z +
-                (double)P.t[i];
-  const double e1[3] = {q[1][0] - q[0][0], q[1][1] - q[0][1], q[1][2] - q[0][2]};
-  const double e2[3] = {q[2][0] - q[0][0], q[2][1] - q[0][1], q[2][2] - q[0][2]};
-  const double n[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
-  const double dx = ((double)c + 0.5 - (double)cam.cx) / (double)cam.fx;
-  const double dy = ((double)r + 0.5 - (double)cam.cy) / (double)cam.fy;
-  return (float)((n[0] * q[0][0] + n[1] * q[0][1] + n[2] * q[0][2]) / (n[0] * dx + n[1] * dy + n[2]));
+  for (int i = 0; i < 3; ++i) {
+    const double *a = r + 3 * ((i + 1) % 3), *b = r + 3 * ((i + 2) % 3);
+    v.c[3 * i] = a[1] * b[2] - a[2] * b[1];
+    v.c[3 * i + 1] = a[2] * b[0] - a[0] * b[2];
+    v.c[3 * i + 2] = a[0] * b[1] - a[1] * b[0];
+    v.t[i] = P.t[i];
+  }
+  v.det = r[0] * v.c[0] + r[1] * v.c[1] + r[2] * v.c[2];
+  v.ifx = 1.0 / (double)cam.fx;
+  v.ify = 1.0 / (double)cam.fy;
+  v.cx = (double)cam.cx - 0.5;
+  v.cy = (double)cam.cy - 0.5;
+  return v;
 }
 
-// Replace the depth of every band pixel drawn by this mesh (id - id_base in
-// [0, T)) by plane_depth, keeping its id.  Whole block; ends with a barrier.
-__device__ __forceinline__ void refine_depths(const MeshDev& m, const Pose& P, const Cam& cam, uint32_t id_base,
-                                              const Rect& band, unsigned long long* zbuf) {
-  const int pitch = band.w();
-  const int np = band.h() * pitch;
-  for (int k = threadIdx.x; k < np; k += kBlock) {
-    const unsigned long long key = zbuf[k];
-    if (key == kEmptyKey) continue;
-    const uint32_t id = key_id(key) - id_base;
-    if (id >= (uint32_t)m.T) continue;
-    const int r = band.y0 + k / pitch, c = band.x0 + (k - (k / pitch) * pitch);
-    zbuf[k] = pack_key(plane_depth(m, P, cam, id, r, c), key_id(key));
-  }
-  __syncthreads();
+// Depth of pixel (r, c) on the plane of triangle `id`: the ray z d meets the
+// plane n.(x - c0) = 0 at z = (n.c0)/(n.d), with c_k = R v_k + t and
+// n = (c1 - c0) x (c2 - c0) = cof(R) n_o, n.c0 = det(R) n_o.v0 + n.t, all in
+// double precision.  The rasteriser's interpolated 1/z decides visibility;
+// this value is the depth reported and scored.  (For a triangle seen nearly
+// edge-on the depth is ill-conditioned in the vertex coordinates, and single
+// precision would put errors of several micrometres into the point and its
+// gradient.)  The quotient takes the hardware reciprocal and two Newton steps,
+// far below the rounding of the result to single precision.
+__device__ __forceinline__ float plane_depth(const MeshDev& m, const PlaneView& v, uint32_t id, int r, int c) {
+  const double4 o = m.planes[id];
+  const double nx = v.c[0] * o.x + v.c[1] * o.y + v.c[2] * o.z;
+  const double ny = v.c[3] * o.x + v.c[4] * o.y + v.c[5] * o.z;
+  const double nz = v.c[6] * o.x + v.c[7] * o.y + v.c[8] * o.z;
+  const double top = v.det * o.w + nx * v.t[0] + ny * v.t[1] + nz * v.t[2];
+  const double den = nx * (((double)c - v.cx) * v.ifx) + ny * (((double)r - v.cy) * v.ify) + nz;
+  double y = __builtin_amdgcn_rcp(den);
+  y = __builtin_fma(y, __builtin_fma(-den, y, 1.0), y);
+  y = __builtin_fma(y, __builtin_fma(-den, y, 1.0), y);
+  return (float)(top * y);
 }
 
 // Whether a cluster can draw into `band` under pose P: false when its
 // sphere lies behind the near plane, when every normal of its cone faces away
-// from every point of its sphere (the angle between the cone axis and the
-// direction to the sphere centre, plus the cone's and the sphere's angular
-// radii, stays below a right angle by a margin), or when the sphere's screen
-// box misses the band.  Uniform across the block.
-// When it may draw and its sphere lies in front of the near plane, box[4]
-// receives the sphere's screen box (umin, umax, vmin, vmax) and *zmin the
-// depth of its nearest point; otherwise *zmin = 0.
+// from every point of its sphere, or when the sphere's screen box misses the
+// band.  With th the angle between the cone's axis a and the direction to the
+// sphere's centre s (at distance d) and ph = asin(r/d) the sphere's angular
+// radius, all face away when th + ph + half-angle stays below a right angle:
+// cos(th + ph) > sin(half-angle), times d^2.
 __device__ __forceinline__ bool cluster_may_draw(const ClusterDev& c, const Pose& P, const Cam& cam,
-                                                 const Rect& band, float* box, float* zmin) {
+                                                 const Rect& band) {
   const float3 s = xform(P, c.sphere.x, c.sphere.y, c.sphere.z);
   const float r = c.sphere.w;
-  *zmin = 0.0f;
-  if (s.z + r <= cam.znear) return false;
+  const float znear = s.z - r, zfar = s.z + r;
+  if (zfar <= cam.znear) return false;
   const float d2 = s.x * s.x + s.y * s.y + s.z * s.z;
-  if (c.cone.w < 1.5f && d2 > r * r) {
+  const float g2 = d2 - r * r;
+  if (c.cone.w < 1.0f && g2 > 0.0f) {
     const float3 a = rotate(P, c.cone.x, c.cone.y, c.cone.z);
-    const float d = sqrtf(d2);
-    const float ct = fminf(1.0f, fmaxf(-1.0f, (a.x * s.x + a.y * s.y + a.z * s.z) / d));
-    if (acosf(ct) + c.cone.w + asinf(fminf(1.0f, r / d)) < 1.5707963f - 2e-3f) return false;
-  }
-  if (s.z - r > cam.znear) {
-    const float lo[3] = {s.x - r, s.y - r, s.z - r}, hi[3] = {s.x + r, s.y + r, s.z + r};
-    project_box(P, lo, hi, false, cam, box);
-    if (box[1] < (float)band.x0 - 1.0f || box[0] > (float)band.x1 + 1.0f || box[3] < (float)band.y0 - 1.0f ||
-        box[2] > (float)band.y1 + 1.0f)
+    const float as = a.x * s.x + a.y * s.y + a.z * s.z;
+    if (as * __builtin_amdgcn_sqrtf(g2) - r * __builtin_amdgcn_sqrtf(fmaxf(d2 - as * as, 0.0f)) > c.cone.w * d2)
       return false;
-    *zmin = s.z - r;
+  }
+  if (znear > cam.znear) {
+    // the box around the sphere, its nearer or farther face whichever bounds
+    const float in = __builtin_amdgcn_rcpf(znear), ifr = __builtin_amdgcn_rcpf(zfar);
+    const float x0 = s.x - r, x1 = s.x + r, y0 = s.y - r, y1 = s.y + r;
+    const float u0 = cam.fx * x0 * (x0 < 0.0f ? in : ifr) + cam.cx, u1 = cam.fx * x1 * (x1 > 0.0f ? in : ifr) + cam.cx;
+    const float v0 = cam.fy * y0 * (y0 < 0.0f ? in : ifr) + cam.cy, v1 = cam.fy * y1 * (y1 > 0.0f ? in : ifr) + cam.cy;
+    if (u1 < (float)band.x0 - 1.0f || u0 > (float)band.x1 + 1.0f || v1 < (float)band.y0 - 1.0f ||
+        v0 > (float)band.y1 + 1.0f)
+      return false;
   }
   return true;
 }
-
 
 // Coverage of pixel (r, c) by triangle `id` decided in double precision with
 // exactly the operations, in the same order, of the plain definition
@@ -328,34 +335,42 @@ __device__ __forceinline__ bool covered_exact(const MeshDev& m, const Pose& P, c
 // fused kernel then reuses it for the window weights, which sets its size).
 struct RasterLds {
   uint2* queue;  // (band pixel, triangle id) pairs left for the exact test
-  int* list;     // drawable clusters of the current group of kBlock
-  int* counts;   // [0] queue fill, [1..kWaves] per-wave drawable counts, [kWaves + 1] next list entry
+  int* list;     // drawable clusters of the current group of one per thread
+  int* counts;   // [0] queue fill, [1..waves] per-wave drawable counts, [waves + 1] next list entry
   int qcap;
 };
 
+// The scratch of a block of BS threads: the queue, the list, the counts.
 constexpr int kQueueCap = 1536;
-constexpr size_t kRasterLdsBytes = sizeof(uint2) * kQueueCap + sizeof(int) * kBlock + sizeof(int) * 16;
+constexpr size_t raster_lds_bytes(int bs) {
+  return sizeof(uint2) * kQueueCap + sizeof(int) * bs + sizeof(int) * (bs > 256 ? 32 : 16);
+}
+constexpr size_t kRasterLdsBytes = raster_lds_bytes(kBlock);
 
 constexpr int kBigCentres = 64;  // a box of more centres than this is walked by the whole wave
 constexpr int kBigSlots = 2;     // such boxes a wave takes together per cluster
 constexpr int kStageWords = 36;  // words of one staged box
 // the staged boxes take the queue's last entries
-constexpr int kStageQueueEntries = (int)((sizeof(float) * kWaves * kBigSlots * kStageWords + 7) / 8);
-static_assert(kStageQueueEntries < kQueueCap / 4, "staging area too large for the exact-test queue");
+constexpr int stage_queue_entries(int bs) {
+  return (int)((sizeof(float) * (bs / 64) * kBigSlots * kStageWords + 7) / 8);
+}
+static_assert(stage_queue_entries(1024) < kQueueCap / 2, "staging area too large for the exact-test queue");
 
+template <int BS>
 __device__ __forceinline__ RasterLds carve_raster_lds(unsigned char* p) {
   RasterLds r;
   r.queue = reinterpret_cast<uint2*>(p);
   r.list = reinterpret_cast<int*>(r.queue + kQueueCap);
-  r.counts = r.list + kBlock;
+  r.counts = r.list + BS;
   r.qcap = kQueueCap;
   return r;
 }
 
 // Staging slots of the large-box walk (only meshes with large primitives use
-// them, with the queue shortened to kQueueCap - kStageQueueEntries).
+// them, with the queue shortened by their entries).
+template <int BS>
 __device__ __forceinline__ float* raster_stage(const RasterLds& r) {
-  return reinterpret_cast<float*>(r.queue + (kQueueCap - kStageQueueEntries));
+  return reinterpret_cast<float*>(r.queue + (kQueueCap - stage_queue_entries(BS)));
 }
 
 // Work counters of the counting instantiation (indices into a per-block
@@ -505,10 +520,7 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
   const float r0 = ceilf(fmaxf(vmin - tau, by0)), r1 = floorf(fminf(vmax + tau, by1));
   const bool has = act && c0 <= c1 && r0 <= r1;
   const float nc = has ? c1 - c0 : -1.0f, nr = has ? r1 - r0 : -1.0f;  // columns and rows less one
-  int Rm = 0, Cm = 0;
-  while (Rm <= kStepBox && __ballot((float)Rm <= nr) != 0ull) ++Rm;
-  while (Cm <= kStepBox && __ballot((float)Cm <= nc) != 0ull) ++Cm;
-  if (Rm > kStepBox || Cm > kStepBox) return false;
+  if (__ballot(fmaxf(nr, nc) >= (float)kStepBox) != 0ull) return false;
   if (COUNT && in) {
     c_work[kCntVert] += 4;
     c_work[kCntTri] += 2;
@@ -526,20 +538,24 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
   const float tq = eon ? 3.0e38f : tm;
   const uint32_t id1 = id_base + ids.x, id2 = id_base + ids.y;
   const int first = (int)((r0 - (float)buf.y0) * (float)pitch + (c0 - (float)buf.x0));  // exact below 2^24
-  for (int r = 0; r < Rm; ++r) {
+  for (int r = 0;; ++r) {
     const float dr = (float)r;
+    const bool row = dr <= nr;
+    if (__ballot(row) == 0ull) break;
     const float w0r = __builtin_fmaf(e0x, dr, w0b), w1r = __builtin_fmaf(e1x, dr, w1b);
     const float w2r = __builtin_fmaf(e2x, dr, w2b), v0r = __builtin_fmaf(f0x, dr, v0b);
     const float v1r = __builtin_fmaf(f1x, dr, v1b), izr = __builtin_fmaf(zr, dr, zb);
-    const float ncr = dr <= nr ? nc : -1.0f;
+    const float ncr = row ? nc : -1.0f;
     const int pixr = first + r * pitch;
-    for (int c = 0; c < Cm; ++c) {
+    for (int c = 0;; ++c) {
       const float dc = (float)c;
+      const bool col = dc <= ncr;
+      if (__ballot(col) == 0ull) break;
       const float w0 = __builtin_fmaf(-e0y, dc, w0r), w1 = __builtin_fmaf(-e1y, dc, w1r);
       const float w2 = __builtin_fmaf(-e2y, dc, w2r), v0 = __builtin_fmaf(-f0y, dc, v0r);
       const float v1 = __builtin_fmaf(-f1y, dc, v1r);
       const float side = fmaxf(fmaxf(fmaxf(w0, w2), v0), v1);
-      if (dc <= ncr && !(side > tq)) {
+      if (col && !(side > tq)) {
         const int pix = pixr + c;
         if (fmaxf(side, -fabsf(w1)) < -tq) {
           if (COUNT) ++c_work[kCntFrag];
@@ -570,7 +586,7 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
 // `band` of an LDS key buffer that covers the rectangle `buf` (row pitch
 // buf.w(); band inside buf).  Triangle ids written are
 // id_base + the caller's triangle index.  Clusters are tested for drawing,
-// kBlock at a time, and the drawable ones compacted into a list; the four
+// one per thread at a time, and the drawable ones compacted into a list; the
 // waves then take clusters from the list independently: a wave transforms
 // its cluster's vertices into its own LDS buffer and each lane takes one
 // primitive (a quad or a triangle), walking the pixel centres of its screen
@@ -580,39 +596,37 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
 // precision places clearly inside all three edges is written at once (64-bit
 // atomicMin of the packed depth/id key); one that lies within a rounding
 // margin of an edge, or any centre of a triangle seen nearly edge-on, is
-// queued and decided afterwards by covered_exact.  Must be called by the whole
-// block; ends after a barrier with the buffer complete.
-template <bool COUNT, bool BIG>
+// queued and decided afterwards by covered_exact (its depth from *view, the
+// pose's plane view in LDS).  Must be called by the whole block; ends after a barrier with the buffer complete.
+template <bool COUNT, bool BIG, int BS>
 __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, const Cam& cam, uint32_t id_base,
                                             const Rect& band, const Rect& buf, unsigned long long* zbuf,
-                                            const RasterLds& lds, unsigned* cnt = nullptr) {
+                                            const RasterLds& lds, const PlaneView* view, unsigned* cnt = nullptr) {
   unsigned c_vert = 0, c_tri = 0, c_setup = 0, c_frag = 0, c_exact = 0;
   unsigned c_alike[kCntN] = {};  // raster_alike's share
   const int pitch = buf.w();
   const float bx0 = (float)band.x0, bx1 = (float)(band.x1 - 1);
   const float by0 = (float)band.y0, by1 = (float)(band.y1 - 1);
   if (threadIdx.x == 0) lds.counts[0] = 0;
-  // the hidden-pair clusters matter only when the object reaches the near plane
-  bool straddle = false;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float3 c = xform(P, (k & 1) ? m.hi[0] : m.lo[0], (k & 2) ? m.hi[1] : m.lo[1], (k & 4) ? m.hi[2] : m.lo[2]);
-    straddle = straddle || !(c.z > cam.znear);
-  }
-  const int n_clusters = straddle ? m.n_clusters : m.n_visible;
+  // the hidden-pair clusters matter only when the object reaches the near
+  // plane: the z of the box's corners, eight lanes sharing them
+  const int k8 = threadIdx.x & 7;
+  const float3 corner =
+      xform(P, (k8 & 1) ? m.hi[0] : m.lo[0], (k8 & 2) ? m.hi[1] : m.lo[1], (k8 & 4) ? m.hi[2] : m.lo[2]);
+  const int n_clusters = __ballot(!(corner.z > cam.znear)) != 0ull ? m.n_clusters : m.n_visible;
+  constexpr int kW = BS / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int base = 0; base < n_clusters; base += kBlock) {
+  for (int base = 0; base < n_clusters; base += BS) {
     // each thread tests one cluster; the drawable ones are compacted into `list`
     const int mine = base + threadIdx.x;
-    float box[4], zmin;
-    const bool draw = mine < n_clusters && cluster_may_draw(m.clusters[mine], P, cam, band, box, &zmin);
+    const bool draw = mine < n_clusters && cluster_may_draw(m.clusters[mine], P, cam, band);
     const unsigned long long mask = __ballot(draw);
     __syncthreads();  // the previous group's list is no longer read
     if (lane == 0) lds.counts[1 + wave] = __popcll(mask);
-    if (threadIdx.x == 0) lds.counts[1 + kWaves] = 0;
+    if (threadIdx.x == 0) lds.counts[1 + kW] = 0;
     __syncthreads();
     int off = 0, total = 0;
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < kW; ++w) {
       off += (w < wave) ? lds.counts[1 + w] : 0;
       total += lds.counts[1 + w];
     }
@@ -620,7 +634,7 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
     __syncthreads();
     for (;;) {
       int q = 0;
-      if (lane == 0) q = atomicAdd(&lds.counts[1 + kWaves], 1);
+      if (lane == 0) q = atomicAdd(&lds.counts[1 + kW], 1);
       q = __shfl(q, 0, 64);
       if (q >= total) break;
       const ClusterDev cl = m.clusters[__builtin_amdgcn_readfirstlane(lds.list[q])];
@@ -699,7 +713,7 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
           const unsigned long long bigm = BIG ? __ballot(n_cent > kBigCentres) : 0ull;
           if (BIG && bigm != 0ull && n_cent > kBigCentres && __popcll(bigm & ((1ull << lane) - 1ull)) < kBigSlots) {
             const int rank = __popcll(bigm & ((1ull << lane) - 1ull));
-            float* st = raster_stage(lds) + (wave * kBigSlots + rank) * kStageWords;
+            float* st = raster_stage<BS>(lds) + (wave * kBigSlots + rank) * kStageWords;
             int* si = reinterpret_cast<int*>(st);
             const float vals[26] = {e0x, e0y, e1x, e1y, e2x, e2y, f0x, f0y, f1x, f1y, t0,  t1,  t2,
                                     s0,  s1,  ia1, ia2, w0b, w1b, w2b, v0b, v1b, A.w, B.w, C.w, D.w};
@@ -750,7 +764,7 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
         if (sm != 0ull) {
           const int n_staged = __popcll(sm);
           for (int j = 0; j < n_staged; ++j)
-            walk_staged<COUNT>(raster_stage(lds) + (wave * kBigSlots + j) * kStageWords, lane, buf, pitch, id_base,
+            walk_staged<COUNT>(raster_stage<BS>(lds) + (wave * kBigSlots + j) * kStageWords, lane, buf, pitch, id_base,
                                zbuf, lds, c_frag);
         }
       }
@@ -759,12 +773,12 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
   __syncthreads();
   // centres near an edge: the exact test, then the plane depth
   const int nq = min(lds.counts[0], lds.qcap);
-  for (int k = threadIdx.x; k < nq; k += kBlock) {
+  for (int k = threadIdx.x; k < nq; k += BS) {
     const uint2 e = lds.queue[k];
     const int r = buf.y0 + (int)e.x / pitch, col = buf.x0 + (int)e.x % pitch;
     if (COUNT) ++c_exact;
     if (!covered_exact(m, P, cam, e.y, r, col)) continue;
-    const float z = plane_depth(m, P, cam, e.y, r, col);
+    const float z = plane_depth(m, *view, e.y, r, col);
     if (!(z > 0.0f)) continue;
     if (COUNT) ++c_frag;
     atomicMin(&zbuf[e.x], pack_key(z, id_base + e.y));
@@ -784,24 +798,65 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
 // walk costs meshes without large primitives a few per cent).
 enum RasterMode { kRasterSmall = 0, kRasterBig = 1, kRasterAny = 2 };
 
-template <bool COUNT, int MODE>
+template <bool COUNT, int MODE, int BS>
 __device__ __forceinline__ void raster_mesh_mode(const MeshDev& m, const Pose& P, const Cam& cam, uint32_t id_base,
                                                  const Rect& band, const Rect& buf, unsigned long long* zbuf,
-                                                 const RasterLds& lds, unsigned* cnt = nullptr) {
+                                                 const RasterLds& lds, const PlaneView* view,
+                                                 unsigned* cnt = nullptr) {
   if (MODE == kRasterBig || (MODE == kRasterAny && m.has_big)) {
     RasterLds shorter = lds;
-    shorter.qcap = kQueueCap - kStageQueueEntries;
-    raster_mesh<COUNT, true>(m, P, cam, id_base, band, buf, zbuf, shorter, cnt);
+    shorter.qcap = kQueueCap - stage_queue_entries(BS);
+    raster_mesh<COUNT, true, BS>(m, P, cam, id_base, band, buf, zbuf, shorter, view, cnt);
   } else {
-    raster_mesh<COUNT, false>(m, P, cam, id_base, band, buf, zbuf, lds, cnt);
+    raster_mesh<COUNT, false, BS>(m, P, cam, id_base, band, buf, zbuf, lds, view, cnt);
   }
 }
 
-template <bool COUNT = false>
-__device__ __forceinline__ void raster_mesh_any(const MeshDev& m, const Pose& P, const Cam& cam, uint32_t id_base,
-                                                const Rect& band, const Rect& buf, unsigned long long* zbuf,
-                                                const RasterLds& lds, unsigned* cnt = nullptr) {
-  raster_mesh_mode<COUNT, kRasterAny>(m, P, cam, id_base, band, buf, zbuf, lds, cnt);
+// Row r and column c of slot k (0 <= k < 2^20) of a rectangle of width w,
+// given inv_w = 1/w correctly rounded: (k + 1/2) inv_w is formed with one
+// rounding, a relative error below 2^-22, so it lies within 1/(4w) of
+// (k + 1/2)/w, whose fractional part is in [1/(2w), 1 - 1/(2w)]: truncating it
+// gives floor(k/w) exactly, with no integer division.
+__device__ __forceinline__ void row_col(int k, int w, float inv_w, int& r, int& c) {
+  r = (int)__builtin_fmaf((float)k, inv_w, 0.5f * inv_w);
+  c = k - __mul24(r, w);
+}
+
+// Work compaction inside a wave: of the items 0 .. n - 1 (64 consecutive ones
+// per wave and turn, wave w of NW taking turns w, w + NW, ...) those that are
+// `wanted` are processed 64 at a time, one per lane, so that a wave does not
+// run long work for a few lanes.  Indices wait in the wave's own LDS queue q
+// (kWaveQueue entries): no barrier.  Called by whole waves; `wanted` and
+// process(index, active) run with all lanes.
+constexpr int kWaveQueue = 128;
+
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
+template <int NW, class W, class F>
+__device__ __forceinline__ void wave_compacted(int n, unsigned short* q, W&& wanted, F&& process) {
+  const int lane = threadIdx.x & 63;
+  int base = __builtin_amdgcn_readfirstlane(((int)threadIdx.x >> 6) * 64);
+  int head = 0, fill = 0;  // the ring's first entry and its number of entries
+  for (;;) {
+    while (fill < 64 && base < n) {
+      const int item = base + lane;
+      const bool want = item < n && wanted(item);
+      const unsigned long long m = __ballot(want);
+      if (want) q[(head + fill + lanes_below(m)) & (kWaveQueue - 1)] = (unsigned short)item;
+      fill += __popcll(m);
+      base += NW * 64;
+    }
+    if (fill <= 0) break;
+    __builtin_amdgcn_wave_barrier();
+    const int item = q[(head + lane) & (kWaveQueue - 1)];
+    const bool act = lane < fill;
+    head += 64;
+    fill -= 64;
+    __builtin_amdgcn_wave_barrier();
+    process(item, act);
+  }
 }
 
 // One Adam ascent step on logL for pose P (row-major 4x4), on the tangent

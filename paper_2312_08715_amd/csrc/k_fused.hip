@@ -16,6 +16,7 @@
 // When the rectangle does not fit the LDS budget it is processed in bands of
 // rows, re-rasterising per band.
 #include "b3d_launch.hpp"
+#include <algorithm>
 #include <type_traits>
 
 namespace b3d {
@@ -30,42 +31,61 @@ __device__ __forceinline__ double rect_sum(const double* sat, int W, const Rect&
          sat[(size_t)r.y0 * p + r.x0];
 }
 
-// LDS: rasteriser scratch (once the depth buffer is complete: the window
-// weights, then the drawn-pixel list) | depth keys [zcap] | reduction [64] |
-// ray tables of columns [-2h, W + 2h) and rows [-2h, H + 2h).
-size_t fused_lds_bytes(const SceneDev& s) {
-  return kRasterLdsBytes + sizeof(float) * (64 + s.cam.W + s.cam.H + 8 * s.sc.h) + kFusedBytesPerKey * (size_t)s.zcap;
+// LDS of a block of bs threads: rasteriser scratch (once the depth buffer is
+// complete: the window weights and the waves' queues) | depth keys [zcap] |
+// plane view (64 floats) | ray tables of columns [-2h, W + 2h) and rows [-2h, H + 2h).
+static size_t fused_lds_bytes(const SceneDev& s, int bs, int zcap) {
+  return raster_lds_bytes(bs) + sizeof(float) * (64 + s.cam.W + s.cam.H + 8 * s.sc.h) + kFusedBytesPerKey * (size_t)zcap;
+}
+size_t fused_lds_bytes(const SceneDev& s) { return fused_lds_bytes(s, kBlock, s.zcap); }
+
+// Bytes beyond these that the adjoint of a wide image needs: its window
+// weights for one row and the halo, and the waves' queues, exceed the scratch
+// only there.
+__host__ __device__ __forceinline__ int weight_bytes(int bs, int W, int h) {
+  return 4 * (2 * h + 1) * W + 2 * kWaveQueue * (bs / 64);
+}
+static size_t launch_lds_bytes(const SceneDev& s, int bs, int zcap, bool grad) {
+  const int over = grad ? weight_bytes(bs, s.cam.W, s.sc.h) - (int)raster_lds_bytes(bs) : 0;
+  return fused_lds_bytes(s, bs, zcap) + (over > 0 ? 2 * kWaveQueue * (bs / 64) : 0);
 }
 
-// One round of block-wide stream compaction: the threads whose flag is set
-// append their value to list[n ...] in thread order; returns how many did.
-// Whole block; `wcnt` holds kWaves ints of LDS.
-__device__ __forceinline__ int append_flagged(bool flag, int value, unsigned short* __restrict__ list, int n,
-                                              int* wcnt) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const unsigned long long m = __ballot(flag);
-  if (lane == 0) wcnt[wave] = __popcll(m);
-  __syncthreads();
-  int off = n, sum = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    off += w < wave ? wcnt[w] : 0;
-    sum += wcnt[w];
-  }
-  if (flag) list[off + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)value;
-  __syncthreads();
-  return sum;
+// Sums over the block of NV doubles per thread, in a fixed order: quads of
+// lanes, then 16 lanes per value.  Afterwards thread t < 16 NV holds the total
+// of value t / 16.  `red`: NV * BS / 4 doubles of LDS.  Whole block; starts
+// with a barrier.  (The terms are single precision; summed in double, their
+// grouping over threads, bands and block sizes moves a total by parts in 2^50,
+// which its rounding to single precision does not show.)
+template <int CTRL>
+__device__ __forceinline__ double lane_swap(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
 }
 
-// Row-major list of the buffer slots [k0, k1) that hold a surface of the mesh
-// (triangle id < T); returns its length.  Whole block.
-__device__ __forceinline__ int list_drawn(const unsigned long long* __restrict__ zbuf, int k0, int k1, uint32_t T,
-                                          unsigned short* __restrict__ list, int* wcnt) {
-  int n = 0;
-  for (int base = k0; base < k1; base += kBlock) {
-    const int k = base + (int)threadIdx.x;
-    n += append_flagged(k < k1 && key_id(zbuf[k]) < T, k, list, n, wcnt);
+template <int NV, int BS>
+__device__ __forceinline__ double block_total(const double (&v)[NV], double* red) {
+  static_assert(16 * NV <= BS, "one group of 16 threads per value");
+  const int t = threadIdx.x;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    double x = v[k];
+    x += lane_swap<0xB1>(x);
+    x += lane_swap<0x4E>(x);
+    if ((t & 3) == 0) red[k * (BS / 4) + (t >> 2)] = x;
   }
-  return n;
+  __syncthreads();
+  double x = 0.0;
+  if (t < 16 * NV) {
+    const double* p = red + (t >> 4) * (BS / 4) + (t & 15);
+#pragma unroll
+    for (int i = 0; i < BS / 64; ++i) x += p[16 * i];
+  }
+  x += lane_swap<0xB1>(x);
+  x += lane_swap<0x4E>(x);
+  x += lane_swap<0x141>(x);
+  x += lane_swap<0x140>(x);
+  return x;
 }
 
 // Window sums for observed point (ox, oy, oz) at pixel (r, c) over the LDS
@@ -198,16 +218,6 @@ __device__ __forceinline__ float window_grad(const float* __restrict__ wbuf, int
   return g;
 }
 
-// Row r and column c of slot k (0 <= k < 2^20) of a rectangle of width w,
-// given inv_w = 1/w correctly rounded: (k + 1/2) inv_w is formed with one
-// rounding, a relative error below 2^-22, so it lies within 1/(4w) of
-// (k + 1/2)/w, whose fractional part is in [1/(2w), 1 - 1/(2w)]: truncating it
-// gives floor(k/w) exactly, with no integer division.
-__device__ __forceinline__ void row_col(int k, int w, float inv_w, int& r, int& c) {
-  r = (int)__builtin_fmaf((float)k, inv_w, 0.5f * inv_w);
-  c = k - __mul24(r, w);
-}
-
 // First local index k >= 0 with (base + k) mod kBlock == t.
 __device__ __forceinline__ int first_of(unsigned t, int base) {
   return ((int)t - base % kBlock + kBlock) % kBlock;
@@ -217,66 +227,86 @@ __device__ __forceinline__ int first_of(unsigned t, int base) {
 // columns possibly beyond the image, which stay empty) initialised from the
 // background keys, the mesh rasterised into its image part, then the depth of
 // every slot the mesh drew recomputed on its triangle's plane.  Whole block.
-template <bool COUNT, int RM = kRasterAny>
+template <bool COUNT, int RM, int BS>
 __device__ __forceinline__ void raster_band(const SceneDev& s, const Pose& P, const Rect& L,
-                                            unsigned long long* zbuf, unsigned char* smem, float* red, unsigned* cnt) {
+                                            unsigned long long* zbuf, unsigned char* smem, unsigned* cnt) {
+  const PlaneView* view = reinterpret_cast<const PlaneView*>(zbuf + s.zcap);
   const Cam& cam = s.cam;
   const int H = cam.H, W = cam.W, lw = L.w();
   const int nk = L.h() * lw;
   const float inv_lw = 1.0f / (float)lw;
-  for (int k = threadIdx.x; k < nk; k += kBlock) {
-    int r, c;
-    row_col(k, lw, inv_lw, r, c);
-    r += L.y0;
-    c += L.x0;
-    const bool in = r >= 0 && r < H && c >= 0 && c < W;
-    zbuf[k] = (in && s.bg) ? s.bg[(size_t)r * W + c] : kEmptyKey;
+  if (s.bg) {
+    for (int k = threadIdx.x; k < nk; k += BS) {
+      int r, c;
+      row_col(k, lw, inv_lw, r, c);
+      r += L.y0;
+      c += L.x0;
+      const bool in = r >= 0 && r < H && c >= 0 && c < W;
+      zbuf[k] = in ? s.bg[(size_t)r * W + c] : kEmptyKey;
+    }
+  } else {
+    ulonglong2* z2 = reinterpret_cast<ulonglong2*>(zbuf);
+    for (int k = threadIdx.x; k < nk / 2; k += BS) z2[k] = make_ulonglong2(kEmptyKey, kEmptyKey);
+    if ((nk & 1) && threadIdx.x == 0) zbuf[nk - 1] = kEmptyKey;
   }
   __syncthreads();
-  raster_mesh_mode<COUNT, RM>(s.mesh, P, cam, 0u, grow_clip(L, 0, W, H), L, zbuf, carve_raster_lds(smem), cnt);
-  // the slots this mesh drew (listed in the free scratch, which holds more
-  // entries than the buffer has slots), then their depths on the planes
-  unsigned short* rlist = reinterpret_cast<unsigned short*>(smem);
-  const int nr = list_drawn(zbuf, 0, nk, (uint32_t)s.mesh.T, rlist, reinterpret_cast<int*>(red));
-  for (int k = threadIdx.x; k < nr; k += kBlock) {
-    const int off = rlist[k];
-    const unsigned long long key = zbuf[off];
-    int r, c;
-    row_col(off, lw, inv_lw, r, c);
-    zbuf[off] = pack_key(plane_depth(s.mesh, P, cam, key_id(key), L.y0 + r, L.x0 + c), key_id(key));
-  }
+  raster_mesh_mode<COUNT, RM, BS>(s.mesh, P, cam, 0u, grow_clip(L, 0, W, H), L, zbuf, carve_raster_lds<BS>(smem), view,
+                                  cnt);
+  // the slots this mesh drew, compacted wave by wave (their queues in the free
+  // scratch): their depths on the triangles' planes
+  const uint32_t T = (uint32_t)s.mesh.T;
+  wave_compacted<BS / 64>(
+      nk, reinterpret_cast<unsigned short*>(smem) + (threadIdx.x >> 6) * kWaveQueue,
+      [&](int k) { return key_id(zbuf[k]) < T; },
+      [&](int k, bool act) {
+        if (!act) return;
+        const unsigned long long key = zbuf[k];
+        int r, c;
+        row_col(k, lw, inv_lw, r, c);
+        zbuf[k] = pack_key(plane_depth(s.mesh, *view, key_id(key), L.y0 + r, L.x0 + c), key_id(key));
+      });
   __syncthreads();
 }
 
 // One hypothesis: pose16 (16 floats), writes *logL_out and, when GRAD,
-// grad_out[0..8).  Must be called by the whole block; `smem` is at least
-// fused_lds_bytes(s).
-template <bool GRAD, bool COUNT = false, int RM = kRasterAny>
+// grad_out[0..8).  Must be called by the whole block of BS threads; `smem` is
+// at least the fused LDS size for BS and s.zcap.
+// What bounds it is VALU issue (about 90 % of the issue slots at 5,000
+// hypotheses of 160x120); so work common to the block is shared between lanes,
+// the observed pixels without a point (44 % of the region there) and the slots
+// the mesh did not draw are compacted away inside each wave, and terms are
+// summed in double, which leaves the assignment of pixels to lanes free.  (5,000
+// hypotheses of 2,000 voxels at 160x120 with the adjoint: 400 us against 429
+// with every wave computing the block's bounds, block-wide lists and one lane
+// per observed pixel.)
+template <bool GRAD, bool COUNT = false, int RM = kRasterAny, int BS = kBlock>
 __device__ __forceinline__ void render_score_one(const SceneDev& s, const float* __restrict__ pose16,
                                                  float* __restrict__ logL_out, float* __restrict__ grad_out,
                                                  unsigned char* smem, unsigned* cnt = nullptr, int row_lo = -1,
                                                  int row_hi = -1) {
+  static_assert(kPlaneViewBytes <= 64 * sizeof(float), "the plane view's share of LDS");
+  constexpr int kScratch = (int)raster_lds_bytes(BS), NW = BS / 64, NV = GRAD ? 9 : 1;
   unsigned c_pair = 0, c_obs = 0, c_adj = 0;
   float* wbuf = reinterpret_cast<float*>(smem);  // after rasterisation
-  unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kRasterLdsBytes);
-  float* red = reinterpret_cast<float*>(zbuf + s.zcap);
+  unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kScratch);
 
   const Cam& cam = s.cam;
   const ScoreConsts& sc = s.sc;
   const int H = cam.H, W = cam.W, h = sc.h;
   // ray tables indexed by column in [-2h, W + 2h) and row in [-2h, H + 2h)
-  float* dxt = red + 64 + 2 * h;
+  float* dxt = reinterpret_cast<float*>(zbuf + s.zcap) + 64 + 2 * h;
   float* dyt = dxt + W + 4 * h;
   const Pose P = load_pose(pose16);
-  for (int i = (int)threadIdx.x - 2 * h; i < W + 2 * h; i += kBlock) dxt[i] = ray_x(cam, i);
-  for (int i = (int)threadIdx.x - 2 * h; i < H + 2 * h; i += kBlock) dyt[i] = ray_y(cam, i);
+  for (int i = (int)threadIdx.x - 2 * h; i < W + 2 * h; i += BS) dxt[i] = ray_x(cam, i);
+  for (int i = (int)threadIdx.x - 2 * h; i < H + 2 * h; i += BS) dyt[i] = ray_y(cam, i);
+  if (threadIdx.x == BS - 1) *reinterpret_cast<PlaneView*>(zbuf + s.zcap) = plane_view(P, cam);
 
   const Rect obj = object_rect(s.mesh, P, cam);
   // observed pixels whose window can see the object (none when nothing is drawn)
   Rect region = grow_clip(obj, h, W, H);
   if (obj.empty()) region.x1 = region.x0;
   // acc: l, d(dt) x3, d(dw) x3, d sigma, d p_out
-  float acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  double acc[NV] = {};
   if (!obj.empty()) {
     // the depth buffer spans the object rectangle grown by 2h, past the image
     // edges if need be (those slots stay empty), so every window is inside it
@@ -284,11 +314,15 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
     const int lw = lds.w(), rw = region.w();
     const int ow = obj.w();
     int band = s.zcap / lw - 4 * h;
-    // the window weights ((band + 2h) x rw floats) leave at least one round
-    // (kBlock entries) of the drawn-pixel list in the scratch
-    if (GRAD) band = min(band, min(s.wcap, (int)(kRasterLdsBytes - 2 * kBlock) / 4) / rw - 2 * h);
+    // the queues of the waves, in the scratch after the window weights ((band +
+    // 2h) x rw floats), or after everything for an image that leaves no room
+    constexpr int kQueues = 2 * kWaveQueue * NW;
+    const bool wide = GRAD && weight_bytes(BS, W, h) > kScratch;
+    unsigned short* queue = reinterpret_cast<unsigned short*>(
+                                wide ? reinterpret_cast<unsigned char*>(dyt + H + 2 * h) : smem + kScratch - kQueues) +
+                            kWaveQueue * ((int)threadIdx.x >> 6);
+    if (GRAD) band = min(band, (kScratch - (wide ? 0 : kQueues)) / 4 / rw - 2 * h);
     band = max(band, 1);
-    int gcarry = 0;  // drawn pixels of earlier bands' own rows
     // with a row range: only the region's rows in [row_lo, row_hi) (the
     // adjoint's weights still span the whole region's halo rows)
     const int ya = row_lo >= 0 ? max(region.y0, row_lo) : region.y0;
@@ -298,120 +332,104 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
       Rect L = lds;
       L.y0 = a - 2 * h;
       L.y1 = b + 2 * h;
-      raster_band<COUNT, RM>(s, P, L, zbuf, smem, red, cnt);
+      raster_band<COUNT, RM, BS>(s, P, L, zbuf, smem, cnt);
       // likelihood over observed rows [wa, wb); rows [a, b) are this band's own
       const int wa = GRAD ? max(a - h, region.y0) : a;
       const int wb = GRAD ? min(b + h, region.y1) : b;
       const int nw = (wb - wa) * rw;
-
-      // pixel g of the region (row-major from its corner) always goes to
-      // thread g mod kBlock, so every thread adds its terms in the same order
-      // however the rows are banded: results do not depend on the band height
       const float inv_rw = 1.0f / (float)rw;
-      for (int k = first_of(threadIdx.x, (wa - region.y0) * rw); k < nw; k += kBlock) {
-        int r, c;
-        row_col(k, rw, inv_rw, r, c);
-        r += wa;
-        c += region.x0;
-        const float* q = s.obs + 3 * ((size_t)r * W + c);
-        const float ox = q[0], oy = q[1], oz = q[2];
-        float wv = 0.0f;
-        if (oz > 0.0f) {
-          float S, T;
-          unsigned pairs = 0;
-          switch (h) {
-            case 1:
-              window_sums<1, GRAD, COUNT>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, sc.c2, S, T, pairs);
-              break;
-            case 2:
-              window_sums<2, GRAD, COUNT>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, sc.c2, S, T, pairs);
-              break;
-            default:
-              window_sums<0, GRAD, COUNT>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, sc.c2, S, T, pairs);
-          }
-          if (COUNT && r >= a && r < b) c_pair += pairs;
-          const float Li = sc.a + sc.bn * S;
-          const float iL = __builtin_amdgcn_rcpf(Li);  // 1 / L_i, hardware reciprocal (1 ulp)
-          const float bL = sc.bn * iL;
-          if (r >= a && r < b) {
-            if (COUNT && S > 0.0f) ++c_obs;
-            acc[0] += f_ln(Li);
-            if (GRAD) {
-              acc[7] += bL * (T * sc.inv_s3 - 3.0f * S * sc.inv_s);
-              acc[8] += (sc.invV - sc.normM * S) * iL;
+      wave_compacted<NW>(
+          nw, queue,
+          [&](int k) {
+            int r, c;
+            row_col(k, rw, inv_rw, r, c);
+            const bool valid = s.obs[3 * ((size_t)(wa + r) * W + (region.x0 + c)) + 2] > 0.0f;
+            if (GRAD && !valid) wbuf[k] = 0.0f;
+            return valid;
+          },
+          [&](int k, bool act) {
+            if (!act) return;
+            int r, c;
+            row_col(k, rw, inv_rw, r, c);
+            r += wa;
+            c += region.x0;
+            const float* q = s.obs + 3 * ((size_t)r * W + c);
+            const float ox = q[0], oy = q[1], oz = q[2];
+            float S, T;
+            unsigned pairs = 0;
+            switch (h) {
+              case 1:
+                window_sums<1, GRAD, COUNT>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, sc.c2, S, T, pairs);
+                break;
+              case 2:
+                window_sums<2, GRAD, COUNT>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, sc.c2, S, T, pairs);
+                break;
+              default:
+                window_sums<0, GRAD, COUNT>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, sc.c2, S, T, pairs);
             }
-          }
-          wv = bL;
-        }
-        if (GRAD) wbuf[k] = wv;
-      }
+            if (COUNT && r >= a && r < b) c_pair += pairs;
+            const float Li = sc.a + sc.bn * S;
+            const float iL = __builtin_amdgcn_rcpf(Li);  // 1 / L_i, hardware reciprocal (1 ulp)
+            const float bL = sc.bn * iL;
+            if (r >= a && r < b) {
+              if (COUNT && S > 0.0f) ++c_obs;
+              acc[0] += (double)f_ln(Li);
+              if constexpr (GRAD) {
+                acc[7] += (double)(bL * (T * sc.inv_s3 - 3.0f * S * sc.inv_s));
+                acc[8] += (double)((sc.invV - sc.normM * S) * iL);
+              }
+            }
+            if (GRAD) wbuf[k] = bL;
+          });
 
-      if (GRAD) {
+      if constexpr (GRAD) {
         __syncthreads();
-        // d logL / d z_j of drawn pixel (r, c) over its window, onto (dt, dw)
-        auto gather = [&](int r, int c, unsigned long long key) {
-          const uint32_t id = key_id(key);
-          if (COUNT) ++c_adj;
-          const float z = key_depth(key);
-          const float dx = dxt[c], dy = dyt[r];
-          const float qx = z * dx, qy = z * dy, qz = z;
-          float g;
-          switch (h) {
-            case 1:
-              g = window_grad<1>(wbuf, wa, wb, region, s.obs, W, r, c, h, qx, qy, qz, dx, dy, sc.c2);
-              break;
-            case 2:
-              g = window_grad<2>(wbuf, wa, wb, region, s.obs, W, r, c, h, qx, qy, qz, dx, dy, sc.c2);
-              break;
-            default:
-              g = window_grad<0>(wbuf, wa, wb, region, s.obs, W, r, c, h, qx, qy, qz, dx, dy, sc.c2);
-          }
-          g *= sc.inv_s2;
-          const float4 no = s.mesh.normals[id];
-          const float3 nn = rotate(P, no.x, no.y, no.z);
-          const float sg = g * __builtin_amdgcn_rcpf(nn.x * dx + nn.y * dy + nn.z);
-          const float tx = P.t[0] - qx, ty = P.t[1] - qy, tz = P.t[2] - qz;
-          acc[1] += sg * nn.x;
-          acc[2] += sg * nn.y;
-          acc[3] += sg * nn.z;
-          acc[4] += sg * (nn.y * tz - nn.z * ty);
-          acc[5] += sg * (nn.z * tx - nn.x * tz);
-          acc[6] += sg * (nn.x * ty - nn.y * tx);
-        };
-        // the drawn pixels of this band's own rows, listed chunk by chunk in the
-        // scratch after the window weights; the i-th of them over all bands and
-        // chunks (row-major) goes to thread i mod kBlock, so each thread's
-        // order does not depend on banding
+        // the drawn pixels of this band's own rows: d logL / d z_j over the
+        // window, onto (dt, dw)
         const int ga = max(a, obj.y0), gb = min(b, obj.y1);
-        const int ng = max(gb - ga, 0) * ow;
         const float inv_ow = 1.0f / (float)ow;
-        unsigned short* glist = reinterpret_cast<unsigned short*>(smem + 4 * nw);
-        const int gcap = ((int)kRasterLdsBytes - 4 * nw) / 2;
-        for (int pos = 0; pos < ng;) {
-          int n = 0;
-          // compaction rounds while a whole round still fits
-          for (; pos < ng && n + kBlock <= gcap; pos += kBlock) {
-            const int k = pos + (int)threadIdx.x;
-            bool d = false;
-            if (k < ng) {
+        wave_compacted<NW>(
+            max(gb - ga, 0) * ow, queue,
+            [&](int k) {
+              int r, c;
+              row_col(k, ow, inv_ow, r, c);
+              return key_id(zbuf[(ga + r - L.y0) * lw + (obj.x0 + c - L.x0)]) < (uint32_t)s.mesh.T;
+            },
+            [&](int k, bool act) {
+              if (!act) return;
               int r, c;
               row_col(k, ow, inv_ow, r, c);
               r += ga;
               c += obj.x0;
-              d = key_id(zbuf[(r - L.y0) * lw + (c - L.x0)]) < (uint32_t)s.mesh.T;
-            }
-            n += append_flagged(d, k, glist, n, reinterpret_cast<int*>(red));
-          }
-          for (int i = first_of(threadIdx.x, gcarry); i < n; i += kBlock) {
-            int r, c;
-            row_col(glist[i], ow, inv_ow, r, c);
-            r += ga;
-            c += obj.x0;
-            gather(r, c, zbuf[(r - L.y0) * lw + (c - L.x0)]);
-          }
-          gcarry += n;
-          __syncthreads();  // the list is rewritten by the next chunk
-        }
+              const unsigned long long key = zbuf[(r - L.y0) * lw + (c - L.x0)];
+              const uint32_t id = key_id(key);
+              if (COUNT) ++c_adj;
+              const float z = key_depth(key);
+              const float dx = dxt[c], dy = dyt[r];
+              const float qx = z * dx, qy = z * dy, qz = z;
+              float g;
+              switch (h) {
+                case 1:
+                  g = window_grad<1>(wbuf, wa, wb, region, s.obs, W, r, c, h, qx, qy, qz, dx, dy, sc.c2);
+                  break;
+                case 2:
+                  g = window_grad<2>(wbuf, wa, wb, region, s.obs, W, r, c, h, qx, qy, qz, dx, dy, sc.c2);
+                  break;
+                default:
+                  g = window_grad<0>(wbuf, wa, wb, region, s.obs, W, r, c, h, qx, qy, qz, dx, dy, sc.c2);
+              }
+              g *= sc.inv_s2;
+              const float4 no = s.mesh.normals[id];
+              const float3 nn = rotate(P, no.x, no.y, no.z);
+              const float sg = g * __builtin_amdgcn_rcpf(nn.x * dx + nn.y * dy + nn.z);
+              const float tx = P.t[0] - qx, ty = P.t[1] - qy, tz = P.t[2] - qz;
+              acc[1] += (double)(sg * nn.x);
+              acc[2] += (double)(sg * nn.y);
+              acc[3] += (double)(sg * nn.z);
+              acc[4] += (double)(sg * (nn.y * tz - nn.z * ty));
+              acc[5] += (double)(sg * (nn.z * tx - nn.x * tz));
+              acc[6] += (double)(sg * (nn.x * ty - nn.y * tx));
+            });
       }
       __syncthreads();
     }
@@ -421,45 +439,34 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
     atomicAdd(&cnt[kCntObs], c_obs);
     atomicAdd(&cnt[kCntAdj], c_adj);
   }
-  block_sum<9>(acc, red);
-  if (row_lo >= 0) {  // the rows' own terms only, no background outside the region
-    if (threadIdx.x == 0) {
-      *logL_out = acc[0];
-      if (GRAD)
-        for (int k = 0; k < 8; ++k) grad_out[k] = acc[1 + k];
-    }
-    return;
-  }
-  if (threadIdx.x == 0) {
-    const size_t stride = (size_t)(H + 1) * (W + 1);
+  // thread 16 k writes value k; the background outside the region (not with a
+  // row range) from summed-area tables: l of 0, d sigma of 2, d p_out of 1
+  const int k = threadIdx.x >> 4;
+  const bool writer = threadIdx.x < 16 * NV && (threadIdx.x & 15) == 0;
+  double outside = 0.0;
+  if (row_lo < 0 && writer && (k == 0 || k >= 7)) {
+    const double* sat = s.sat + (k == 0 ? 0 : k == 7 ? 2 : 1) * ((size_t)(H + 1) * (W + 1));
     Rect all;
     all.x0 = 0;
     all.x1 = W;
     all.y0 = 0;
     all.y1 = H;
-    const double outside_l = rect_sum(s.sat, W, all) - rect_sum(s.sat, W, region);
-    *logL_out = (float)((double)acc[0] + outside_l);
-    if (GRAD) {
-      const double outside_dp = rect_sum(s.sat + stride, W, all) - rect_sum(s.sat + stride, W, region);
-      const double outside_ds = rect_sum(s.sat + 2 * stride, W, all) - rect_sum(s.sat + 2 * stride, W, region);
-      float* g = grad_out;
-      for (int k = 0; k < 6; ++k) g[k] = acc[1 + k];
-      g[6] = (float)((double)acc[7] + outside_ds);
-      g[7] = (float)((double)acc[8] + outside_dp);
-    }
+    outside = rect_sum(sat, W, all) - rect_sum(sat, W, region);
   }
+  const double total = block_total<NV, BS>(acc, reinterpret_cast<double*>(smem)) + outside;
+  if (writer) *(k == 0 ? logL_out : grad_out + (k - 1)) = (float)total;
 }
 
 // RM: the rasteriser compiled in (the launcher picks it from the mesh, so
 // that meshes without large primitives run the plain one alone).
-template <bool GRAD, int RM>
-__global__ __launch_bounds__(kBlock, 4) void k_render_score(SceneDev s, const float* __restrict__ poses, int N,
-                                                         float* __restrict__ logL, float* __restrict__ grad) {
+template <bool GRAD, int RM, int BS>
+__global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float* __restrict__ poses, int N,
+                                                        float* __restrict__ logL, float* __restrict__ grad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = blockIdx.x;
   if (n >= N) return;
-  render_score_one<GRAD, false, RM>(s, poses + 16 * (size_t)n, logL + n, GRAD ? grad + 8 * (size_t)n : nullptr,
-                                    smem);
+  render_score_one<GRAD, false, RM, BS>(s, poses + 16 * (size_t)n, logL + n, GRAD ? grad + 8 * (size_t)n : nullptr,
+                                        smem);
 }
 
 // A group of scenes in one launch, one workgroup per (scene, hypothesis)
@@ -498,6 +505,7 @@ hipError_t launch_batch(const BatchGroupDev& g, bool grad, size_t lds, hipStream
   bool big = false;
   for (int k = 0; k < g.S; ++k) big = big || g.s[k].mesh.has_big != 0;
   const dim3 grid((unsigned)g.first[g.S]);
+  for (int k = 0; k < g.S; ++k) lds = std::max(lds, launch_lds_bytes(g.s[k], kBlock, g.s[k].zcap, grad));
   if (grad && big)
     hipLaunchKernelGGL((k_batch<true, kRasterAny>), grid, dim3(kBlock), lds, st, g);
   else if (grad)
@@ -554,7 +562,10 @@ hipError_t launch_batch_queue(const BatchGroupDev& g, unsigned long long* counte
                               hipStream_t st) {
   hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, st, counter);
   bool big = false;
-  for (int k = 0; k < g.S; ++k) big = big || g.s[k].mesh.has_big != 0;
+  for (int k = 0; k < g.S; ++k) {
+    big = big || g.s[k].mesh.has_big != 0;
+    lds = std::max(lds, launch_lds_bytes(g.s[k], kBlock, g.s[k].zcap, grad));
+  }
   if (grad && big)
     hipLaunchKernelGGL((k_batch_queue<true, kRasterAny>), dim3(blocks), dim3(kBlock), lds, st, g, counter);
   else if (grad)
@@ -592,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void k_refine_pose(SceneDev s, float* __res
 
 hipError_t launch_refine_pose(const SceneDev& s, float* poses, int N, int n_refine, float lr_t, float lr_r, float b1,
                               float b2, float eps, hipStream_t st) {
-  hipLaunchKernelGGL(k_refine_pose, dim3(N), dim3(kBlock), fused_lds_bytes(s), st, s, poses, N, n_refine, lr_t,
+  hipLaunchKernelGGL(k_refine_pose, dim3(N), dim3(kBlock), launch_lds_bytes(s, kBlock, s.zcap, true), st, s, poses, N, n_refine, lr_t,
                      lr_r, b1, b2, eps);
   return hipGetLastError();
 }
@@ -637,13 +648,12 @@ __global__ void k_refine_update(float* __restrict__ pose, const float* __restric
 hipError_t launch_refine_banded(const SceneDev& s, float* pose, int n_refine, float lr_t, float lr_r, float b1,
                                 float b2, float eps, int R, float* partial, float* state, hipStream_t st) {
   const int nb = (s.cam.H + R - 1) / R;
+  const size_t lds = launch_lds_bytes(s, kBlock, s.zcap, true);
   for (int it = 1; it <= n_refine; ++it) {
     if (s.mesh.has_big)
-      hipLaunchKernelGGL(k_refine_bands<kRasterBig>, dim3(nb), dim3(kBlock), fused_lds_bytes(s), st, s, pose, R,
-                         partial);
+      hipLaunchKernelGGL(k_refine_bands<kRasterBig>, dim3(nb), dim3(kBlock), lds, st, s, pose, R, partial);
     else
-      hipLaunchKernelGGL(k_refine_bands<kRasterSmall>, dim3(nb), dim3(kBlock), fused_lds_bytes(s), st, s, pose, R,
-                         partial);
+      hipLaunchKernelGGL(k_refine_bands<kRasterSmall>, dim3(nb), dim3(kBlock), lds, st, s, pose, R, partial);
     hipLaunchKernelGGL(k_refine_update, dim3(1), dim3(64), 0, st, pose, partial, nb, state, it, lr_t, lr_r, b1, b2,
                        eps);
   }
@@ -721,6 +731,7 @@ __device__ __forceinline__ void render_score_grid_one(const SceneDev& s, const N
   const Pose P = load_pose(pose16);
   for (int i = (int)threadIdx.x - 2 * h; i < W + 2 * h; i += kBlock) dxt[i] = ray_x(cam, i);
   for (int i = (int)threadIdx.x - 2 * h; i < H + 2 * h; i += kBlock) dyt[i] = ray_y(cam, i);
+  if (threadIdx.x == kBlock - 1) *reinterpret_cast<PlaneView*>(zbuf + s.zcap) = plane_view(P, cam);
   const bool rows = row0 >= 0;
   Rect all;
   all.x0 = 0;
@@ -749,7 +760,7 @@ __device__ __forceinline__ void render_score_grid_one(const SceneDev& s, const N
       Rect L = lds;
       L.y0 = a - 2 * h;
       L.y1 = b + 2 * h;
-      raster_band<false>(s, P, L, zbuf, smem, red, nullptr);
+      raster_band<false, kRasterAny, kBlock>(s, P, L, zbuf, smem, nullptr);
       const int nw = (b - a) * rw;
       // observed pixel g of the region always goes to thread g mod kBlock;
       // na: the grid's number of deviations as a compile-time constant (0: any)
@@ -933,25 +944,31 @@ __global__ __launch_bounds__(kBlock) void k_render_score_count(SceneDev s, const
 
 hipError_t launch_render_score_count(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                      unsigned long long* work, hipStream_t st) {
-  hipLaunchKernelGGL(k_render_score_count, dim3(N), dim3(kBlock), fused_lds_bytes(s), st, s, poses, N, logL, grad,
-                     work);
+  hipLaunchKernelGGL(k_render_score_count, dim3(N), dim3(kBlock), launch_lds_bytes(s, kBlock, s.zcap, true), st, s,
+                     poses, N, logL, grad, work);
+  return hipGetLastError();
+}
+
+template <int BS>
+static hipError_t launch_render_score_bs(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
+                                         hipStream_t st) {
+  const size_t lds = launch_lds_bytes(s, BS, s.zcap, grad != nullptr);
+  const bool big = s.mesh.has_big != 0;
+  if (grad && big)
+    hipLaunchKernelGGL((k_render_score<true, kRasterBig, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
+  else if (grad)
+    hipLaunchKernelGGL((k_render_score<true, kRasterSmall, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
+  else if (big)
+    hipLaunchKernelGGL((k_render_score<false, kRasterBig, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
+  else
+    hipLaunchKernelGGL((k_render_score<false, kRasterSmall, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL,
+                       grad);
   return hipGetLastError();
 }
 
 hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                hipStream_t st) {
-  const size_t lds = fused_lds_bytes(s);
-  const bool big = s.mesh.has_big != 0;
-  if (grad && big)
-    hipLaunchKernelGGL((k_render_score<true, kRasterBig>), dim3(N), dim3(kBlock), lds, st, s, poses, N, logL, grad);
-  else if (grad)
-    hipLaunchKernelGGL((k_render_score<true, kRasterSmall>), dim3(N), dim3(kBlock), lds, st, s, poses, N, logL, grad);
-  else if (big)
-    hipLaunchKernelGGL((k_render_score<false, kRasterBig>), dim3(N), dim3(kBlock), lds, st, s, poses, N, logL, grad);
-  else
-    hipLaunchKernelGGL((k_render_score<false, kRasterSmall>), dim3(N), dim3(kBlock), lds, st, s, poses, N, logL,
-                       grad);
-  return hipGetLastError();
+  return launch_render_score_bs<kBlock>(s, poses, N, logL, grad, st);
 }
 
 }  // namespace b3d

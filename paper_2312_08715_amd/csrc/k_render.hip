@@ -85,11 +85,12 @@ __device__ __forceinline__ void write_rows4(const Cam& cam, int y0, int y1, cons
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_render_batch(MeshDev m, Cam cam, const float* __restrict__ poses, int N,
+template <int RM>
+__global__ __launch_bounds__(kBlock, 4) void k_render_batch(MeshDev m, Cam cam, const float* __restrict__ poses, int N,
                                                          float* __restrict__ xyz, int* __restrict__ tri, int zcap,
                                                          int vec) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const RasterLds rl = carve_raster_lds(smem);
+  const RasterLds rl = carve_raster_lds<kBlock>(smem);
   unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kRasterLdsBytes);
   const int n = blockIdx.x;
   if (n >= N) return;
@@ -106,6 +107,9 @@ __global__ __launch_bounds__(kBlock) void k_render_batch(MeshDev m, Cam cam, con
     return;
   }
   const int band_rows = max(zcap / obj.w(), 1);
+  PlaneView* view = reinterpret_cast<PlaneView*>(zbuf + zcap);
+  if (threadIdx.x == 0) *view = plane_view(P, cam);
+  const float inv_w = 1.0f / (float)obj.w();
   for (int a = obj.y0; a < obj.y1; a += band_rows) {
     Rect band = obj;
     band.y0 = a;
@@ -113,8 +117,19 @@ __global__ __launch_bounds__(kBlock) void k_render_batch(MeshDev m, Cam cam, con
     const int nk = band.h() * band.w();
     for (int k = threadIdx.x; k < nk; k += kBlock) zbuf[k] = kEmptyKey;
     __syncthreads();
-    raster_mesh_any(m, P, cam, 0u, band, band, zbuf, rl);
-    refine_depths(m, P, cam, 0u, band, zbuf);
+    raster_mesh_mode<false, RM, kBlock>(m, P, cam, 0u, band, band, zbuf, rl, view);
+    // the drawn slots' depths on their triangles' planes
+    wave_compacted<kWaves>(
+        nk, reinterpret_cast<unsigned short*>(smem) + (threadIdx.x >> 6) * kWaveQueue,
+        [&](int k) { return zbuf[k] != kEmptyKey; },
+        [&](int k, bool act) {
+          if (!act) return;
+          const uint32_t id = key_id(zbuf[k]);
+          int r, c;
+          row_col(k, band.w(), inv_w, r, c);
+          zbuf[k] = pack_key(plane_depth(m, *view, id, band.y0 + r, band.x0 + c), id);
+        });
+    __syncthreads();
     WRITE_ROWS(cam, band.y0, band.y1, band, zbuf, 0u, xn, tn);
     __syncthreads();
   }
@@ -128,10 +143,15 @@ __global__ __launch_bounds__(kBlock) void k_render_batch(MeshDev m, Cam cam, con
 
 hipError_t launch_render_batch(const MeshDev& m, const Cam& cam, const float* poses, int N, float* xyz, int* tri,
                                int zcap, hipStream_t st) {
-  const size_t lds = kRasterLdsBytes + sizeof(unsigned long long) * (size_t)zcap;
+  const size_t lds = kRasterLdsBytes + sizeof(unsigned long long) * (size_t)zcap + kPlaneViewBytes;
   // quads of pixels as whole 16-byte words: rows of W % 4 == 0 pixels in 16-byte aligned buffers
   const int vec = (cam.W % 4 == 0) && ((uintptr_t)xyz & 15) == 0 && ((uintptr_t)tri & 15) == 0;
-  hipLaunchKernelGGL(k_render_batch, dim3(N), dim3(kBlock), lds, st, m, cam, poses, N, xyz, tri, zcap, vec);
+  if (m.has_big)
+    hipLaunchKernelGGL(k_render_batch<kRasterBig>, dim3(N), dim3(kBlock), lds, st, m, cam, poses, N, xyz, tri, zcap,
+                       vec);
+  else
+    hipLaunchKernelGGL(k_render_batch<kRasterSmall>, dim3(N), dim3(kBlock), lds, st, m, cam, poses, N, xyz, tri, zcap,
+                       vec);
   return hipGetLastError();
 }
 
@@ -167,6 +187,7 @@ __global__ __launch_bounds__(kBlock) void k_render_backward(MeshDev m, Cam cam, 
   const int HW = cam.H * cam.W;
   const int* tn = tri + (size_t)n * HW;
   const float* dn = d_rend + (size_t)n * HW * 3;
+  const PlaneView pv = plane_view(P, cam);
   float acc[6] = {0, 0, 0, 0, 0, 0};
   for (int p = threadIdx.x; p < HW; p += kBlock) {
     const int id = tn[p];
@@ -178,7 +199,7 @@ __global__ __launch_bounds__(kBlock) void k_render_backward(MeshDev m, Cam cam, 
     const float4 no = m.normals[id];
     const float3 nn = rotate(P, no.x, no.y, no.z);
     const float nd = nn.x * dx + nn.y * dy + nn.z;
-    const float z = plane_depth(m, P, cam, (uint32_t)id, r, c);
+    const float z = plane_depth(m, pv, (uint32_t)id, r, c);
     const float tx = P.t[0] - z * dx, ty = P.t[1] - z * dy, tz = P.t[2] - z;
     const float s = g / nd;
     acc[0] += s * nn.x;
@@ -270,7 +291,7 @@ __global__ void k_refine_global(MeshDev m, Cam cam, Pose P, const float* __restr
   if (id >= (uint32_t)m.T) return;
   const Pose Q = pose16_dev ? load_pose(pose16_dev) : P;
   const int r = p / cam.W, c = p - r * cam.W;
-  keys[p] = pack_key(plane_depth(m, Q, cam, id, r, c), key_id(key));
+  keys[p] = pack_key(plane_depth(m, plane_view(Q, cam), id, r, c), key_id(key));
 }
 
 hipError_t launch_raster_global(const MeshDev& m, const Cam& cam, const float* pose16, uint32_t id_base,

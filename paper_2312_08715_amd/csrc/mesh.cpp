@@ -446,9 +446,10 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
           cos_a = std::min(cos_a, d);
         }
       }
-      // half-angle of the normal cone, widened slightly; > pi/2 disables culling
-      const double alpha = ok ? std::acos(std::max(-1.0, std::min(1.0, cos_a))) + 1e-4 : 4.0;
-      c.cone = ok ? make_float4((float)(axis[0] / al), (float)(axis[1] / al), (float)(axis[2] / al), (float)alpha)
+      // half-angle of the normal cone, widened slightly; near a right angle it disables culling
+      const double alpha = ok ? std::acos(std::max(-1.0, std::min(1.0, cos_a))) + 2.1e-3 : 4.0;
+      c.cone = ok ? make_float4((float)(axis[0] / al), (float)(axis[1] / al), (float)(axis[2] / al),
+                                alpha < 1.5 ? (float)std::sin(alpha) : 4.0f)
                   : make_float4(0.0f, 0.0f, 1.0f, 4.0f);
       L.clusters.push_back(c);
       i = j;
