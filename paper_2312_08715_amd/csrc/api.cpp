@@ -450,12 +450,10 @@ b3d_status b3d_scene_create(const b3d_mesh* mesh, const b3d_intrinsics* K, const
       return fail(B3D_ESHAPE, "scene_create: field of view too wide (|x/z| or |y/z| above 1e3 at the image edge)");
     }
   }
-  // window weights live in the rasteriser's scratch once the depth buffer is done
-  S->dev.wcap = (int)(kRasterLdsBytes / sizeof(float));
   // depth keys: as many as leave room for four workgroups per CU (160 KB of LDS)
   S->dev.zcap = std::max(default_zcap(S->dev, 4), min_zcap(S->dev));
-  // one band row of window weights must leave a round of the drawn-pixel list
-  if ((2 * h + 1) * W > S->dev.wcap || 4 * (size_t)(2 * h + 1) * W + 2 * kBlock > kRasterLdsBytes ||
+  // one band row of window weights must fit the rasteriser's scratch
+  if (4 * (size_t)(2 * h + 1) * W + 2 * kBlock > kRasterLdsBytes ||
       S->dev.zcap > max_zcap(S->dev) || fused_lds_bytes(S->dev) > kLdsMax) {
     delete S;
     return fail(B3D_ESHAPE, "scene_create: image width %d too large for the fused kernel's LDS budget", W);
@@ -700,20 +698,6 @@ b3d_status run_batch(const BatchPlan& plan, hipStream_t st, hipStream_t side, hi
   return B3D_OK;
 }
 
-b3d_status run_batch_queue(const BatchPlan& plan, unsigned long long* counters, hipStream_t st) {
-  if (plan.groups.empty()) return B3D_OK;
-  int dev = 0, cus = 0, occ = 0;
-  B3D_CHECK_HIP(hipGetDevice(&dev), "batch");
-  B3D_CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "batch");
-  B3D_CHECK_HIP(batch_queue_occupancy(plan.grad, plan.lds, &occ), "batch");
-  for (size_t k = 0; k < plan.groups.size(); ++k) {
-    const BatchGroupDev& g = plan.groups[k];
-    const int blocks = (int)std::max<long long>(1, std::min<long long>((long long)cus * std::max(occ, 1), g.first[g.S]));
-    B3D_CHECK_HIP(launch_batch_queue(g, counters + 32 * k, plan.grad, plan.lds, blocks, st), "batch");
-  }
-  return B3D_OK;
-}
-
 }  // namespace b3d_api
 
 extern "C" {
@@ -779,6 +763,7 @@ b3d_status b3d_scene_set_tile(b3d_scene* S, int32_t zcap) {
   if (t.zcap < min_zcap(S->dev) || t.zcap > max_zcap(S->dev) || fused_lds_bytes(t) > kLdsMax)
     return fail(B3D_ESHAPE, "scene_set_tile: %d keys outside [%d, LDS limit]", zcap, min_zcap(S->dev));
   S->dev.zcap = t.zcap;
+  S->dev.fixed_tile = zcap > 0;
   return B3D_OK;
 }
 
@@ -827,6 +812,7 @@ b3d_status b3d_scene_autotune(b3d_scene* S, const float* poses, int32_t N, int32
   (void)hipFree(out);
   if (status != B3D_OK) return status;
   S->dev.zcap = best;
+  S->dev.fixed_tile = 0;
   if (zcap_out) *zcap_out = best;
   return B3D_OK;
 }

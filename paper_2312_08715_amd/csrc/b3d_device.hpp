@@ -10,6 +10,8 @@ namespace b3d {
 
 constexpr int kBlock = 256;          // threads per workgroup (4 wave64)
 constexpr int kWaves = kBlock / 64;
+constexpr int kCUs = 256;            // compute units of an MI355X
+constexpr size_t kLdsPerCU = 160 * 1024;
 constexpr int kClusterPrims = 64;    // max primitives (triangles or quads) per cluster, one per lane of a wave
 constexpr uint32_t kNoTri = 0xFFFFFFFFu;  // second id of a primitive that is a single triangle
 // The key of a pixel with no surface: depth 1e15 m (bits 0x58635FA9), id all

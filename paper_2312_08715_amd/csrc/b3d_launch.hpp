@@ -32,7 +32,8 @@ struct SceneDev {
   const float* obs;                // [H][W][3]
   const unsigned long long* bg;    // [H][W] background keys, or nullptr
   const double* sat;               // 3 summed-area tables [(H+1)(W+1)]: l, dl/dp, dl/dsigma of the background
-  int zcap, wcap;                  // LDS capacities: depth keys, window weights (wcap <= kRasterLdsBytes / 4)
+  int zcap;                        // LDS capacity of the depth buffer in keys
+  int fixed_tile;                  // zcap is the caller's: launches keep it whatever their size
 };
 
 // A grid of noise parameters for the hierarchical likelihood: A standard
@@ -214,14 +215,9 @@ hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, flo
 hipError_t launch_render_score_count(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                      unsigned long long* work, hipStream_t st);
 
-// One workgroup per hypothesis of the group's scenes.
+// One workgroup per hypothesis of the group's scenes; of a group with large
+// images, a second launch for the objects beyond its depth buffers.
 hipError_t launch_batch(const BatchGroupDev& g, bool grad, size_t lds, hipStream_t st);
-// The same by `blocks` persistent workgroups draining a device counter (256
-// bytes of device memory per launch).
-hipError_t batch_queue_occupancy(bool grad, size_t lds, int* blocks_per_cu);
-hipError_t launch_batch_queue(const BatchGroupDev& g, unsigned long long* counter, bool grad, size_t lds, int blocks,
-                              hipStream_t st);
-
 // scene preparation
 hipError_t launch_fill_keys(unsigned long long* keys, size_t n, hipStream_t st);
 hipError_t launch_raster_global(const MeshDev& m, const Cam& cam, const float* pose16_host, uint32_t id_base,

@@ -39,13 +39,15 @@ static size_t fused_lds_bytes(const SceneDev& s, int bs, int zcap) {
 }
 size_t fused_lds_bytes(const SceneDev& s) { return fused_lds_bytes(s, kBlock, s.zcap); }
 
-// Bytes beyond these that the adjoint of a wide image needs: its window
-// weights for one row and the halo, and the waves' queues, exceed the scratch
-// only there.
+// Bytes beyond these that the adjoint needs: blocks of more than kBlock threads
+// keep the window weights in an area of their own, as many as depth keys; and
+// the weights of one row and the halo together with the waves' queues exceed
+// the scratch for a wide image.
 __host__ __device__ __forceinline__ int weight_bytes(int bs, int W, int h) {
   return 4 * (2 * h + 1) * W + 2 * kWaveQueue * (bs / 64);
 }
 static size_t launch_lds_bytes(const SceneDev& s, int bs, int zcap, bool grad) {
+  if (grad && bs > kBlock) return fused_lds_bytes(s, bs, zcap) + 4 * (size_t)zcap;
   const int over = grad ? weight_bytes(bs, s.cam.W, s.sc.h) - (int)raster_lds_bytes(bs) : 0;
   return fused_lds_bytes(s, bs, zcap) + (over > 0 ? 2 * kWaveQueue * (bs / 64) : 0);
 }
@@ -268,8 +270,14 @@ __device__ __forceinline__ void raster_band(const SceneDev& s, const Pose& P, co
   __syncthreads();
 }
 
+// What a deferred hypothesis leaves in its logL for the second launch: a NaN
+// that no arithmetic makes (were an input's NaN to carry it here, the
+// hypothesis would be scored twice, with one result).
+constexpr uint32_t kDeferred = 0x7fcb3d5eu;
+
 // One hypothesis: pose16 (16 floats), writes *logL_out and, when GRAD,
-// grad_out[0..8).  Must be called by the whole block of BS threads; `smem` is
+// grad_out[0..8).  DEFER: one whose depth buffer exceeds the block's writes
+// kDeferred instead, and nothing else.  Must be called by the whole block of BS threads; `smem` is
 // at least the fused LDS size for BS and s.zcap.
 // What bounds it is VALU issue (about 90 % of the issue slots at 5,000
 // hypotheses of 160x120); so work common to the block is shared between lanes,
@@ -279,7 +287,7 @@ __device__ __forceinline__ void raster_band(const SceneDev& s, const Pose& P, co
 // hypotheses of 2,000 voxels at 160x120 with the adjoint: 400 us against 429
 // with every wave computing the block's bounds, block-wide lists and one lane
 // per observed pixel.)
-template <bool GRAD, bool COUNT = false, int RM = kRasterAny, int BS = kBlock>
+template <bool GRAD, bool COUNT = false, int RM = kRasterAny, int BS = kBlock, bool DEFER = false>
 __device__ __forceinline__ void render_score_one(const SceneDev& s, const float* __restrict__ pose16,
                                                  float* __restrict__ logL_out, float* __restrict__ grad_out,
                                                  unsigned char* smem, unsigned* cnt = nullptr, int row_lo = -1,
@@ -287,7 +295,7 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
   static_assert(kPlaneViewBytes <= 64 * sizeof(float), "the plane view's share of LDS");
   constexpr int kScratch = (int)raster_lds_bytes(BS), NW = BS / 64, NV = GRAD ? 9 : 1;
   unsigned c_pair = 0, c_obs = 0, c_adj = 0;
-  float* wbuf = reinterpret_cast<float*>(smem);  // after rasterisation
+  constexpr bool kOwnWeights = GRAD && BS > kBlock;
   unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kScratch);
 
   const Cam& cam = s.cam;
@@ -297,11 +305,14 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
   float* dxt = reinterpret_cast<float*>(zbuf + s.zcap) + 64 + 2 * h;
   float* dyt = dxt + W + 4 * h;
   const Pose P = load_pose(pose16);
+  const Rect obj = object_rect(s.mesh, P, cam);
+  if (DEFER && (obj.w() + 4 * h) * (obj.h() + 4 * h) > s.zcap) {
+    if (threadIdx.x == 0) *logL_out = __uint_as_float(kDeferred);
+    return;
+  }
   for (int i = (int)threadIdx.x - 2 * h; i < W + 2 * h; i += BS) dxt[i] = ray_x(cam, i);
   for (int i = (int)threadIdx.x - 2 * h; i < H + 2 * h; i += BS) dyt[i] = ray_y(cam, i);
   if (threadIdx.x == BS - 1) *reinterpret_cast<PlaneView*>(zbuf + s.zcap) = plane_view(P, cam);
-
-  const Rect obj = object_rect(s.mesh, P, cam);
   // observed pixels whose window can see the object (none when nothing is drawn)
   Rect region = grow_clip(obj, h, W, H);
   if (obj.empty()) region.x1 = region.x0;
@@ -317,11 +328,12 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
     // the queues of the waves, in the scratch after the window weights ((band +
     // 2h) x rw floats), or after everything for an image that leaves no room
     constexpr int kQueues = 2 * kWaveQueue * NW;
-    const bool wide = GRAD && weight_bytes(BS, W, h) > kScratch;
+    const bool wide = GRAD && !kOwnWeights && weight_bytes(BS, W, h) > kScratch;
+    float* wbuf = kOwnWeights ? dyt + H + 2 * h : reinterpret_cast<float*>(smem);  // once the band is drawn
     unsigned short* queue = reinterpret_cast<unsigned short*>(
                                 wide ? reinterpret_cast<unsigned char*>(dyt + H + 2 * h) : smem + kScratch - kQueues) +
                             kWaveQueue * ((int)threadIdx.x >> 6);
-    if (GRAD) band = min(band, (kScratch - (wide ? 0 : kQueues)) / 4 / rw - 2 * h);
+    if (GRAD) band = min(band, (kOwnWeights ? s.zcap : (kScratch - (wide ? 0 : kQueues)) / 4) / rw - 2 * h);
     band = max(band, 1);
     // with a row range: only the region's rows in [row_lo, row_hi) (the
     // adjoint's weights still span the whole region's halo rows)
@@ -459,14 +471,45 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
 
 // RM: the rasteriser compiled in (the launcher picks it from the mesh, so
 // that meshes without large primitives run the plain one alone).
-template <bool GRAD, int RM, int BS>
-__global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float* __restrict__ poses, int N,
-                                                        float* __restrict__ logL, float* __restrict__ grad) {
+// How a launch takes part: alone; first, leaving the hypotheses beyond its
+// depth buffer; or second, scoring those that were left.
+enum Part { kAlone = 0, kFirst = 1, kRest = 2 };
+
+template <bool GRAD, int RM, int BS, int PART>
+__global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float* __restrict__ poses, int N, float* logL,
+                                                        float* __restrict__ grad) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = blockIdx.x;
   if (n >= N) return;
-  render_score_one<GRAD, false, RM, BS>(s, poses + 16 * (size_t)n, logL + n, GRAD ? grad + 8 * (size_t)n : nullptr,
-                                        smem);
+  if (PART == kRest && __float_as_uint(logL[n]) != kDeferred) return;
+  render_score_one<GRAD, false, RM, BS, PART == kFirst>(s, poses + 16 * (size_t)n, logL + n,
+                                                        GRAD ? grad + 8 * (size_t)n : nullptr, smem);
+}
+
+// Images above which objects often exceed the 256-thread block's depth buffer,
+// and the 512-thread block's (an object takes about a tenth to a quarter of
+// its image); hypotheses above which a second launch costs at most a few per cent.
+constexpr long long kBandedPixels = 24000, kWholeCuPixels = 56000;
+constexpr int kBandedCount = 2048;
+
+static bool defers(const SceneDev& s, long long N) {
+  const long long whole = (long long)(s.cam.W + 4 * s.sc.h) * (s.cam.H + 4 * s.sc.h);
+  return !s.fixed_tile && whole > s.zcap && ((long long)s.cam.W * s.cam.H > kBandedPixels || N >= kBandedCount);
+}
+static int rest_block(const SceneDev& s) { return (long long)s.cam.W * s.cam.H > kWholeCuPixels ? 1024 : 512; }
+
+// The scene with the depth buffer that a block of bs threads has room for: its
+// share of a CU's LDS, no more than the image needs.  The caller's own tile
+// stays.  False when even that does not fit (the widest images).
+static bool roomy_scene(const SceneDev& s, int bs, bool grad, SceneDev* t) {
+  *t = s;
+  if (!s.fixed_tile) {
+    const size_t share = kLdsPerCU / (1024 / bs), rest = fused_lds_bytes(s, bs, 0);
+    const int fit = share > rest ? (int)((share - rest) / (kFusedBytesPerKey + (grad ? 4 : 0))) : 0;
+    const int whole = (s.cam.W + 4 * s.sc.h) * (s.cam.H + 4 * s.sc.h);
+    t->zcap = std::max(s.zcap, std::min(fit, whole));
+  }
+  return launch_lds_bytes(*t, bs, t->zcap, grad) <= kLdsPerCU;
 }
 
 // A group of scenes in one launch, one workgroup per (scene, hypothesis)
@@ -477,8 +520,8 @@ __global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float*
 // positions: indexing the argument with the scene number would move it to
 // scratch memory.  No static LDS either, which would cost a resident block
 // per CU at the default tile.
-template <bool GRAD, int RM>
-__global__ __launch_bounds__(kBlock, 4) void k_batch(const BatchGroupDev G) {
+template <bool GRAD, int RM, int BS, int PART>
+__global__ __launch_bounds__(BS, 4) void k_batch(const BatchGroupDev G) {
   extern __shared__ __align__(16) unsigned char smem[];
   const long long w = blockIdx.x;
   if (w >= G.first[G.S]) return;
@@ -498,82 +541,47 @@ __global__ __launch_bounds__(kBlock, 4) void k_batch(const BatchGroupDev G) {
       first = G.first[j];
     }
   const long long n = w - first;
-  render_score_one<GRAD, false, RM>(s, poses + 16 * n, logL + n, GRAD ? grad + 8 * n : nullptr, smem);
+  if (PART == kRest && __float_as_uint(logL[n]) != kDeferred) return;
+  render_score_one<GRAD, false, RM, BS, PART == kFirst>(s, poses + 16 * n, logL + n, GRAD ? grad + 8 * n : nullptr,
+                                                        smem);
 }
 
+template <int BS, int PART>
+static void launch_batch_part(const BatchGroupDev& g, bool grad, bool big, size_t lds, hipStream_t st) {
+  auto k = grad ? (big ? k_batch<true, kRasterAny, BS, PART> : k_batch<true, kRasterSmall, BS, PART>)
+                : (big ? k_batch<false, kRasterAny, BS, PART> : k_batch<false, kRasterSmall, BS, PART>);
+  hipLaunchKernelGGL(k, dim3((unsigned)g.first[g.S]), dim3(BS), lds, st, g);
+}
+
+// The group's launch and, when one of its images is large enough for objects
+// beyond the tiles (see launch_render_score), a second one for what it leaves.
 hipError_t launch_batch(const BatchGroupDev& g, bool grad, size_t lds, hipStream_t st) {
-  bool big = false;
-  for (int k = 0; k < g.S; ++k) big = big || g.s[k].mesh.has_big != 0;
-  const dim3 grid((unsigned)g.first[g.S]);
-  for (int k = 0; k < g.S; ++k) lds = std::max(lds, launch_lds_bytes(g.s[k], kBlock, g.s[k].zcap, grad));
-  if (grad && big)
-    hipLaunchKernelGGL((k_batch<true, kRasterAny>), grid, dim3(kBlock), lds, st, g);
-  else if (grad)
-    hipLaunchKernelGGL((k_batch<true, kRasterSmall>), grid, dim3(kBlock), lds, st, g);
-  else if (big)
-    hipLaunchKernelGGL((k_batch<false, kRasterAny>), grid, dim3(kBlock), lds, st, g);
-  else
-    hipLaunchKernelGGL((k_batch<false, kRasterSmall>), grid, dim3(kBlock), lds, st, g);
-  return hipGetLastError();
-}
-
-// The same work drained by a persistent grid instead: as many workgroups as
-// fit the chip, each pulling the next item from a device counter (reset by
-// a one-thread kernel, not a memset, so that launches can be captured) and
-// exiting once the counter passes the group's total.  Its loop keeps more
-// state live (some of it spills) and `work` takes static LDS, so it loses
-// where items are short, but it keeps every slot busy to the end of long
-// launches of long items.
-template <bool GRAD, int RM>
-__global__ __launch_bounds__(kBlock, 4) void k_batch_queue(const BatchGroupDev G,
-                                                           unsigned long long* __restrict__ counter) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ long long work;
-  const long long total = G.first[G.S];
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) work = (long long)atomicAdd(counter, 1ull);
-    __syncthreads();
-    // the same value in every lane: keep it (and the scene it selects) scalar
-    const unsigned long long wr = (unsigned long long)work;
-    const long long w = (long long)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(wr >> 32)) << 32) |
-                                    (unsigned)__builtin_amdgcn_readfirstlane((unsigned)wr));
-    if (w >= total) break;
-    int k = 0;
-    for (int j = 1; j < G.S; ++j) k = G.first[j] <= w ? j : k;
-    const long long n = w - G.first[k];
-    render_score_one<GRAD, false, RM>(G.s[k], G.poses[k] + 16 * n, G.logL[k] + n, GRAD ? G.grad[k] + 8 * n : nullptr,
-                                      smem);
-  }
-}
-
-__global__ void k_reset_counter(unsigned long long* c) {
-  if (threadIdx.x == 0) c[threadIdx.x] = 0ull;
-}
-
-hipError_t batch_queue_occupancy(bool grad, size_t lds, int* blocks_per_cu) {
-  // every raster variant has the same launch bounds and LDS
-  if (grad)
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_batch_queue<true, kRasterSmall>, kBlock, lds);
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_batch_queue<false, kRasterSmall>, kBlock, lds);
-}
-
-hipError_t launch_batch_queue(const BatchGroupDev& g, unsigned long long* counter, bool grad, size_t lds, int blocks,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, st, counter);
-  bool big = false;
+  bool big = false, defer = false, fits = true;
+  int bs = 512;
   for (int k = 0; k < g.S; ++k) {
     big = big || g.s[k].mesh.has_big != 0;
     lds = std::max(lds, launch_lds_bytes(g.s[k], kBlock, g.s[k].zcap, grad));
+    if (defers(g.s[k], g.first[k + 1] - g.first[k])) {
+      defer = true;
+      bs = std::max(bs, rest_block(g.s[k]));
+    }
   }
-  if (grad && big)
-    hipLaunchKernelGGL((k_batch_queue<true, kRasterAny>), dim3(blocks), dim3(kBlock), lds, st, g, counter);
-  else if (grad)
-    hipLaunchKernelGGL((k_batch_queue<true, kRasterSmall>), dim3(blocks), dim3(kBlock), lds, st, g, counter);
-  else if (big)
-    hipLaunchKernelGGL((k_batch_queue<false, kRasterAny>), dim3(blocks), dim3(kBlock), lds, st, g, counter);
-  else
-    hipLaunchKernelGGL((k_batch_queue<false, kRasterSmall>), dim3(blocks), dim3(kBlock), lds, st, g, counter);
+  BatchGroupDev rest = g;
+  size_t rest_lds = 0;
+  for (int k = 0; k < g.S && defer; ++k) {
+    // a scene with a tile of the caller's has nothing left to it, or bands
+    fits = fits && roomy_scene(g.s[k], bs, grad, &rest.s[k]);
+    rest_lds = std::max(rest_lds, launch_lds_bytes(rest.s[k], bs, rest.s[k].zcap, grad));
+  }
+  if (defer && fits) {
+    launch_batch_part<kBlock, kFirst>(g, grad, big, lds, st);
+    if (bs == 1024)
+      launch_batch_part<1024, kRest>(rest, grad, big, rest_lds, st);
+    else
+      launch_batch_part<512, kRest>(rest, grad, big, rest_lds, st);
+  } else {
+    launch_batch_part<kBlock, kAlone>(g, grad, big, lds, st);
+  }
   return hipGetLastError();
 }
 
@@ -949,26 +957,49 @@ hipError_t launch_render_score_count(const SceneDev& s, const float* poses, int 
   return hipGetLastError();
 }
 
-template <int BS>
-static hipError_t launch_render_score_bs(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
-                                         hipStream_t st) {
+template <int BS, int PART = kAlone>
+static void launch_render_score_bs(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
+                                   hipStream_t st) {
   const size_t lds = launch_lds_bytes(s, BS, s.zcap, grad != nullptr);
   const bool big = s.mesh.has_big != 0;
-  if (grad && big)
-    hipLaunchKernelGGL((k_render_score<true, kRasterBig, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
-  else if (grad)
-    hipLaunchKernelGGL((k_render_score<true, kRasterSmall, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
-  else if (big)
-    hipLaunchKernelGGL((k_render_score<false, kRasterBig, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
-  else
-    hipLaunchKernelGGL((k_render_score<false, kRasterSmall, BS>), dim3(N), dim3(BS), lds, st, s, poses, N, logL,
-                       grad);
-  return hipGetLastError();
+  auto k = grad ? (big ? k_render_score<true, kRasterBig, BS, PART> : k_render_score<true, kRasterSmall, BS, PART>)
+                : (big ? k_render_score<false, kRasterBig, BS, PART> : k_render_score<false, kRasterSmall, BS, PART>);
+  hipLaunchKernelGGL(k, dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
 }
 
+// One workgroup scores one hypothesis; how large a one is chosen for two
+// reasons, and no result depends on it.
+// * A launch of fewer hypotheses than the chip has slots lasts as long as one
+//   workgroup: up to one hypothesis per CU, each gets all of a CU's sixteen
+//   waves and its LDS (256 hypotheses at 64x48: 13.6 against 17.5 us), up to two,
+//   half of them.
+// * An object beyond the 256-thread block's depth buffer is drawn in bands of
+//   rows, each setting the mesh up again.  Such hypotheses are left to a second
+//   launch of 512 threads with half a CU's LDS, or all of it where images are
+//   large enough for objects beyond that too.  The second launch costs about
+//   4 us where nothing is left to it, so small images go without unless there
+//   are hypotheses enough to hide that.  (10,000 hypotheses of 1,500 voxels at
+//   320x240: 1,824 against 3,091 us; 700 of 6,000 at 301x227: 844 against 1,510.)
+//   512 threads for everything cost small objects 11 % (partly filled waves,
+//   work that every wave repeats).
 hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                hipStream_t st) {
-  return launch_render_score_bs<kBlock>(s, poses, N, logL, grad, st);
+  const bool g = grad != nullptr;
+  SceneDev t;
+  if (N <= kCUs && roomy_scene(s, 1024, g, &t)) {
+    launch_render_score_bs<1024>(t, poses, N, logL, grad, st);
+  } else if (N <= 2 * kCUs && roomy_scene(s, 512, g, &t)) {
+    launch_render_score_bs<512>(t, poses, N, logL, grad, st);
+  } else if (defers(s, N) && roomy_scene(s, rest_block(s), g, &t)) {
+    launch_render_score_bs<kBlock, kFirst>(s, poses, N, logL, grad, st);
+    if (rest_block(s) == 1024)
+      launch_render_score_bs<1024, kRest>(t, poses, N, logL, grad, st);
+    else
+      launch_render_score_bs<512, kRest>(t, poses, N, logL, grad, st);
+  } else {
+    launch_render_score_bs<kBlock>(s, poses, N, logL, grad, st);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace b3d

@@ -111,10 +111,6 @@ struct b3d_smc {
   int rows_R = 0, n_bands = 0;
   long long scored = 0;  // hypotheses rendered and scored since the last reset
   int zcap = 0;          // depth-buffer tile of the particles' scenes, tuned on the first step
-  // one work counter per launch of a step's scoring (persistent grids: the
-  // sampler's launches are few, long and of long items)
-  unsigned long long* counters = nullptr;
-  int max_groups = 0;
   std::vector<void*> owned;
 };
 
@@ -326,8 +322,6 @@ b3d_status b3d_smc_create(const b3d_mesh* const* types, int32_t n_types, const b
     S->n_bands = (K->H + S->rows_R - 1) / S->rows_R;
     if ((s = dev_alloc(S->owned, &S->partial, (size_t)M * S->n_bands * kMaxNoise))) return bail(s);
   }
-  S->max_groups = (M * n_types + kBatchGroup - 1) / kBatchGroup;
-  if ((s = dev_alloc(S->owned, &S->counters, 32 * (size_t)S->max_groups))) return bail(s);
   // the root cells (every type and face: dx, dy over the table less the
   // footprint, dth over a full turn) and the stage-0 hypotheses, the same
   // for every particle
@@ -489,7 +483,7 @@ b3d_status b3d_smc_step(b3d_smc* S, void* stream) {
                                      S->logL_h + (size_t)m * N0 + (size_t)o * 6 * n0, nullptr});
   BatchPlan plan;
   if (b3d_status s = plan_batch(items, false, &plan)) return s;
-  if (b3d_status s = run_batch_queue(plan, S->counters, st)) return s;
+  if (b3d_status s = run_batch(plan, st)) return s;
   for (const BatchItemDev& it : items) S->scored += it.N;
   for (int m = 0; m < M; ++m)
     if (rep[m] != m)
@@ -521,7 +515,7 @@ b3d_status b3d_smc_step(b3d_smc* S, void* stream) {
       items.push_back(BatchItemDev{scene_of(m, type_of[m]), S->hyp + 16 * (size_t)m * ns, ns,
                                    S->logL_h + (size_t)m * ns, nullptr});
     if (b3d_status s = plan_batch(items, false, &plan)) return s;
-    if (b3d_status s = run_batch_queue(plan, S->counters, st)) return s;
+    if (b3d_status s = run_batch(plan, st)) return s;
     S->scored += (long long)M * ns;
     B3D_CHECK_HIP(launch_sample(S->logL_h, M, ns, 1, key0, key1, ((uint32_t)i << 8) | (uint32_t)t, 0u, nullptr, S->idx,
                                 S->logw, st),

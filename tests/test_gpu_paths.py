@@ -69,3 +69,61 @@ def test_render_of_equal_voxels_matches_oracle(b3d, f, depth, kind):
     z = xyz[..., 2].cpu().numpy()
     assert np.abs(z - d)[same & (ids >= 0)].max(initial=0.0) <= 1e-5
     assert np.all(z[same & (ids < 0)] == 0.0)
+
+
+def scored(b3d, scene, P, grad):
+    L = b3d.render_score(scene, P, grad=grad)
+    return [x.cpu().numpy() for x in (L if grad else (L,))]
+
+
+# blocks of 1,024, 512 and 256 threads (up to 256, 512 and more hypotheses), an
+# object within the 256-thread block's depth buffer and beyond it (drawn by a
+# second launch: more pixels than 24,000, or than 56,000) and a caller's own
+# tile of one band of two rows: the same values whichever way
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("H,W,window", [(48, 64, 3), (151, 200, 5), (231, 300, 7)])
+def test_block_sizes_and_second_launch_give_the_same(b3d, H, W, window, grad):
+    rng = np.random.default_rng(H)
+    verts, tris = voxel_mesh(voxel_blob(400, rng))
+    f = 0.94 * W
+    cam = Camera(f, f, W / 2 + 0.2, H / 2 - 0.3, H, W)
+    K = b3d.intrinsics_of(cam)
+    P = f32(random_poses(rng, 600, 0.8, 0.03))
+    P[::7, 2, 3] = 2.5  # far ones fit the small block
+    P[5, :3, 3] = 0.0, 0.0, 0.05  # around the camera: every row of the image, bands in any block
+    P = dev(P)
+    scene = b3d.Scene(b3d.Mesh(f32(verts), tris), K, b3d.score_params(0.004, 0.05, 1.0, window))
+    xyz, _ = b3d.render_batch(scene.mesh, P[1:2].contiguous(), K)
+    noise = torch.as_tensor(rng.normal(0.0, 0.002, (H, W, 1)), dtype=torch.float32, device="cuda")
+    scene.set_observed((xyz[0] * (1.0 + noise)).contiguous())
+    whole = scored(b3d, scene, P, grad)
+    for n in (1, 256, 257, 512, 513):
+        for a, b in zip(scored(b3d, scene, P[:n].contiguous(), grad), whole):
+            np.testing.assert_array_equal(a, b[:n])
+    scene.set_tile(scene.tile_limits()[0])
+    for n in (40, 600):
+        for a, b in zip(scored(b3d, scene, P[:n].contiguous(), grad), whole):
+            np.testing.assert_array_equal(a, b[:n])
+
+
+@pytest.mark.parametrize("grad", [False, True])
+def test_batch_of_large_and_small_images_equals_per_scene_calls(b3d, grad):
+    rng = np.random.default_rng(3)
+    items = []
+    for H, W, n in [(48, 64, 70), (180, 240, 90), (231, 300, 30), (60, 100, 1), (151, 200, 11)]:
+        verts, tris = voxel_mesh(voxel_blob(300, rng))
+        cam = Camera(0.94 * W, 0.94 * W, W / 2, H / 2, H, W)
+        P = f32(random_poses(rng, n, 0.8, 0.03))
+        P[::5, 2, 3] = 2.0
+        scene = b3d.Scene(b3d.Mesh(f32(verts), tris), b3d.intrinsics_of(cam), b3d.score_params(0.004, 0.05, 1.0, 5))
+        xyz, _ = b3d.render_batch(scene.mesh, dev(P[:1]), b3d.intrinsics_of(cam))
+        scene.set_observed(xyz[0].contiguous())
+        items.append((scene, dev(P[:n])))
+    batch = b3d.Batch(items, grad=grad)
+    out = batch.run()
+    logL, g = out if grad else (out, None)
+    for i, (scene, P) in enumerate(items):
+        one = scored(b3d, scene, P, grad)
+        np.testing.assert_array_equal(logL[i].cpu().numpy(), one[0])
+        if grad:
+            np.testing.assert_array_equal(g[i].cpu().numpy(), one[1])
