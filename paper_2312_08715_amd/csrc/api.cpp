@@ -103,9 +103,6 @@ int default_zcap(const SceneDev& d, int blocks_per_cu) {
   return (int)((share > rest ? share - rest : 0) / kFusedBytesPerKey);
 }
 
-// two rows of the widest depth buffer (image width plus 2h each side)
-int min_zcap(const SceneDev& d) { return (4 * d.sc.h + 2) * (d.cam.W + 4 * d.sc.h); }
-
 int max_zcap(const SceneDev& d) {
   SceneDev t = d;
   t.zcap = 0;
@@ -158,17 +155,51 @@ struct b3d_batch {
 struct b3d_tracker;
 
 
-// Background-only per-pixel terms of every noise-grid point, as summed-area
-// tables (stream-ordered; the scene's own terms buffer is reused).
+// Background-only per-pixel terms of the scene's parameters as summed-area
+// tables (stream-ordered).
+static hipError_t scene_background(const b3d_scene* S, hipStream_t st) {
+  BgTablesDev B;
+  B.sc[0] = S->dev.sc;
+  B.sat = S->sat;
+  B.stride = 0;
+  B.n = 1;
+  return launch_background_tables(S->dev, B, st);
+}
+
+// The same for every noise-grid point.
 static b3d_status grid_background(b3d_scene* S, hipStream_t st) {
-  const size_t SP = (size_t)(S->K.H + 1) * (S->K.W + 1);
-  for (size_t k = 0; k < S->grid_params.size(); ++k) {
-    SceneDev t = S->dev;
-    if (b3d_status s = make_consts(&S->grid_params[k], S->K.H, S->K.W, &t.sc)) return s;
-    t.sat = S->grid_sat + 3 * SP * k;
-    B3D_CHECK_HIP(launch_background_terms(t, S->terms, st), "noise grid");
-  }
+  if (S->grid_params.empty()) return B3D_OK;
+  BgTablesDev B;
+  B.sat = S->grid_sat;
+  B.stride = 3 * (long long)(S->K.H + 1) * (S->K.W + 1);
+  B.n = (int)S->grid_params.size();
+  for (int k = 0; k < B.n; ++k)
+    if (b3d_status s = make_consts(&S->grid_params[k], S->K.H, S->K.W, &B.sc[k])) return s;
+  B3D_CHECK_HIP(launch_background_tables(S->dev, B, st), "noise grid");
   return B3D_OK;
+}
+
+// The static objects 0 .. n - 1 drawn into the cleared keys, in groups of one
+// launch each: all of them, then their pixels' depths on the triangles'
+// planes.  get(k, group, j) fills slot j of a group with object k.
+template <class F>
+static hipError_t draw_statics(int n, uint32_t id_base, const Cam& cam, unsigned long long* keys, hipStream_t st,
+                               F&& get) {
+  for (int pass = 0; pass < 2; ++pass) {
+    uint32_t id = id_base;
+    for (int k = 0; k < n; k += kStaticsGroup) {
+      StaticsDev G{};
+      G.n = std::min(kStaticsGroup, n - k);
+      for (int j = 0; j < G.n; ++j) {
+        get(k + j, G, j);
+        G.id_base[j] = id;
+        id += (uint32_t)G.m[j].T;
+      }
+      if (hipError_t e = pass == 0 ? launch_raster_statics(G, cam, keys, st) : launch_refine_statics(G, cam, keys, st))
+        return e;
+    }
+  }
+  return hipSuccess;
 }
 
 extern "C" {
@@ -459,10 +490,8 @@ b3d_status b3d_scene_create(const b3d_mesh* mesh, const b3d_intrinsics* K, const
     return fail(B3D_ESHAPE, "scene_create: image width %d too large for the fused kernel's LDS budget", W);
   }
   const size_t HW = (size_t)K->H * K->W, SP = (size_t)(K->H + 1) * (K->W + 1);
-  if (hipMalloc((void**)&S->terms, 3 * HW * sizeof(double)) != hipSuccess ||
-      hipMalloc((void**)&S->sat, 3 * SP * sizeof(double)) != hipSuccess ||
+  if (hipMalloc((void**)&S->sat, 3 * SP * sizeof(double)) != hipSuccess ||
       hipMalloc((void**)&S->bg, HW * sizeof(unsigned long long)) != hipSuccess) {
-    (void)hipFree(S->terms);
     (void)hipFree(S->sat);
     (void)hipFree(S->bg);
     delete S;
@@ -477,7 +506,6 @@ b3d_status b3d_scene_create(const b3d_mesh* mesh, const b3d_intrinsics* K, const
 b3d_status b3d_scene_destroy(b3d_scene* S) {
   if (!S) return B3D_OK;
   (void)hipDeviceSynchronize();
-  (void)hipFree(S->terms);
   (void)hipFree(S->sat);
   (void)hipFree(S->bg);
   (void)hipFree(S->grid_sat);
@@ -501,22 +529,23 @@ b3d_status b3d_scene_set_background(b3d_scene* S, const b3d_mesh* const* meshes,
     if (!meshes[i]) return fail(B3D_EINVAL, "scene_set_background: NULL mesh %d", i);
   hipStream_t st = (hipStream_t)stream;
   const size_t HW = (size_t)S->K.H * S->K.W;
-  B3D_CHECK_HIP(launch_fill_keys(S->bg, HW, st), "scene_set_background");
   uint64_t base = (uint64_t)S->mesh->T;
   for (int i = 0; i < n; ++i) {
     if (base + (uint64_t)meshes[i]->T >= 0xffffffffull)
       return fail(B3D_ESHAPE, "scene_set_background: too many triangles for 32-bit ids");
-    B3D_CHECK_HIP(launch_raster_global(meshes[i]->dev, S->dev.cam, poses + 16 * (size_t)i, (uint32_t)base, S->bg, st),
-                  "scene_set_background");
     base += (uint64_t)meshes[i]->T;
   }
-  base = (uint64_t)S->mesh->T;
-  for (int i = 0; i < n; ++i) {
-    B3D_CHECK_HIP(launch_refine_global(meshes[i]->dev, S->dev.cam, poses + 16 * (size_t)i, nullptr, (uint32_t)base,
-                                       S->bg, st),
-                  "scene_set_background");
-    base += (uint64_t)meshes[i]->T;
-  }
+  B3D_CHECK_HIP(launch_fill_keys(S->bg, HW, st), "scene_set_background");
+  B3D_CHECK_HIP(draw_statics(n, (uint32_t)S->mesh->T, S->dev.cam, S->bg, st,
+                             [&](int k, StaticsDev& G, int j) {
+                               const float* p = poses + 16 * (size_t)k;
+                               G.m[j] = meshes[k]->dev;
+                               for (int r = 0; r < 3; ++r) {
+                                 for (int c = 0; c < 3; ++c) G.pose[j].r[3 * r + c] = p[4 * r + c];
+                                 G.pose[j].t[r] = p[4 * r + 3];
+                               }
+                             }),
+                "scene_set_background");
   S->has_bg = true;
   S->dev.bg = S->bg;
   return B3D_OK;
@@ -525,7 +554,7 @@ b3d_status b3d_scene_set_background(b3d_scene* S, const b3d_mesh* const* meshes,
 b3d_status b3d_scene_set_observed(b3d_scene* S, const float* observed, void* stream) {
   if (!S || !observed) return fail(B3D_EINVAL, "scene_set_observed: NULL pointer");
   S->dev.obs = observed;
-  B3D_CHECK_HIP(launch_background_terms(S->dev, S->terms, (hipStream_t)stream), "scene_set_observed");
+  B3D_CHECK_HIP(scene_background(S, (hipStream_t)stream), "scene_set_observed");
   if (b3d_status s = grid_background(S, (hipStream_t)stream)) return s;
   S->observed = true;
   return B3D_OK;
@@ -539,7 +568,7 @@ b3d_status b3d_scene_set_params(b3d_scene* S, const b3d_score_params* p, void* s
   S->params = *p;
   S->dev.sc = sc;
   if (S->observed)
-    B3D_CHECK_HIP(launch_background_terms(S->dev, S->terms, (hipStream_t)stream), "scene_set_params");
+    B3D_CHECK_HIP(scene_background(S, (hipStream_t)stream), "scene_set_params");
   return B3D_OK;
 }
 
@@ -1006,6 +1035,8 @@ b3d_status b3d_adam_pose_step(float* poses, const float* grad, int32_t gstride, 
 
 // Image rows per block of the tracker's refinement steps.
 constexpr int kRefineRows = 8;
+// Words of its partial sums: nine per block and the count of finished blocks.
+static size_t refine_words(int H) { return 9 * (size_t)((H + kRefineRows - 1) / kRefineRows) + 1; }
 
 struct b3d_tracker {
   int M = 0;
@@ -1025,7 +1056,7 @@ struct b3d_tracker {
   unsigned long long* objkeys = nullptr;  // [H][W] the updated object drawn alone
   float* hyp = nullptr;      // [N][16]
   float* logL = nullptr;     // [N]
-  float* partial = nullptr;  // [ceil(H / kRefineRows)][9] band sums of a refinement step
+  float* partial = nullptr;  // [refine_words] band sums of a refinement step and its count of finished blocks
   float* adam = nullptr;     // [M][12] Adam moments of the refinement
   size_t obs_bytes = 0;
   hipStream_t cap = nullptr;
@@ -1041,17 +1072,15 @@ static b3d_status tracker_background(b3d_tracker* T, int o, hipStream_t st) {
   const size_t HW = (size_t)S->K.H * S->K.W;
   if (T->M > 1) {
     B3D_CHECK_HIP(launch_fill_keys(S->bg, HW, st), "tracker");
-    uint32_t base = (uint32_t)S->mesh->T;
-    for (int k = 0; k < T->M; ++k) {
-      if (k == o) continue;
-      B3D_CHECK_HIP(launch_raster_global_dev(T->meshes[k]->dev, S->dev.cam, T->poses + 16 * k, base, S->bg, st),
-                    "tracker");
-      B3D_CHECK_HIP(launch_refine_global(T->meshes[k]->dev, S->dev.cam, nullptr, T->poses + 16 * k, base, S->bg, st),
-                    "tracker");
-      base += (uint32_t)T->meshes[k]->T;
-    }
+    B3D_CHECK_HIP(draw_statics(T->M - 1, (uint32_t)S->mesh->T, S->dev.cam, S->bg, st,
+                               [&](int k, StaticsDev& G, int j) {
+                                 const int other = k < o ? k : k + 1;
+                                 G.m[j] = T->meshes[other]->dev;
+                                 G.dev_pose[j] = T->poses + 16 * other;
+                               }),
+                  "tracker");
   }
-  B3D_CHECK_HIP(launch_background_terms(S->dev, S->terms, st), "tracker");
+  B3D_CHECK_HIP(scene_background(S, st), "tracker");
   return B3D_OK;
 }
 
@@ -1085,8 +1114,12 @@ static b3d_status tracker_record(b3d_tracker* T, hipStream_t st) {
       const SceneDev& d = S->dev;
       const size_t HW = (size_t)d.cam.H * d.cam.W;
       B3D_CHECK_HIP(launch_fill_keys(T->objkeys, HW, st), "tracker");
-      B3D_CHECK_HIP(launch_raster_global_dev(d.mesh, d.cam, T->poses + 16 * o, 0u, T->objkeys, st), "tracker");
-      B3D_CHECK_HIP(launch_refine_global(d.mesh, d.cam, nullptr, T->poses + 16 * o, 0u, T->objkeys, st), "tracker");
+      B3D_CHECK_HIP(draw_statics(1, 0u, d.cam, T->objkeys, st,
+                                 [&](int, StaticsDev& G, int j) {
+                                   G.m[j] = d.mesh;
+                                   G.dev_pose[j] = T->poses + 16 * o;
+                                 }),
+                    "tracker");
       B3D_CHECK_HIP(launch_track_gate(T->objkeys, T->M > 1 ? S->bg : nullptr, T->obs, d.cam, d.sc.h,
                                       3.0f * S->params.sigma, tp.min_visible, tp.widen, T->prev + 16 * o,
                                       T->poses + 16 * o, T->motion + 12 * o, T->gate + 4 * o, st),
@@ -1203,7 +1236,7 @@ b3d_status b3d_tracker_create(const b3d_mesh* const* meshes, int32_t M, const b3
       hipMalloc((void**)&T->objkeys, sizeof(unsigned long long) * (size_t)K->H * K->W) != hipSuccess ||
       hipMalloc((void**)&T->hyp, sizeof(float) * 16 * (size_t)n) != hipSuccess ||
       hipMalloc((void**)&T->logL, sizeof(float) * (size_t)n) != hipSuccess ||
-      hipMalloc((void**)&T->partial, sizeof(float) * 9 * (size_t)((K->H + kRefineRows - 1) / kRefineRows)) != hipSuccess ||
+      hipMalloc((void**)&T->partial, sizeof(float) * refine_words(K->H)) != hipSuccess ||
       hipMalloc((void**)&T->adam, sizeof(float) * 12 * (size_t)M) != hipSuccess)
     return cleanup(B3D_ENOMEM, "tracker_create: device allocation failed");
   T->prev = T->poses + 16 * M;
@@ -1217,7 +1250,8 @@ b3d_status b3d_tracker_create(const b3d_mesh* const* meshes, int32_t M, const b3
     state[44 * M + 4 * o + 2] = 1.0f;  // stage 0 at its own extents
   }
   if (hipMemcpy(T->poses, state.data(), sizeof(float) * state.size(), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(T->obs, 0, T->obs_bytes) != hipSuccess)
+      hipMemset(T->obs, 0, T->obs_bytes) != hipSuccess ||
+      hipMemset(T->partial, 0, sizeof(float) * refine_words(K->H)) != hipSuccess)
     return cleanup(B3D_EHIP, "tracker_create: initial copy failed");
   for (int o = 0; o < M; ++o) {
     b3d_scene* S = nullptr;

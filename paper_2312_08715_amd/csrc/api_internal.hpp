@@ -30,7 +30,6 @@ Cam make_cam(const b3d_intrinsics* K);
 // Likelihood constants of eq. (1) for an H x W image (validates p).
 b3d_status make_consts(const b3d_score_params* p, int H, int W, ScoreConsts* sc);
 int default_zcap(const SceneDev& d, int blocks_per_cu);
-int min_zcap(const SceneDev& d);
 int max_zcap(const SceneDev& d);
 
 // Noise-grid constants for sigma[A] x p_out[B] (other parameters from base);
@@ -83,7 +82,6 @@ struct b3d_scene {
   b3d_score_params params{};
   b3d::SceneDev dev{};
   unsigned long long* bg = nullptr;  // background keys [H][W]
-  double* terms = nullptr;           // [3][H][W]
   double* sat = nullptr;             // [3][(H+1)(W+1)]
   bool has_bg = false;
   bool observed = false;

@@ -187,6 +187,7 @@ struct GridDev {
 // LDS bytes of the fused kernel: fixed part + kFusedBytesPerKey per depth key.
 constexpr size_t kFusedBytesPerKey = 8;
 size_t fused_lds_bytes(const SceneDev& s);
+int min_zcap(const SceneDev& s);
 
 hipError_t launch_render_batch(const MeshDev& m, const Cam& cam, const float* poses, int N, float* xyz, int* tri,
                                int zcap, hipStream_t st);
@@ -220,11 +221,29 @@ hipError_t launch_render_score_count(const SceneDev& s, const float* poses, int 
 hipError_t launch_batch(const BatchGroupDev& g, bool grad, size_t lds, hipStream_t st);
 // scene preparation
 hipError_t launch_fill_keys(unsigned long long* keys, size_t n, hipStream_t st);
-hipError_t launch_raster_global(const MeshDev& m, const Cam& cam, const float* pose16_host, uint32_t id_base,
-                                unsigned long long* keys, hipStream_t st);
-hipError_t launch_refine_global(const MeshDev& m, const Cam& cam, const float* pose16_host, const float* pose16_dev,
-                                uint32_t id_base, unsigned long long* keys, hipStream_t st);
-hipError_t launch_background_terms(const SceneDev& s, double* terms, hipStream_t st);
+// Up to kStaticsGroup static objects of a scene, drawn together: poses by value
+// or, where dev_pose is set, from device memory (float[16]).
+constexpr int kStaticsGroup = 8;
+struct StaticsDev {
+  MeshDev m[kStaticsGroup];
+  Pose pose[kStaticsGroup];
+  const float* dev_pose[kStaticsGroup];
+  uint32_t id_base[kStaticsGroup];
+  int n;
+};
+static_assert(sizeof(StaticsDev) <= 3000, "the static objects must fit the kernel-argument segment");
+hipError_t launch_raster_statics(const StaticsDev& G, const Cam& cam, unsigned long long* keys, hipStream_t st);
+hipError_t launch_refine_statics(const StaticsDev& G, const Cam& cam, unsigned long long* keys, hipStream_t st);
+// Background-only terms of the scene's observed image as summed-area tables,
+// for n sets of parameters: those of set y at sat + y stride, three tables
+// [(H + 1)(W + 1)] each (l, dl/dp_out, dl/dsigma).
+struct BgTablesDev {
+  ScoreConsts sc[kMaxNoise];
+  double* sat;
+  long long stride;
+  int n;
+};
+hipError_t launch_background_tables(const SceneDev& s, const BgTablesDev& B, hipStream_t st);
 
 // hypotheses and sampling
 hipError_t launch_enumerate(const GridDev& g, const float* centres, int P, uint32_t key0, uint32_t key1,
@@ -242,8 +261,10 @@ hipError_t launch_pose_retract_backward(const float* xi, const float* grad, cons
 hipError_t launch_refine_pose(const SceneDev& s, float* poses, int N, int n_refine, float lr_t, float lr_r, float b1,
                               float b2, float eps, hipStream_t st);
 // n_refine Adam steps of one pose, each over row bands of R image rows (one
-// block per band, ceil(H / R) blocks) then a one-thread reduce + update.
-// partial: device float[ceil(H / R)][9]; state: device float[12] (moments).
+// block per band, ceil(H / R) blocks, the last to finish updating the pose).
+// partial: device float[ceil(H / R)][9] and one more word, which has to be
+// zero before the first step and is zero after each; state: device float[12]
+// (moments).
 hipError_t launch_refine_banded(const SceneDev& s, float* pose, int n_refine, float lr_t, float lr_r, float b1,
                                 float b2, float eps, int R, float* partial, float* state, hipStream_t st);
 hipError_t launch_adam_pose(float* poses, const float* grad, int gstride, float* state, int N, int iter, float lr_t,
@@ -260,7 +281,5 @@ hipError_t launch_track_gate(const unsigned long long* objkeys, const unsigned l
                              const Cam& cam, int h, float tol, float min_visible, float widen, const float* prev,
                              float* pose, float* motion, float* gate, hipStream_t st);
 hipError_t launch_argmax_pose(const float* logL, const float* poses, int N, float* out, hipStream_t st);
-hipError_t launch_raster_global_dev(const MeshDev& m, const Cam& cam, const float* pose16_dev, uint32_t id_base,
-                                    unsigned long long* keys, hipStream_t st);
 
 }  // namespace b3d

@@ -39,6 +39,9 @@ static size_t fused_lds_bytes(const SceneDev& s, int bs, int zcap) {
 }
 size_t fused_lds_bytes(const SceneDev& s) { return fused_lds_bytes(s, kBlock, s.zcap); }
 
+// Two rows of the widest depth buffer (image width plus 2h each side).
+int min_zcap(const SceneDev& s) { return (4 * s.sc.h + 2) * (s.cam.W + 4 * s.sc.h); }
+
 // Bytes beyond these that the adjoint needs: blocks of more than kBlock threads
 // keep the window weights in an area of their own, as many as depth keys; and
 // the weights of one row and the halo together with the waves' queues exceed
@@ -620,51 +623,68 @@ hipError_t launch_refine_pose(const SceneDev& s, float* poses, int N, int n_refi
 // rows [b R, (b + 1) R) of the pose's region (render, windows, adjoint) and
 // writes its terms to partial[9 b .. 9 b + 9) (logL, d(dt, dw), d sigma,
 // d p_out, without the background outside the region, which the pose
-// gradient does not involve).
+// gradient does not involve).  The block that finishes last (the count of
+// finished blocks follows the partial sums and is left at zero) adds the bands
+// in band order, in double, and updates the pose; the moments live in
+// state[0..12) (zero at iter 1).
+// A step is a few dozen blocks on 256 CUs, so it lasts as long as one block:
+// 1,024 threads and a depth buffer that holds the band.  (A 160x120 frame's
+// step: 36 us; with 256 threads and the update in a launch of its own, 53 + 8.)
+constexpr int kBandBlock = 1024;
 template <int RM>
-__global__ __launch_bounds__(kBlock, 4) void k_refine_bands(SceneDev s, const float* __restrict__ pose, int R,
-                                                            float* __restrict__ partial) {
+__global__ __launch_bounds__(kBandBlock, 4) void k_refine_bands(SceneDev s, float* pose, int R, float* partial,
+                                                                float* __restrict__ state, int iter, float lr_t,
+                                                                float lr_r, float b1, float b2, float eps) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int b = blockIdx.x;
-  render_score_one<true, false, RM>(s, pose, partial + 9 * b, partial + 9 * b + 1, smem, nullptr, b * R,
-                                    (b + 1) * R);
-}
-
-// The band sums in band order (double), then the Adam update of the pose;
-// the moments live in state[0..12) (zero at iter 1).  One thread.
-__global__ void k_refine_update(float* __restrict__ pose, const float* __restrict__ partial, int nb,
-                                float* __restrict__ state, int iter, float lr_t, float lr_r, float b1, float b2,
-                                float eps) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  float g[6], m[6], v[6], P[16];
-  for (int k = 0; k < 6; ++k) {
+  const int b = blockIdx.x, nb = gridDim.x;
+  render_score_one<true, false, RM, kBandBlock>(s, pose, partial + 9 * b, partial + 9 * b + 1, smem, nullptr, b * R,
+                                                (b + 1) * R);
+  __threadfence();  // each writer's terms, before the count
+  __syncthreads();
+  unsigned* count = reinterpret_cast<unsigned*>(partial + 9 * nb);
+  if (threadIdx.x >= 64) return;
+  unsigned done = 0;
+  if (threadIdx.x == 0) done = atomicAdd(count, 1u);
+  if (__builtin_amdgcn_readfirstlane(done) != (unsigned)nb - 1u) return;
+  __threadfence();
+  // lane k < 6: the bands of component k in order
+  float g = 0.0f;
+  if (threadIdx.x < 6) {
     double t = 0.0;
-    for (int b = 0; b < nb; ++b) t += (double)partial[9 * b + 1 + k];
-    g[k] = (float)t;
+    for (int i = 0; i < nb; ++i)
+      t += (double)__hip_atomic_load(partial + 9 * i + 1 + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    g = (float)t;
+  }
+  float gk[6], m[6], v[6], P[16];
+  for (int k = 0; k < 6; ++k) gk[k] = __shfl(g, k, 64);
+  if (threadIdx.x != 0) return;
+  for (int k = 0; k < 6; ++k) {
     m[k] = iter == 1 ? 0.0f : state[k];
     v[k] = iter == 1 ? 0.0f : state[6 + k];
   }
   for (int k = 0; k < 16; ++k) P[k] = pose[k];
-  adam_update(P, g, m, v, iter, lr_t, lr_r, b1, b2, eps);
+  adam_update(P, gk, m, v, iter, lr_t, lr_r, b1, b2, eps);
   for (int k = 0; k < 16; ++k) pose[k] = P[k];
   for (int k = 0; k < 6; ++k) {
     state[k] = m[k];
     state[6 + k] = v[k];
   }
+  *count = 0u;
 }
 
 hipError_t launch_refine_banded(const SceneDev& s, float* pose, int n_refine, float lr_t, float lr_r, float b1,
                                 float b2, float eps, int R, float* partial, float* state, hipStream_t st) {
-  const int nb = (s.cam.H + R - 1) / R;
-  const size_t lds = launch_lds_bytes(s, kBlock, s.zcap, true);
-  for (int it = 1; it <= n_refine; ++it) {
-    if (s.mesh.has_big)
-      hipLaunchKernelGGL(k_refine_bands<kRasterBig>, dim3(nb), dim3(kBlock), lds, st, s, pose, R, partial);
-    else
-      hipLaunchKernelGGL(k_refine_bands<kRasterSmall>, dim3(nb), dim3(kBlock), lds, st, s, pose, R, partial);
-    hipLaunchKernelGGL(k_refine_update, dim3(1), dim3(64), 0, st, pose, partial, nb, state, it, lr_t, lr_r, b1, b2,
-                       eps);
-  }
+  const int nb = (s.cam.H + R - 1) / R, h = s.sc.h;
+  // the depth buffer and the weights of R rows at the image's width; the
+  // widest images fall back to bands within the block
+  SceneDev t = s;
+  t.zcap = std::max(min_zcap(s), (R + 4 * h) * (s.cam.W + 4 * h));
+  const size_t fixed = launch_lds_bytes(s, kBandBlock, 0, true);
+  t.zcap = std::min(t.zcap, (int)((kLdsPerCU - fixed) / (kFusedBytesPerKey + 4)));
+  const size_t lds = launch_lds_bytes(t, kBandBlock, t.zcap, true);
+  for (int it = 1; it <= n_refine; ++it)
+    hipLaunchKernelGGL((s.mesh.has_big ? k_refine_bands<kRasterBig> : k_refine_bands<kRasterSmall>), dim3(nb),
+                       dim3(kBandBlock), lds, st, t, pose, R, partial, state, it, lr_t, lr_r, b1, b2, eps);
   return hipGetLastError();
 }
 

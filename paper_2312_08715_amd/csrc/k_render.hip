@@ -231,91 +231,115 @@ hipError_t launch_fill_keys(unsigned long long* keys, size_t n, hipStream_t st) 
   return hipGetLastError();
 }
 
-// One thread per (triangle, slice of its rows), whole image, global 64-bit
-// atomicMin: used per scene to draw the static objects.  Slicing the rows
-// keeps a triangle that spans the image (a table top) from serialising on
-// one thread; the minimum does not depend on the order.
+// The static objects drawn into a full-image key buffer with global 64-bit
+// atomicMin: mesh blockIdx.z, one lane per triangle.  A lane walks a small box
+// itself; a box of more than kBigCentres centres (a table top, a wall) is walked
+// by its whole wave, and for meshes with large primitives the rows of such
+// boxes are dealt over kRasterSlices blocks, so that a triangle that spans the
+// image does not serialise on one thread (with the rows dealt over blocks but
+// one thread per row, a table top at 320x240 took 240 us).  The minimum does
+// not depend on the order.
 constexpr int kRasterSlices = 32;
 
-__global__ void k_raster_global(MeshDev m, Cam cam, Pose P, uint32_t id_base, unsigned long long* keys) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int slice = blockIdx.y;
-  if (i >= m.T) return;
-  const int4 tr = m.tris[i];
-  float4 pv[3];
+__global__ __launch_bounds__(256) void k_raster_statics(StaticsDev G, Cam cam, unsigned long long* keys) {
+  const MeshDev m = G.m[blockIdx.z];
+  const int slice = blockIdx.y, slices = m.has_big ? kRasterSlices : 1;
+  if (slice >= slices || (int)blockIdx.x * 256 >= m.T) return;
+  const uint32_t id_base = G.id_base[blockIdx.z];
+  const Pose P = G.dev_pose[blockIdx.z] ? load_pose(G.dev_pose[blockIdx.z]) : G.pose[blockIdx.z];
+  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int4 tr = m.tris[min(i, m.T - 1)];
+  float u[3], v[3], iz[3], zmin = 3.0e38f;
   const int vi[3] = {tr.x, tr.y, tr.z};
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float4 o = m.verts[vi[k]];
     const float3 p = xform(P, o.x, o.y, o.z);
-    const float iz = 1.0f / p.z;
-    pv[k] = make_float4(cam.fx * p.x * iz + cam.cx, cam.fy * p.y * iz + cam.cy, p.z, iz);
+    iz[k] = 1.0f / p.z;
+    u[k] = cam.fx * p.x * iz[k] + cam.cx;
+    v[k] = cam.fy * p.y * iz[k] + cam.cy;
+    zmin = fminf(zmin, p.z);
   }
-  const float4 p0 = pv[0], p1 = pv[1], p2 = pv[2];
-  if (p0.z <= cam.znear || p1.z <= cam.znear || p2.z <= cam.znear) return;
-  const float area = (p1.x - p0.x) * (p2.y - p0.y) - (p2.x - p0.x) * (p1.y - p0.y);
-  if (!(area < 0.0f)) return;
-  const float umin = fminf(p0.x, fminf(p1.x, p2.x)), umax = fmaxf(p0.x, fmaxf(p1.x, p2.x));
-  const float vmin = fminf(p0.y, fminf(p1.y, p2.y)), vmax = fmaxf(p0.y, fmaxf(p1.y, p2.y));
-  const float fc0 = ceilf(fmaxf(umin - 0.5f, 0.0f)), fc1 = floorf(fminf(umax - 0.5f, (float)(cam.W - 1)));
-  const float fr0 = ceilf(fmaxf(vmin - 0.5f, 0.0f)), fr1 = floorf(fminf(vmax - 0.5f, (float)(cam.H - 1)));
-  if (!(fc0 <= fc1) || !(fr0 <= fr1)) return;
+  const float area = (u[1] - u[0]) * (v[2] - v[0]) - (u[2] - u[0]) * (v[1] - v[0]);
+  const float fc0 = ceilf(fmaxf(fminf(u[0], fminf(u[1], u[2])) - 0.5f, 0.0f));
+  const float fc1 = floorf(fminf(fmaxf(u[0], fmaxf(u[1], u[2])) - 0.5f, (float)(cam.W - 1)));
+  const float fr0 = ceilf(fmaxf(fminf(v[0], fminf(v[1], v[2])) - 0.5f, 0.0f));
+  const float fr1 = floorf(fminf(fmaxf(v[0], fmaxf(v[1], v[2])) - 0.5f, (float)(cam.H - 1)));
+  const bool draw = i < m.T && zmin > cam.znear && area < 0.0f && fc0 <= fc1 && fr0 <= fr1;
+  int box[4] = {0, -1, 0, -1};
+  if (draw) {
+    box[0] = (int)fc0;
+    box[1] = (int)fc1;
+    box[2] = (int)fr0;
+    box[3] = (int)fr1;
+  }
   const float inv_area = 1.0f / area;
-  const float e0x = p2.x - p1.x, e0y = p2.y - p1.y;
-  const float e1x = p0.x - p2.x, e1y = p0.y - p2.y;
-  const float e2x = p1.x - p0.x, e2y = p1.y - p0.y;
-  for (int r = (int)fr0 + slice; r <= (int)fr1; r += kRasterSlices) {
-    const float py = (float)r + 0.5f;
-    for (int c = (int)fc0; c <= (int)fc1; ++c) {
-      const float px = (float)c + 0.5f;
-      const float w0 = e0x * (py - p1.y) - e0y * (px - p1.x);
-      const float w1 = e1x * (py - p2.y) - e1y * (px - p2.x);
-      const float w2 = e2x * (py - p0.y) - e2y * (px - p0.x);
-      if (w0 > 0.0f || w1 > 0.0f || w2 > 0.0f) continue;
-      const float invz = (w0 * p0.w + w1 * p1.w + w2 * p2.w) * inv_area;
-      const float z = __builtin_amdgcn_rcpf(invz);
-      if (!(z > 0.0f)) continue;
-      atomicMin(&keys[(size_t)r * cam.W + c], pack_key(z, id_base + (uint32_t)i));
+  auto centre = [&](int r, int c, uint32_t id, const float(&a)[3], const float(&b)[3], const float(&w)[3], float ia) {
+    const float py = (float)r + 0.5f, px = (float)c + 0.5f;
+    const float e0x = a[2] - a[1], e0y = b[2] - b[1];
+    const float e1x = a[0] - a[2], e1y = b[0] - b[2];
+    const float e2x = a[1] - a[0], e2y = b[1] - b[0];
+    const float w0 = e0x * (py - b[1]) - e0y * (px - a[1]);
+    const float w1 = e1x * (py - b[2]) - e1y * (px - a[2]);
+    const float w2 = e2x * (py - b[0]) - e2y * (px - a[0]);
+    if (w0 > 0.0f || w1 > 0.0f || w2 > 0.0f) return;
+    const float z = __builtin_amdgcn_rcpf((w0 * w[0] + w1 * w[1] + w2 * w[2]) * ia);
+    if (!(z > 0.0f)) return;
+    atomicMin(&keys[(size_t)r * cam.W + c], pack_key(z, id));
+  };
+  const bool large = (box[1] - box[0] + 1) * (box[3] - box[2] + 1) > kBigCentres;
+  if (slice == 0 && !large)
+    for (int r = box[2]; r <= box[3]; ++r)
+      for (int c = box[0]; c <= box[1]; ++c) centre(r, c, id_base + (uint32_t)i, u, v, iz, inv_area);
+  unsigned long long left = __ballot(large);
+  while (left != 0ull) {
+    const int b = __ffsll(left) - 1;
+    left &= left - 1ull;
+    float bu[3], bv[3], bw[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      bu[k] = __shfl(u[k], b, 64);
+      bv[k] = __shfl(v[k], b, 64);
+      bw[k] = __shfl(iz[k], b, 64);
     }
+    const float bi = __shfl(inv_area, b, 64);
+    const int c0 = __shfl(box[0], b, 64), c1 = __shfl(box[1], b, 64);
+    const int q0 = __shfl(box[2], b, 64), q1 = __shfl(box[3], b, 64);
+    const uint32_t id = id_base + (uint32_t)(i - lane + b);
+    for (int r = q0 + slice; r <= q1; r += slices)
+      for (int c = c0 + lane; c <= c1; c += 64) centre(r, c, id, bu, bv, bw, bi);
   }
 }
 
-// Exact plane depth for every pixel of a full-image key buffer drawn by this
-// mesh (see plane_depth); the pose comes from `pose16_dev` when not null.
-__global__ void k_refine_global(MeshDev m, Cam cam, Pose P, const float* __restrict__ pose16_dev, uint32_t id_base,
-                                unsigned long long* keys) {
+// Exact plane depth for every pixel of a full-image key buffer drawn by one of
+// these meshes (see plane_depth).
+__global__ void k_refine_statics(StaticsDev G, Cam cam, unsigned long long* keys) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= cam.H * cam.W) return;
   const unsigned long long key = keys[p];
   if (key == kEmptyKey) return;
-  const uint32_t id = key_id(key) - id_base;
-  if (id >= (uint32_t)m.T) return;
-  const Pose Q = pose16_dev ? load_pose(pose16_dev) : P;
-  const int r = p / cam.W, c = p - r * cam.W;
-  keys[p] = pack_key(plane_depth(m, plane_view(Q, cam), id, r, c), key_id(key));
+  for (int j = 0; j < G.n; ++j) {
+    const uint32_t id = key_id(key) - G.id_base[j];
+    if (id >= (uint32_t)G.m[j].T) continue;
+    const Pose Q = G.dev_pose[j] ? load_pose(G.dev_pose[j]) : G.pose[j];
+    const int r = p / cam.W, c = p - r * cam.W;
+    keys[p] = pack_key(plane_depth(G.m[j], plane_view(Q, cam), id, r, c), key_id(key));
+  }
 }
 
-hipError_t launch_raster_global(const MeshDev& m, const Cam& cam, const float* pose16, uint32_t id_base,
-                                unsigned long long* keys, hipStream_t st) {
-  Pose P;
-  for (int i = 0; i < 3; ++i) {
-    for (int j = 0; j < 3; ++j) P.r[3 * i + j] = pose16[4 * i + j];
-    P.t[i] = pose16[4 * i + 3];
+hipError_t launch_raster_statics(const StaticsDev& G, const Cam& cam, unsigned long long* keys, hipStream_t st) {
+  int T = 1, slices = 1;
+  for (int j = 0; j < G.n; ++j) {
+    T = max(T, G.m[j].T);
+    if (G.m[j].has_big) slices = kRasterSlices;
   }
-  hipLaunchKernelGGL(k_raster_global, dim3((m.T + 255) / 256, kRasterSlices), dim3(256), 0, st, m, cam, P, id_base,
-                     keys);
+  hipLaunchKernelGGL(k_raster_statics, dim3((T + 255) / 256, slices, G.n), dim3(256), 0, st, G, cam, keys);
   return hipGetLastError();
 }
 
-hipError_t launch_refine_global(const MeshDev& m, const Cam& cam, const float* pose16_host, const float* pose16_dev,
-                                uint32_t id_base, unsigned long long* keys, hipStream_t st) {
-  Pose P = {};
-  if (pose16_host)
-    for (int i = 0; i < 3; ++i) {
-      for (int j = 0; j < 3; ++j) P.r[3 * i + j] = pose16_host[4 * i + j];
-      P.t[i] = pose16_host[4 * i + 3];
-    }
-  hipLaunchKernelGGL(k_refine_global, dim3((cam.H * cam.W + 255) / 256), dim3(256), 0, st, m, cam, P, pose16_dev,
-                     id_base, keys);
+hipError_t launch_refine_statics(const StaticsDev& G, const Cam& cam, unsigned long long* keys, hipStream_t st) {
+  hipLaunchKernelGGL(k_refine_statics, dim3((cam.H * cam.W + 255) / 256), dim3(256), 0, st, G, cam, keys);
   return hipGetLastError();
 }
 

@@ -237,14 +237,15 @@ hipError_t launch_track_gate(const unsigned long long* objkeys, const unsigned l
 }
 
 // out = poses[argmax logL] (ties to the lowest index); one block.
-__global__ __launch_bounds__(kBlock) void k_argmax_pose(const float* __restrict__ logL, const float* __restrict__ poses,
+constexpr int kArgmaxBlock = 1024;
+__global__ __launch_bounds__(kArgmaxBlock) void k_argmax_pose(const float* __restrict__ logL, const float* __restrict__ poses,
                                                         int N, float* __restrict__ out) {
-  __shared__ float rv[kWaves];
-  __shared__ int ri[kWaves];
+  __shared__ float rv[(kArgmaxBlock / 64)];
+  __shared__ int ri[(kArgmaxBlock / 64)];
   __shared__ int best;
   float bv = -INFINITY;
   int bi = -1;
-  for (int n = threadIdx.x; n < N; n += kBlock)
+  for (int n = threadIdx.x; n < N; n += kArgmaxBlock)
     if (bi < 0 || logL[n] > bv) {
       bv = logL[n];
       bi = n;
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(kBlock) void k_argmax_pose(const float* __restrict_
   if (threadIdx.x == 0) {
     bv = rv[0];
     bi = ri[0];
-    for (int i = 1; i < kWaves; ++i)
+    for (int i = 1; i < (kArgmaxBlock / 64); ++i)
       if (ri[i] >= 0 && (bi < 0 || rv[i] > bv || (rv[i] == bv && ri[i] < bi))) {
         bv = rv[i];
         bi = ri[i];
@@ -278,58 +279,7 @@ __global__ __launch_bounds__(kBlock) void k_argmax_pose(const float* __restrict_
 }
 
 hipError_t launch_argmax_pose(const float* logL, const float* poses, int N, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_argmax_pose, dim3(1), dim3(kBlock), 0, st, logL, poses, N, out);
-  return hipGetLastError();
-}
-
-// As k_raster_global, with the pose read from device memory.
-__global__ void k_raster_global_dev(MeshDev m, Cam cam, const float* __restrict__ pose16, uint32_t id_base,
-                                    unsigned long long* keys) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m.T) return;
-  const Pose P = load_pose(pose16);
-  const int4 tr = m.tris[i];
-  float4 pv[3];
-  const int vi[3] = {tr.x, tr.y, tr.z};
-  for (int k = 0; k < 3; ++k) {
-    const float4 o = m.verts[vi[k]];
-    const float3 p = xform(P, o.x, o.y, o.z);
-    const float iz = 1.0f / p.z;
-    pv[k] = make_float4(cam.fx * p.x * iz + cam.cx, cam.fy * p.y * iz + cam.cy, p.z, iz);
-  }
-  const float4 p0 = pv[0], p1 = pv[1], p2 = pv[2];
-  if (p0.z <= cam.znear || p1.z <= cam.znear || p2.z <= cam.znear) return;
-  const float area = (p1.x - p0.x) * (p2.y - p0.y) - (p2.x - p0.x) * (p1.y - p0.y);
-  if (!(area < 0.0f)) return;
-  const float umin = fminf(p0.x, fminf(p1.x, p2.x)), umax = fmaxf(p0.x, fmaxf(p1.x, p2.x));
-  const float vmin = fminf(p0.y, fminf(p1.y, p2.y)), vmax = fmaxf(p0.y, fmaxf(p1.y, p2.y));
-  const float fc0 = ceilf(fmaxf(umin - 0.5f, 0.0f)), fc1 = floorf(fminf(umax - 0.5f, (float)(cam.W - 1)));
-  const float fr0 = ceilf(fmaxf(vmin - 0.5f, 0.0f)), fr1 = floorf(fminf(vmax - 0.5f, (float)(cam.H - 1)));
-  if (!(fc0 <= fc1) || !(fr0 <= fr1)) return;
-  const float inv_area = 1.0f / area;
-  const float e0x = p2.x - p1.x, e0y = p2.y - p1.y;
-  const float e1x = p0.x - p2.x, e1y = p0.y - p2.y;
-  const float e2x = p1.x - p0.x, e2y = p1.y - p0.y;
-  for (int r = (int)fr0; r <= (int)fr1; ++r) {
-    const float py = (float)r + 0.5f;
-    for (int c = (int)fc0; c <= (int)fc1; ++c) {
-      const float px = (float)c + 0.5f;
-      const float w0 = e0x * (py - p1.y) - e0y * (px - p1.x);
-      const float w1 = e1x * (py - p2.y) - e1y * (px - p2.x);
-      const float w2 = e2x * (py - p0.y) - e2y * (px - p0.x);
-      if (w0 > 0.0f || w1 > 0.0f || w2 > 0.0f) continue;
-      const float invz = (w0 * p0.w + w1 * p1.w + w2 * p2.w) * inv_area;
-      const float z = __builtin_amdgcn_rcpf(invz);
-      if (!(z > 0.0f)) continue;
-      atomicMin(&keys[(size_t)r * cam.W + c], pack_key(z, id_base + (uint32_t)i));
-    }
-  }
-}
-
-hipError_t launch_raster_global_dev(const MeshDev& m, const Cam& cam, const float* pose16_dev, uint32_t id_base,
-                                    unsigned long long* keys, hipStream_t st) {
-  hipLaunchKernelGGL(k_raster_global_dev, dim3((m.T + 255) / 256), dim3(256), 0, st, m, cam, pose16_dev, id_base,
-                     keys);
+  hipLaunchKernelGGL(k_argmax_pose, dim3(1), dim3(kArgmaxBlock), 0, st, logL, poses, N, out);
   return hipGetLastError();
 }
 

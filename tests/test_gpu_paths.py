@@ -127,3 +127,52 @@ def test_batch_of_large_and_small_images_equals_per_scene_calls(b3d, grad):
         np.testing.assert_array_equal(logL[i].cpu().numpy(), one[0])
         if grad:
             np.testing.assert_array_equal(g[i].cpu().numpy(), one[1])
+
+
+# rows and columns either side of a wave, a block and a 16-row run of the
+# tables' sums; nine static objects are two launches; triangles of a few pixels
+# and of the whole image.  The pose is behind the camera, so a result is the
+# background's sum over the whole image: logL and its derivatives within 1e-6
+# of the L1 mass of the oracle's terms (single precision rounds a sum by 6e-8).
+# The static objects' render decides pixel centres on an edge in single
+# precision, so with them logL may differ by two such pixels' windows
+@pytest.mark.parametrize("H,W", [(1, 63), (15, 64), (16, 65), (31, 255), (17, 256), (33, 257)])
+@pytest.mark.parametrize("statics", [0, 9])
+def test_background_sums_match_oracle(b3d, H, W, statics):
+    rng = np.random.default_rng(H * W + statics)
+    f = 0.9 * max(H, W)
+    cam = Camera(f, f, W / 2 + 0.37, H / 2 - 0.21, H, W)
+    K = b3d.intrinsics_of(cam)
+    quad = f32([[-2, -2, 0], [2, -2, 0], [2, 2, 0], [-2, 2, 0]]), np.array([[0, 2, 1], [0, 3, 2]], np.int32)
+    meshes = [quad] + [voxel_mesh(voxel_blob(12, rng, radius=0.04)) for _ in range(8)]
+    meshes = [(f32(v), t) for v, t in meshes][:statics]
+    poses = f32(random_poses(rng, 9, 0.8, 0.1))
+    poses[0] = np.eye(4)
+    poses[0, 2, 3] = 1.2
+    mesh = voxel_mesh(voxel_blob(5, rng, radius=0.03))
+    rays = oracle.unproject(np.ones((1, H, W)), cam)[0]
+    if statics:
+        d, _ = oracle.render([(v, t, p[None]) for (v, t), p in zip(meshes, poses)], cam)
+        z = np.where(d[0] > 0, d[0] + rng.normal(0, 0.002, (H, W)), 0.0)
+    else:
+        d = np.zeros((1, H, W))
+        z = rng.uniform(0.5, 1.0, (H, W))
+    z[rng.random((H, W)) < 0.1] = 0.0
+    obs = f32(z[..., None] * rays)
+    scene = b3d.Scene(b3d.Mesh(f32(mesh[0]), mesh[1]), K, b3d.score_params(0.004, 0.05, 1.0, 3))
+    if statics:
+        scene.set_background([b3d.Mesh(*m) for m in meshes], poses[:statics])
+    scene.set_observed(dev(obs))
+    P = np.eye(4)[None].copy()
+    P[0, 2, 3] = -1.0
+    L, g = scored(b3d, scene, dev(P), True)
+    sg, po = float(np.float32(0.004)), float(np.float32(0.05))
+    pts = oracle.unproject(d, cam)
+    L64, l1 = oracle.score(obs, pts, sg, po, 1.0, 3)
+    _, ds, dp = oracle.score_grad(obs, pts, sg, po, 1.0, 3)
+    slack = 0.0 if not statics else 9 * 12.0 * 2
+    assert abs(L[0] - L64[0]) <= 1e-6 * l1[0] + slack, (L[0], L64[0])
+    if not statics:
+        assert abs(g[0, 6] - ds[0]) <= 1e-6 * abs(ds[0]) + 1e-4
+        assert abs(g[0, 7] - dp[0]) <= 1e-6 * abs(dp[0]) + 1e-4
+    assert np.all(g[0, :6] == 0.0)
