@@ -39,6 +39,9 @@ static size_t fused_lds_bytes(const SceneDev& s, int bs, int zcap) {
 }
 size_t fused_lds_bytes(const SceneDev& s) { return fused_lds_bytes(s, kBlock, s.zcap); }
 
+// LDS of block_total over nv values (below), which reuses all of the block's.
+static size_t total_lds_bytes(int nv, int bs) { return sizeof(double) * (size_t)nv * (bs / 4); }
+
 // Two rows of the widest depth buffer (image width plus 2h each side).
 int min_zcap(const SceneDev& s) { return (4 * s.sc.h + 2) * (s.cam.W + 4 * s.sc.h); }
 
@@ -50,9 +53,11 @@ __host__ __device__ __forceinline__ int weight_bytes(int bs, int W, int h) {
   return 4 * (2 * h + 1) * W + 2 * kWaveQueue * (bs / 64);
 }
 static size_t launch_lds_bytes(const SceneDev& s, int bs, int zcap, bool grad) {
-  if (grad && bs > kBlock) return fused_lds_bytes(s, bs, zcap) + 4 * (size_t)zcap;
-  const int over = grad ? weight_bytes(bs, s.cam.W, s.sc.h) - (int)raster_lds_bytes(bs) : 0;
-  return fused_lds_bytes(s, bs, zcap) + (over > 0 ? 2 * kWaveQueue * (bs / 64) : 0);
+  size_t bytes = fused_lds_bytes(s, bs, zcap);
+  if (grad && bs > kBlock) bytes += 4 * (size_t)zcap;
+  if (grad && bs == kBlock && weight_bytes(bs, s.cam.W, s.sc.h) > (int)raster_lds_bytes(bs))
+    bytes += 2 * kWaveQueue * (bs / 64);
+  return std::max(bytes, total_lds_bytes(grad ? 9 : 1, bs));
 }
 
 // Sums over the block of NV doubles per thread, in a fixed order: quads of
@@ -221,11 +226,6 @@ __device__ __forceinline__ float window_grad(const float* __restrict__ wbuf, int
     }
   }
   return g;
-}
-
-// First local index k >= 0 with (base + k) mod kBlock == t.
-__device__ __forceinline__ int first_of(unsigned t, int base) {
-  return ((int)t - base % kBlock + kBlock) % kBlock;
 }
 
 // The depth buffer of one band: the LDS rectangle L (pitch L.w(), rows and
@@ -739,27 +739,33 @@ __device__ __forceinline__ void window_sums_grid(const unsigned long long* __res
 }
 
 // logL of one hypothesis under every point of the noise grid (grid_out[k],
-// k = a * B + b) and their weighted log-sum-exp (*marg_out).  The same
-// render and windows as render_score_one; each observed pixel's window
+// k = a * B + b, unless null) and their weighted log-sum-exp (*marg_out).  The
+// same render and windows as render_score_one; each observed pixel's window
 // distances are computed once and exponentiated per deviation.  With
 // row0 >= 0 the block instead scores the full-width image rows [row0, row1)
 // (their pixels only, no background table) and grid_out[k] receives the
-// block's sum for grid point k; marg_out is not written.  Whole block.
+// block's sum for grid point k; marg_out is not written.  DEFER as for
+// render_score_one, the mark in *marg_out.  Whole block of BS threads.
+// What bounds it is VALU issue, most of it the windows' exponentials (A per
+// pair): so observed pixels without a point are compacted away, and the grid
+// points of a deviation are unrolled over registers for up to four deviations
+// (NB of them each; more deviations go through LDS, blocks of kBlock only).
+// 5,000 hypotheses of 2,000 voxels at 160x120, 4 x 4 points: 491 us against 697
+// with one lane per observed pixel and the sums indexed through LDS.
+template <int RM, int BS, bool DEFER>
 __device__ __forceinline__ void render_score_grid_one(const SceneDev& s, const NoiseGridDev& g,
                                                       const float* __restrict__ pose16, float* __restrict__ grid_out,
                                                       float* __restrict__ marg_out, unsigned char* smem, int row0,
                                                       int row1) {
-  unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kRasterLdsBytes);
-  float* red = reinterpret_cast<float*>(zbuf + s.zcap);
-  float* sbuf = reinterpret_cast<float*>(smem);  // per thread: S[a] normM[a] (raster scratch, free by then)
+  constexpr int kScratch = (int)raster_lds_bytes(BS), NW = BS / 64;
+  unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kScratch);
+  float* sbuf = reinterpret_cast<float*>(smem);  // NA = 0, per thread: S[a] normM[a] (raster scratch, free by then)
+  unsigned short* queue = reinterpret_cast<unsigned short*>(smem + kScratch) - kWaveQueue * (NW - ((int)threadIdx.x >> 6));
   const Cam& cam = s.cam;
   const int H = cam.H, W = cam.W, h = s.sc.h;
-  float* dxt = red + 64 + 2 * h;
+  float* dxt = reinterpret_cast<float*>(zbuf + s.zcap) + 64 + 2 * h;
   float* dyt = dxt + W + 4 * h;
   const Pose P = load_pose(pose16);
-  for (int i = (int)threadIdx.x - 2 * h; i < W + 2 * h; i += kBlock) dxt[i] = ray_x(cam, i);
-  for (int i = (int)threadIdx.x - 2 * h; i < H + 2 * h; i += kBlock) dyt[i] = ray_y(cam, i);
-  if (threadIdx.x == kBlock - 1) *reinterpret_cast<PlaneView*>(zbuf + s.zcap) = plane_view(P, cam);
   const bool rows = row0 >= 0;
   Rect all;
   all.x0 = 0;
@@ -773,12 +779,19 @@ __device__ __forceinline__ void render_score_grid_one(const SceneDev& s, const N
   } else {
     obj = object_rect(s.mesh, P, cam);
   }
+  if (DEFER && (obj.w() + 4 * h) * (obj.h() + 4 * h) > s.zcap) {
+    if (threadIdx.x == 0) *marg_out = __uint_as_float(kDeferred);
+    return;
+  }
+  for (int i = (int)threadIdx.x - 2 * h; i < W + 2 * h; i += BS) dxt[i] = ray_x(cam, i);
+  for (int i = (int)threadIdx.x - 2 * h; i < H + 2 * h; i += BS) dyt[i] = ray_y(cam, i);
+  if (threadIdx.x == BS - 1) *reinterpret_cast<PlaneView*>(zbuf + s.zcap) = plane_view(P, cam);
   Rect region = rows ? obj : grow_clip(obj, h, W, H);
   if (obj.empty()) region.x1 = region.x0;
   const int nk_grid = g.A * g.B;
-  float acc[kMaxNoise];
-#pragma unroll
-  for (int k = 0; k < kMaxNoise; ++k) acc[k] = 0.0f;
+  // the sum of grid point (a, b) in slot a NB + b (NA > 0) or a B + b
+  double acc[kMaxNoise] = {};
+  int NBs = g.B;
   if (!obj.empty()) {
     const Rect lds = grow(obj, 2 * h);
     const int lw = lds.w(), rw = region.w();
@@ -788,39 +801,57 @@ __device__ __forceinline__ void render_score_grid_one(const SceneDev& s, const N
       Rect L = lds;
       L.y0 = a - 2 * h;
       L.y1 = b + 2 * h;
-      raster_band<false, kRasterAny, kBlock>(s, P, L, zbuf, smem, nullptr);
-      const int nw = (b - a) * rw;
-      // observed pixel g of the region always goes to thread g mod kBlock;
-      // na: the grid's number of deviations as a compile-time constant (0: any)
+      raster_band<false, RM, BS>(s, P, L, zbuf, smem, nullptr);
       const float inv_rw = 1.0f / (float)rw;
+      // na: the grid's number of deviations as a compile-time constant (0: any)
       auto pixels = [&](auto na) {
-        constexpr int NA = decltype(na)::value;
-        for (int k = first_of(threadIdx.x, (a - region.y0) * rw); k < nw; k += kBlock) {
-          int r, c;
-          row_col(k, rw, inv_rw, r, c);
-          r += a;
-          c += region.x0;
-          const float* q = s.obs + 3 * ((size_t)r * W + c);
-          const float ox = q[0], oy = q[1], oz = q[2];
-          if (!(oz > 0.0f)) continue;
-          float S[kMaxSigma];
-          switch (h) {
-            case 1:
-              window_sums_grid<1, NA>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, g, S);
-              break;
-            case 2:
-              window_sums_grid<2, NA>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, g, S);
-              break;
-            default:
-              window_sums_grid<0, NA>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, g, S);
-          }
+        constexpr int NA = decltype(na)::value, NB = NA > 0 ? kMaxNoise / (NA > 0 ? NA : 1) : 1;
+        if (NA > 0) NBs = NB;
+        wave_compacted<NW>(
+            (b - a) * rw, queue,
+            [&](int k) {
+              int r, c;
+              row_col(k, rw, inv_rw, r, c);
+              return s.obs[3 * ((size_t)(a + r) * W + (region.x0 + c)) + 2] > 0.0f;
+            },
+            [&](int k, bool act) {
+              if (!act) return;
+              int r, c;
+              row_col(k, rw, inv_rw, r, c);
+              r += a;
+              c += region.x0;
+              const float* q = s.obs + 3 * ((size_t)r * W + c);
+              const float ox = q[0], oy = q[1], oz = q[2];
+              float S[kMaxSigma];
+              switch (h) {
+                case 1:
+                  window_sums_grid<1, NA>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, g, S);
+                  break;
+                case 2:
+                  window_sums_grid<2, NA>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, g, S);
+                  break;
+                default:
+                  window_sums_grid<0, NA>(zbuf, L, lw, dxt, dyt, r, c, h, ox, oy, oz, g, S);
+              }
+              if constexpr (NA > 0) {
 #pragma unroll
-          for (int ai = 0; ai < (NA > 0 ? NA : kMaxSigma); ++ai)
-            if (NA > 0 || ai < g.A) sbuf[ai * kBlock + threadIdx.x] = S[ai] * g.normM[ai];
+                for (int ai = 0; ai < NA; ++ai) {
+                  const float Sn = S[ai] * g.normM[ai];
 #pragma unroll
-          for (int kk = 0; kk < kMaxNoise; ++kk)
-            if (kk < nk_grid) acc[kk] += f_ln(g.pa[kk] + g.pomp[kk] * sbuf[g.ka[kk] * kBlock + threadIdx.x]);
-        }
+                  for (int bi = 0; bi < NB; ++bi)
+                    if (bi < g.B)
+                      acc[ai * NB + bi] += (double)f_ln(g.pa[ai * g.B + bi] + g.pomp[ai * g.B + bi] * Sn);
+                }
+              } else {
+#pragma unroll
+                for (int ai = 0; ai < kMaxSigma; ++ai)
+                  if (ai < g.A) sbuf[ai * BS + threadIdx.x] = S[ai] * g.normM[ai];
+#pragma unroll
+                for (int kk = 0; kk < kMaxNoise; ++kk)
+                  if (kk < nk_grid)
+                    acc[kk] += (double)f_ln(g.pa[kk] + g.pomp[kk] * sbuf[g.ka[kk] * BS + threadIdx.x]);
+              }
+            });
       };
       switch (g.A) {
         case 1:
@@ -836,46 +867,78 @@ __device__ __forceinline__ void render_score_grid_one(const SceneDev& s, const N
           pixels(std::integral_constant<int, 4>{});
           break;
         default:
-          pixels(std::integral_constant<int, 0>{});
+          if constexpr (BS == kBlock) pixels(std::integral_constant<int, 0>{});
       }
       __syncthreads();
     }
   }
-  block_sum<kMaxNoise>(acc, red);
-  if (threadIdx.x == 0) {
-    if (rows) {
-      for (int k = 0; k < nk_grid; ++k) grid_out[k] = acc[k];
-      return;
-    }
-    double v[kMaxNoise], m = -1e300;
-    for (int k = 0; k < nk_grid; ++k) {
-      const double* sat = g.sat + g.sat_stride * k;
-      v[k] = (double)acc[k] + rect_sum(sat, W, all) - rect_sum(sat, W, region);
-      grid_out[k] = (float)v[k];
-      m = fmax(m, v[k] + (double)g.logw[k]);
-    }
-    double t = 0.0;
-    for (int k = 0; k < nk_grid; ++k) t += exp(v[k] + (double)g.logw[k] - m);
-    *marg_out = (float)(m + log(t));
+  // thread 16 slot holds a grid point's sum: k and, when it is one, the
+  // background outside the region
+  const int slot = threadIdx.x >> 4, ka = slot / NBs, kb = slot - ka * NBs;
+  const int k = ka * g.B + kb;
+  const bool writer = threadIdx.x < 16 * kMaxNoise && (threadIdx.x & 15) == 0 && ka < g.A && kb < g.B;
+  double outside = 0.0;
+  if (writer && !rows) {
+    const double* sat = g.sat + g.sat_stride * k;
+    outside = rect_sum(sat, W, all) - rect_sum(sat, W, region);
+  }
+  double* red = reinterpret_cast<double*>(smem);
+  const double v = block_total<kMaxNoise, BS>(acc, red) + outside;
+  if (writer && grid_out) grid_out[k] = (float)v;
+  if (rows) return;
+  double* lse = red + kMaxNoise * (BS / 4);
+  if (writer) lse[k] = v + (double)g.logw[k];
+  __syncthreads();
+  if (threadIdx.x < 64) {  // lanes 0 .. 15 hold the grid points
+    const bool has = (int)threadIdx.x < nk_grid;
+    const double x = has ? lse[threadIdx.x] : -1e300;
+    double m = x;
+    for (int o = 8; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    double e = has ? exp(x - m) : 0.0;
+    for (int o = 8; o >= 1; o >>= 1) e += __shfl_xor(e, o, 64);
+    if (threadIdx.x == 0) *marg_out = (float)(m + log(e));
   }
 }
 
-__global__ __launch_bounds__(kBlock, 4) void k_render_score_grid(SceneDev s, NoiseGridDev g,
-                                                                 const float* __restrict__ poses, int N,
-                                                                 float* __restrict__ logL_grid,
-                                                                 float* __restrict__ logL_marg) {
+template <int RM, int BS, int PART>
+__global__ __launch_bounds__(BS, 4) void k_render_score_grid(SceneDev s, NoiseGridDev g,
+                                                             const float* __restrict__ poses, int N,
+                                                             float* __restrict__ logL_grid, float* logL_marg) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = blockIdx.x;
   if (n >= N) return;
-  float dummy[kMaxNoise];
-  float* gout = logL_grid ? logL_grid + (size_t)g.A * g.B * n : dummy;
-  render_score_grid_one(s, g, poses + 16 * (size_t)n, gout, logL_marg + n, smem, -1, -1);
+  if (PART == kRest && __float_as_uint(logL_marg[n]) != kDeferred) return;
+  float* gout = logL_grid ? logL_grid + (size_t)g.A * g.B * n : nullptr;
+  render_score_grid_one<RM, BS, PART == kFirst>(s, g, poses + 16 * (size_t)n, gout, logL_marg + n, smem, -1, -1);
 }
 
+template <int BS, int PART = kAlone>
+static void launch_grid_bs(const SceneDev& s, const NoiseGridDev& g, const float* poses, int N, float* logL_grid,
+                           float* logL_marg, hipStream_t st) {
+  hipLaunchKernelGGL((s.mesh.has_big ? k_render_score_grid<kRasterBig, BS, PART>
+                                     : k_render_score_grid<kRasterSmall, BS, PART>),
+                     dim3(N), dim3(BS),
+                     std::max(fused_lds_bytes(s, BS, s.zcap), total_lds_bytes(kMaxNoise, BS) + kMaxNoise * sizeof(double)),
+                     st, s, g, poses, N, logL_grid, logL_marg);
+}
+
+// Block sizes as for launch_render_score; more than four deviations need the
+// 256-thread block.
 hipError_t launch_render_score_grid(const SceneDev& s, const NoiseGridDev& g, const float* poses, int N,
                                     float* logL_grid, float* logL_marg, hipStream_t st) {
-  hipLaunchKernelGGL(k_render_score_grid, dim3(N), dim3(kBlock), fused_lds_bytes(s), st, s, g, poses, N, logL_grid,
-                     logL_marg);
+  SceneDev t;
+  if (g.A > 4) {
+    launch_grid_bs<kBlock>(s, g, poses, N, logL_grid, logL_marg, st);
+  } else if (N <= kCUs && roomy_scene(s, 1024, false, &t)) {
+    launch_grid_bs<1024>(t, g, poses, N, logL_grid, logL_marg, st);
+  } else if (N <= 2 * kCUs && roomy_scene(s, 512, false, &t)) {
+    launch_grid_bs<512>(t, g, poses, N, logL_grid, logL_marg, st);
+  } else if (defers(s, N) && roomy_scene(s, 512, false, &t)) {
+    launch_grid_bs<kBlock, kFirst>(s, g, poses, N, logL_grid, logL_marg, st);
+    launch_grid_bs<512, kRest>(t, g, poses, N, logL_grid, logL_marg, st);
+  } else {
+    launch_grid_bs<kBlock>(s, g, poses, N, logL_grid, logL_marg, st);
+  }
   return hipGetLastError();
 }
 
@@ -914,9 +977,9 @@ __global__ __launch_bounds__(kBlock) void k_score_rows_grid(RowsGroupDev G, int 
   }
   if (G.noise[j]) {
     const NoiseGridDev g = grid_point(G.noise[j][0], G.noise[j][1], G.inv_V, G.M_norm);
-    render_score_grid_one(s, g, G.pose[j], out, nullptr, smem, row0, row1);
+    render_score_grid_one<kRasterAny, kBlock, false>(s, g, G.pose[j], out, nullptr, smem, row0, row1);
   } else {
-    render_score_grid_one(s, G.grid, G.pose[j], out, nullptr, smem, row0, row1);
+    render_score_grid_one<kRasterAny, kBlock, false>(s, G.grid, G.pose[j], out, nullptr, smem, row0, row1);
   }
 }
 
@@ -942,8 +1005,8 @@ __global__ void k_reduce_rows_grid(const float* __restrict__ partial, int P, int
 }
 
 hipError_t launch_score_rows_grid(const RowsGroupDev& G, int R, int n_bands, float* partial, hipStream_t st) {
-  hipLaunchKernelGGL(k_score_rows_grid, dim3(n_bands, G.S), dim3(kBlock), fused_lds_bytes(G.s[0]), st, G, R, n_bands,
-                     partial);
+  hipLaunchKernelGGL(k_score_rows_grid, dim3(n_bands, G.S), dim3(kBlock),
+                     std::max(fused_lds_bytes(G.s[0]), total_lds_bytes(kMaxNoise, kBlock)), st, G, R, n_bands, partial);
   return hipGetLastError();
 }
 

@@ -176,3 +176,62 @@ def test_background_sums_match_oracle(b3d, H, W, statics):
         assert abs(g[0, 6] - ds[0]) <= 1e-6 * abs(ds[0]) + 1e-4
         assert abs(g[0, 7] - dp[0]) <= 1e-6 * abs(dp[0]) + 1e-4
     assert np.all(g[0, :6] == 0.0)
+
+
+# the noise grid's registers hold 16 // A grid points per deviation up to four
+# deviations (LDS beyond); block sizes and the second launch as for the score
+@pytest.mark.parametrize("A,B", [(1, 16), (2, 8), (3, 5), (4, 4), (4, 1), (5, 3), (8, 2)])
+@pytest.mark.parametrize("H,W", [(48, 64), (151, 200)])
+def test_noise_grid_block_sizes_give_the_same_and_match_single_points(b3d, H, W, A, B):
+    rng = np.random.default_rng(A * 31 + B)
+    verts, tris = voxel_mesh(voxel_blob(200, rng))
+    cam = Camera(0.94 * W, 0.94 * W, W / 2 + 0.2, H / 2 - 0.3, H, W)
+    K = b3d.intrinsics_of(cam)
+    P = f32(random_poses(rng, 520, 0.8, 0.03))
+    P[::7, 2, 3] = 2.5
+    P = dev(P)
+    scene = b3d.Scene(b3d.Mesh(f32(verts), tris), K, b3d.score_params(0.004, 0.05, 1.0, 5))
+    xyz, _ = b3d.render_batch(scene.mesh, P[1:2].contiguous(), K)
+    obs = xyz[0].clone()
+    obs[::3, ::2] = 0.0
+    scene.set_observed(obs.contiguous())
+    sig, po = b3d.noise_grid_midpoints(0.012, A, B)
+    scene.set_noise_grid(sig, po)
+    marg, grid = b3d.render_score_marginal(scene, P, grid=True)
+    for n in (1, 256, 300, 512):
+        m, g = b3d.render_score_marginal(scene, P[:n].contiguous(), grid=True)
+        assert torch.equal(m, marg[:n]) and torch.equal(g, grid[:n])
+    assert torch.equal(b3d.render_score_marginal(scene, P), marg)
+    # each grid point is the plain score at its parameters; the two kernels' terms
+    # ln(a + b S) differ by single-precision roundings of each pixel's term: 1e-5 of logL's size
+    for a, b in ((0, 0), (A - 1, B - 1)):
+        scene.set_params(b3d.score_params(float(sig[a]), float(po[b]), 1.0, 5))
+        one = b3d.render_score(scene, P)
+        assert (one - grid[:, a, b]).abs().max() <= 1e-5 * one.abs().max()
+    ref = torch.logsumexp(grid.double().flatten(1), 1) - np.log(A * B)
+    assert (marg - ref).abs().max() <= 1e-6 * ref.abs().max() + 1e-3
+
+
+# the smallest images and tiles: the block's sums need more LDS than its tile
+@pytest.mark.parametrize("H,W,window", [(1, 1, 1), (2, 3, 3), (5, 4, 1)])
+@pytest.mark.parametrize("N", [1, 300, 600])
+def test_smallest_images_match_oracle(b3d, H, W, window, N):
+    rng = np.random.default_rng(N)
+    verts, tris = voxel_mesh(voxel_blob(20, rng, radius=0.04))
+    verts = f32(verts)
+    cam = Camera(4.0, 4.0, W / 2 + 0.03, H / 2 - 0.04, H, W)
+    P = f32(random_poses(rng, N, 0.2, 0.01))
+    d, ids = oracle.render([(verts, tris, P)], cam)
+    obs = f32(oracle.unproject(np.where(d[:1] > 0, d[:1], 0.2), cam)[0])
+    scene = b3d.Scene(b3d.Mesh(verts, tris), b3d.intrinsics_of(cam), b3d.score_params(0.02, 0.1, 1.0, window))
+    scene.set_observed(dev(obs))
+    L, g = scored(b3d, scene, dev(P), True)
+    L64, l1 = oracle.score(obs, oracle.unproject(d, cam), float(np.float32(0.02)), float(np.float32(0.1)), 1.0, window)
+    assert np.all(np.abs(L - L64) <= 1e-4 * l1)
+    assert np.array_equal(scored(b3d, scene, dev(P), False)[0], L)
+    scene.set_noise_grid(*b3d.noise_grid_midpoints(0.03, 4, 4))
+    marg, grid = b3d.render_score_marginal(scene, dev(P), grid=True)
+    ref = torch.logsumexp(grid.double().flatten(1), 1) - np.log(16)
+    assert (marg - ref).abs().max() <= 1e-5 * ref.abs().max() + 1e-5
+    scene.set_tile(scene.tile_limits()[0])
+    assert np.array_equal(scored(b3d, scene, dev(P), True)[1], g)
