@@ -429,9 +429,8 @@ b3d_status b3d_score_backward(const float* observed, const float* rendered, int3
   if (!d_rendered && !d_sigma && !d_pout) return B3D_OK;
   if (workspace && ws_bytes < score_workspace_bytes(H, W))
     return fail(B3D_ESHAPE, "score_backward: workspace of %zu bytes < %zu", ws_bytes, score_workspace_bytes(H, W));
-  const int R = score_backward_ring_rows(H, W, sc.h);
-  if (workspace && R > 0 && aligned16(rendered) && aligned16(d_rendered) && aligned16(workspace)) {
-    B3D_CHECK_HIP(launch_score_backward_ring(observed, rendered, N, H, W, sc, R, workspace, dlogL, d_rendered, d_sigma,
+  if (workspace && score_backward_crop_fits(W, sc.h) && aligned16(workspace)) {
+    B3D_CHECK_HIP(launch_score_backward_crop(observed, rendered, N, H, W, sc, workspace, dlogL, d_rendered, d_sigma,
                                              d_pout, (hipStream_t)stream),
                   "score_backward");
     return B3D_OK;

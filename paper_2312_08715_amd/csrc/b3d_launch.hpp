@@ -200,12 +200,12 @@ hipError_t launch_render_backward(const MeshDev& m, const Cam& cam, const float*
 // half-width h, 0 when the ring does not apply (W not a multiple of 4, or
 // the rows do not fit).
 int score_ring_rows(int H, int W, int h);
-int score_backward_ring_rows(int H, int W, int h);
 size_t score_workspace_bytes(int H, int W);
 hipError_t launch_score_ring(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc, int R,
                              void* workspace, float* logL, hipStream_t st);
-hipError_t launch_score_backward_ring(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc,
-                                      int R, void* workspace, const float* dlogL, float* d_rend, float* d_sigma,
+bool score_backward_crop_fits(int W, int h);
+hipError_t launch_score_backward_crop(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc,
+                                      void* workspace, const float* dlogL, float* d_rend, float* d_sigma,
                                       float* d_pout, hipStream_t st);
 hipError_t launch_score(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc, float* logL,
                         int cap, hipStream_t st);

@@ -235,3 +235,62 @@ def test_smallest_images_match_oracle(b3d, H, W, window, N):
     assert (marg - ref).abs().max() <= 1e-5 * ref.abs().max() + 1e-5
     scene.set_tile(scene.tile_limits()[0])
     assert np.array_equal(scored(b3d, scene, dev(P), True)[1], g)
+
+
+# the adjoint over the rectangle of drawn pixels: word and single-float images
+# (a width of 4 k or not), an empty image, one pixel, a rectangle in one band
+# and in several, every compiled window and the general one
+@pytest.mark.parametrize("window", [1, 3, 5, 7, 9])
+@pytest.mark.parametrize("H,W", [(24, 32), (37, 41), (60, 200)])
+def test_score_adjoint_over_the_drawn_rectangle_matches_oracle(b3d, H, W, window):
+    rng = np.random.default_rng(H + window)
+    cam = Camera(0.9 * W, 0.9 * W, W / 2, H / 2, H, W)
+    rays = oracle.unproject(np.ones((1, H, W)), cam)[0]
+    z = np.zeros((5, H, W))
+    z[1, H // 2, W - 1] = 0.8  # one pixel, in the last column
+    z[2, 3:15, 5:19] = 0.8 + rng.normal(0, 0.003, (12, 14))
+    z[3] = 0.8 + rng.normal(0, 0.003, (H, W))  # the whole image
+    z[4, 0, 0] = z[4, H - 1, W - 1] = 0.8  # two corners: a rectangle of empty pixels
+    z[3, ::3, ::4] = 0.0
+    rend = f32(z[..., None] * rays)
+    zo = np.where(rng.random((H, W)) < 0.2, 0.0, 0.8 + rng.normal(0, 0.003, (H, W)))
+    obs = f32(zo[..., None] * rays)
+    dl = f32(rng.uniform(-1.0, 2.0, 5))
+    sg, po = float(np.float32(0.005)), float(np.float32(0.1))
+    dr, ds, dp = b3d.score_backward(dev(obs), dev(rend), b3d.score_params(sg, po, 1.0, window), dev(dl))
+    r64, s64, p64 = oracle.score_grad(obs, rend, sg, po, 1.0, window)
+    k = dl[:, None, None, None]
+    scale = np.abs(r64 * k).max()
+    assert np.abs(dr.cpu().numpy() - r64 * k).max() <= 1e-5 * scale
+    for got, want in ((ds, s64 * dl), (dp, p64 * dl)):
+        assert np.all(np.abs(got.cpu().numpy() - want) <= 1e-5 * np.abs(want).max())
+    none = b3d.score_backward(dev(obs), dev(rend), b3d.score_params(sg, po, 1.0, window), dev(dl), want_rendered=False)
+    assert torch.equal(none[1], ds) and torch.equal(none[2], dp)
+    # odd starts of the images in memory take the single-float route: the same values
+    buf = torch.zeros(rend.size + 1, dtype=torch.float32, device="cuda")
+    buf[1:] = dev(rend).reshape(-1)
+    odd = b3d.score_backward(dev(obs), buf[1:].view(rend.shape), b3d.score_params(sg, po, 1.0, window), dev(dl))
+    assert all(torch.equal(a, b) for a, b in zip(odd, (dr, ds, dp)))
+
+
+# ids read four at a time or one by one, ids of no triangle among them
+@pytest.mark.parametrize("H,W", [(16, 20), (17, 21), (64, 64)])
+def test_pose_adjoint_reads_ids_either_way(b3d, H, W):
+    rng = np.random.default_rng(W)
+    verts, tris = voxel_mesh(voxel_blob(40, rng, radius=0.04))
+    verts = f32(verts)
+    cam = Camera(1.5 * W, 1.5 * W, W / 2 + 0.1, H / 2, H, W)
+    P = f32(random_poses(rng, 7, 0.3, 0.01))
+    d, ids = oracle.render([(verts, tris, P)], cam)
+    g = f32(rng.normal(size=(7, H, W, 3)))
+    want = oracle.render_grad(verts, tris, P, cam, ids, d, g)
+    t = torch.as_tensor(ids.astype(np.int32), device="cuda")
+    t[t < 0] = torch.tensor(-7, dtype=torch.int32, device="cuda")
+    t[0, 0, 0] = len(tris) + 5 if ids[0, 0, 0] < 0 else t[0, 0, 0]
+    K = b3d.intrinsics_of(cam)
+    out = b3d.render_backward(b3d.Mesh(verts, tris), dev(P), K, t.contiguous(), dev(g)).cpu().numpy()
+    assert np.all(np.linalg.norm(out - want, axis=1) <= 1e-3 * np.linalg.norm(want, axis=1) + 1e-6)
+    buf = torch.zeros(t.numel() + 1, dtype=torch.int32, device="cuda")
+    buf[1:] = t.reshape(-1)
+    odd = b3d.render_backward(b3d.Mesh(verts, tris), dev(P), K, buf[1:].view(t.shape), dev(g)).cpu().numpy()
+    assert np.all(np.abs(odd - out) <= 1e-6 * np.abs(out).max())
