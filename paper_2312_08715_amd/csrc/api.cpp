@@ -371,11 +371,7 @@ b3d_status b3d_render_batch(const b3d_mesh* mesh, const float* poses, int32_t N,
   if (N < 0) return fail(B3D_ESHAPE, "render_batch: N < 0");
   if (N == 0) return B3D_OK;
   if (!poses || !xyz_out) return fail(B3D_EINVAL, "render_batch: NULL pointer");
-  // a depth buffer of 2048 keys (or one image row) leaves room for five workgroups per CU
-  const int zcap = std::max(2048, K->W);
-  if (kRasterLdsBytes + 8 * (size_t)zcap > kLdsMax)
-    return fail(B3D_ESHAPE, "render_batch: image too wide for the LDS depth buffer");
-  B3D_CHECK_HIP(launch_render_batch(mesh->dev, make_cam(K), poses, N, xyz_out, tri_out, zcap, (hipStream_t)stream),
+  B3D_CHECK_HIP(launch_render_batch(mesh->dev, make_cam(K), poses, N, xyz_out, tri_out, (hipStream_t)stream),
                 "render_batch");
   return B3D_OK;
 }

@@ -21,6 +21,14 @@ constexpr uint32_t kNoTri = 0xFFFFFFFFu;  // second id of a primitive that is a 
 // |x/z|, |y/z| <= 1e3 (checked when a scene is created).
 constexpr unsigned long long kEmptyKey = (0x58635FA9ull << 32) | 0xFFFFFFFFull;
 
+// A workgroup barrier that orders LDS only: global loads and stores stay in
+// flight across it, where __syncthreads would first wait for all of them.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Pinhole camera and image size.
 struct Cam {
   float fx, fy, cx, cy, znear;
@@ -333,6 +341,21 @@ __device__ __forceinline__ bool covered_exact(const MeshDev& m, const Pose& P, c
   return !(w0 > 0.0 || w1 > 0.0 || w2 > 0.0);
 }
 
+// How a launch takes part: alone; first, leaving the hypotheses beyond its
+// depth buffer; or second, scoring those that were left.
+enum Part { kAlone = 0, kFirst = 1, kRest = 2 };
+
+// What a deferred hypothesis leaves in its result for the second launch: a NaN
+// that no arithmetic makes (were an input's NaN to carry it here, the
+// hypothesis would be taken twice, with one result).
+constexpr uint32_t kDeferred = 0x7fcb3d5eu;
+
+// Images above which objects often exceed the 256-thread block's depth buffer,
+// and the 512-thread block's (an object takes about a tenth to a quarter of
+// its image); hypotheses above which a second launch costs at most a few per cent.
+constexpr int kBandedPixels = 24000, kWholeCuPixels = 56000;
+constexpr int kBandedCount = 2048;
+
 // LDS scratch of the rasteriser (free again once raster_mesh returns; the
 // fused kernel then reuses it for the window weights, which sets its size).
 struct RasterLds {
@@ -599,7 +622,7 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
 // atomicMin of the packed depth/id key); one that lies within a rounding
 // margin of an edge, or any centre of a triangle seen nearly edge-on, is
 // queued and decided afterwards by covered_exact (its depth from *view, the
-// pose's plane view in LDS).  Must be called by the whole block; ends after a barrier with the buffer complete.
+// pose's plane view in LDS).  Must be called by the whole block; its barriers order LDS alone; ends after a barrier with the buffer complete.
 template <bool COUNT, bool BIG, int BS>
 __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, const Cam& cam, uint32_t id_base,
                                             const Rect& band, const Rect& buf, unsigned long long* zbuf,
@@ -623,17 +646,17 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
     const int mine = base + threadIdx.x;
     const bool draw = mine < n_clusters && cluster_may_draw(m.clusters[mine], P, cam, band);
     const unsigned long long mask = __ballot(draw);
-    __syncthreads();  // the previous group's list is no longer read
+    lds_barrier();  // the previous group's list is no longer read
     if (lane == 0) lds.counts[1 + wave] = __popcll(mask);
     if (threadIdx.x == 0) lds.counts[1 + kW] = 0;
-    __syncthreads();
+    lds_barrier();
     int off = 0, total = 0;
     for (int w = 0; w < kW; ++w) {
       off += (w < wave) ? lds.counts[1 + w] : 0;
       total += lds.counts[1 + w];
     }
     if (draw) lds.list[off + __popcll(mask & ((1ull << lane) - 1ull))] = mine;
-    __syncthreads();
+    lds_barrier();
     for (;;) {
       int q = 0;
       if (lane == 0) q = atomicAdd(&lds.counts[1 + kW], 1);
@@ -772,7 +795,7 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
   // centres near an edge: the exact test, then the plane depth
   const int nq = min(lds.counts[0], lds.qcap);
   for (int k = threadIdx.x; k < nq; k += BS) {
@@ -792,7 +815,7 @@ __device__ __forceinline__ void raster_mesh(const MeshDev& m, const Pose& P, con
     atomicAdd(&cnt[kCntFrag], c_frag + c_alike[kCntFrag]);
     atomicAdd(&cnt[kCntExact], c_exact);
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // Which rasteriser a kernel holds: the plain one, the one with the wave walk

@@ -190,7 +190,7 @@ size_t fused_lds_bytes(const SceneDev& s);
 int min_zcap(const SceneDev& s);
 
 hipError_t launch_render_batch(const MeshDev& m, const Cam& cam, const float* poses, int N, float* xyz, int* tri,
-                               int zcap, hipStream_t st);
+                               hipStream_t st);
 hipError_t launch_unproject(const float* depth, int B, const Cam& cam, float* xyz, hipStream_t st);
 hipError_t launch_render_backward(const MeshDev& m, const Cam& cam, const float* poses, int N, const int* tri,
                                   const float* d_rend, float* d_pose, hipStream_t st);

@@ -273,11 +273,6 @@ __device__ __forceinline__ void raster_band(const SceneDev& s, const Pose& P, co
   __syncthreads();
 }
 
-// What a deferred hypothesis leaves in its logL for the second launch: a NaN
-// that no arithmetic makes (were an input's NaN to carry it here, the
-// hypothesis would be scored twice, with one result).
-constexpr uint32_t kDeferred = 0x7fcb3d5eu;
-
 // One hypothesis: pose16 (16 floats), writes *logL_out and, when GRAD,
 // grad_out[0..8).  DEFER: one whose depth buffer exceeds the block's writes
 // kDeferred instead, and nothing else.  Must be called by the whole block of BS threads; `smem` is
@@ -474,10 +469,6 @@ __device__ __forceinline__ void render_score_one(const SceneDev& s, const float*
 
 // RM: the rasteriser compiled in (the launcher picks it from the mesh, so
 // that meshes without large primitives run the plain one alone).
-// How a launch takes part: alone; first, leaving the hypotheses beyond its
-// depth buffer; or second, scoring those that were left.
-enum Part { kAlone = 0, kFirst = 1, kRest = 2 };
-
 template <bool GRAD, int RM, int BS, int PART>
 __global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float* __restrict__ poses, int N, float* logL,
                                                         float* __restrict__ grad) {
@@ -489,17 +480,11 @@ __global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float*
                                                         GRAD ? grad + 8 * (size_t)n : nullptr, smem);
 }
 
-// Images above which objects often exceed the 256-thread block's depth buffer,
-// and the 512-thread block's (an object takes about a tenth to a quarter of
-// its image); hypotheses above which a second launch costs at most a few per cent.
-constexpr long long kBandedPixels = 24000, kWholeCuPixels = 56000;
-constexpr int kBandedCount = 2048;
-
 static bool defers(const SceneDev& s, long long N) {
   const long long whole = (long long)(s.cam.W + 4 * s.sc.h) * (s.cam.H + 4 * s.sc.h);
-  return !s.fixed_tile && whole > s.zcap && ((long long)s.cam.W * s.cam.H > kBandedPixels || N >= kBandedCount);
+  return !s.fixed_tile && whole > s.zcap && (s.cam.W * s.cam.H > kBandedPixels || N >= kBandedCount);
 }
-static int rest_block(const SceneDev& s) { return (long long)s.cam.W * s.cam.H > kWholeCuPixels ? 1024 : 512; }
+static int rest_block(const SceneDev& s) { return s.cam.W * s.cam.H > kWholeCuPixels ? 1024 : 512; }
 
 // The scene with the depth buffer that a block of bs threads has room for: its
 // share of a CU's LDS, no more than the image needs.  The caller's own tile

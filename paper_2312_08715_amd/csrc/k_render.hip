@@ -6,104 +6,111 @@
 
 namespace b3d {
 
-// Write rows [y0, y1) of one hypothesis's outputs: pixels inside `band`
-// come from the LDS key buffer, others are empty.
-__device__ __forceinline__ void write_rows(const Cam& cam, int y0, int y1, const Rect& band,
-                                           const unsigned long long* zbuf, uint32_t id_base, float* __restrict__ xyz,
-                                           int* __restrict__ tri) {
-  const int W = cam.W;
-  const int nf = (y1 - y0) * W * 3;
-  float* xo = xyz + (size_t)y0 * W * 3;
-  for (int f = threadIdx.x; f < nf; f += kBlock) {
-    const int p = f / 3, comp = f - 3 * p;
-    const int r = y0 + p / W, c = p - (p / W) * W;
-    float v = 0.0f;
-    if (r >= band.y0 && r < band.y1 && c >= band.x0 && c < band.x1) {
-      const unsigned long long k = zbuf[(r - band.y0) * band.w() + (c - band.x0)];
-      if (k != kEmptyKey) {
-        const float z = key_depth(k);
-        v = comp == 0 ? z * ray_x(cam, c) : (comp == 1 ? z * ray_y(cam, r) : z);
-      }
+static size_t render_lds_bytes(int bs, int zcap) {
+  return raster_lds_bytes(bs) + sizeof(unsigned long long) * (size_t)zcap + kPlaneViewBytes;
+}
+
+// Rows [y0, y1) of an image written empty, as 16-byte words where the image is
+// made of them (VEC: rows of 4 k pixels in 16-byte aligned buffers).
+template <bool VEC, int BS>
+__device__ __forceinline__ void write_empty_rows(int W, int y0, int y1, float* __restrict__ xyz, int* __restrict__ tri) {
+  const size_t first = (size_t)y0 * W;
+  const int np = (y1 - y0) * W;
+  if constexpr (VEC) {
+    float4* x4 = reinterpret_cast<float4*>(xyz + 3 * first);
+    for (int k = threadIdx.x; k < 3 * (np / 4); k += BS) x4[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (tri) {
+      int4* t4 = reinterpret_cast<int4*>(tri + first);
+      for (int k = threadIdx.x; k < np / 4; k += BS) t4[k] = make_int4(-1, -1, -1, -1);
     }
-    xo[f] = v;
-  }
-  if (tri) {
-    int* to = tri + (size_t)y0 * W;
-    const int np = (y1 - y0) * W;
-    for (int p = threadIdx.x; p < np; p += kBlock) {
-      const int r = y0 + p / W, c = p - (p / W) * W;
-      int id = -1;
-      if (r >= band.y0 && r < band.y1 && c >= band.x0 && c < band.x1) {
-        const unsigned long long k = zbuf[(r - band.y0) * band.w() + (c - band.x0)];
-        if (k != kEmptyKey) id = (int)(key_id(k) - id_base);
-      }
-      to[p] = id;
+  } else {
+    float* x = xyz + 3 * first;
+    for (int k = threadIdx.x; k < 3 * np; k += BS) x[k] = 0.0f;
+    if (tri) {
+      int* t = tri + first;
+      for (int k = threadIdx.x; k < np; k += BS) t[k] = -1;
     }
   }
 }
 
-// write_rows for W a multiple of 4: each thread writes four pixels at a time
-// (three 16-byte words of points, one of ids), so every store is a whole
-// 16-byte word of a contiguous row span.
-__device__ __forceinline__ void write_rows4(const Cam& cam, int y0, int y1, const Rect& band,
-                                            const unsigned long long* zbuf, uint32_t id_base, float* __restrict__ xyz,
-                                            int* __restrict__ tri) {
-  const int W = cam.W, qpr = W / 4;  // pixel quads per row
-  const int nq = (y1 - y0) * qpr;
-  float4* xo = reinterpret_cast<float4*>(xyz + (size_t)y0 * W * 3);
-  int4* to = tri ? reinterpret_cast<int4*>(tri + (size_t)y0 * W) : nullptr;
-  const bool rows_in = y0 < band.y1 && y1 > band.y0 && !band.empty();
-  for (int q = threadIdx.x; q < nq; q += kBlock) {
-    const int dr = q / qpr;
-    const int r = y0 + dr, c0 = 4 * (q - dr * qpr);
-    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    int id[4] = {-1, -1, -1, -1};
-    if (rows_in && r >= band.y0 && r < band.y1 && c0 + 4 > band.x0 && c0 < band.x1) {
+// Rows of the band: pixels inside it come from the LDS key buffer, others are
+// empty.  Four pixels per lane (VEC), or one.
+template <bool VEC, int BS>
+__device__ __forceinline__ void write_band_rows(const Cam& cam, const Rect& band, const unsigned long long* zbuf,
+                                                float* __restrict__ xyz, int* __restrict__ tri) {
+  constexpr int V = VEC ? 4 : 1;
+  const int W = cam.W, per_row = W / V, n = band.h() * per_row, bw = band.w();
+  const float inv = 1.0f / (float)per_row;
+  for (int q = threadIdx.x; q < n; q += BS) {
+    int dr, qc;
+    row_col(q, per_row, inv, dr, qc);
+    const int r = band.y0 + dr, c0 = V * qc;
+    float x[V], y[V], z[V];
+    int id[V];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < V; ++u) {
+      x[u] = y[u] = z[u] = 0.0f;
+      id[u] = -1;
+    }
+    if (c0 + V > band.x0 && c0 < band.x1) {
+      const float ry = ray_y(cam, r);
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
         const int c = c0 + u;
-        if (c >= band.x0 && c < band.x1) {
-          const unsigned long long k = zbuf[(r - band.y0) * band.w() + (c - band.x0)];
-          if (k != kEmptyKey) {
-            z[u] = key_depth(k);
-            id[u] = (int)(key_id(k) - id_base);
-          }
-        }
+        if (c < band.x0 || c >= band.x1) continue;
+        const unsigned long long k = zbuf[dr * bw + (c - band.x0)];
+        if (k == kEmptyKey) continue;
+        z[u] = key_depth(k);
+        x[u] = z[u] * ray_x(cam, c);
+        y[u] = z[u] * ry;
+        id[u] = (int)key_id(k);
       }
     }
-    const float ry = ray_y(cam, r);
-    float x[4], y[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      x[u] = z[u] * ray_x(cam, c0 + u);
-      y[u] = z[u] * ry;
+    const size_t p = (size_t)r * W + c0;
+    if constexpr (VEC) {
+      float4* o = reinterpret_cast<float4*>(xyz + 3 * p);
+      o[0] = make_float4(x[0], y[0], z[0], x[1]);
+      o[1] = make_float4(y[1], z[1], x[2], y[2]);
+      o[2] = make_float4(z[2], x[3], y[3], z[3]);
+      if (tri) *reinterpret_cast<int4*>(tri + p) = make_int4(id[0], id[1], id[2], id[3]);
+    } else {
+      xyz[3 * p] = x[0];
+      xyz[3 * p + 1] = y[0];
+      xyz[3 * p + 2] = z[0];
+      if (tri) tri[p] = id[0];
     }
-    xo[3 * q + 0] = make_float4(x[0], y[0], z[0], x[1]);
-    xo[3 * q + 1] = make_float4(y[1], z[1], x[2], y[2]);
-    xo[3 * q + 2] = make_float4(z[2], x[3], y[3], z[3]);
-    if (to) to[q] = make_int4(id[0], id[1], id[2], id[3]);
   }
 }
 
-template <int RM>
-__global__ __launch_bounds__(kBlock, 4) void k_render_batch(MeshDev m, Cam cam, const float* __restrict__ poses, int N,
-                                                         float* __restrict__ xyz, int* __restrict__ tri, int zcap,
-                                                         int vec) {
+// One workgroup per hypothesis.  What bounds it is writing the images (16 bytes
+// a pixel) and, before its rows can be written, rasterising: the rows that the
+// object does not reach come last, so that their stores drain while the next
+// workgroup on the CU rasterises, and the barriers in between order LDS alone.
+// (Writing the whole image empty first and the drawn pixels after their depths
+// took 214 us for 2,000 images of 160x120: every workgroup of the first wave then
+// waits on the same stores.)
+// Block sizes and the second launch as for the fused kernel; a hypothesis left
+// to it is marked in its image's first word, which it rewrites.
+template <int RM, bool VEC, int BS, int PART>
+__global__ __launch_bounds__(BS, 4) void k_render_batch(MeshDev m, Cam cam, const float* __restrict__ poses, int N,
+                                                         float* __restrict__ xyz, int* __restrict__ tri, int zcap) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const RasterLds rl = carve_raster_lds<kBlock>(smem);
-  unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + kRasterLdsBytes);
+  const RasterLds rl = carve_raster_lds<BS>(smem);
+  unsigned long long* zbuf = reinterpret_cast<unsigned long long*>(smem + raster_lds_bytes(BS));
   const int n = blockIdx.x;
   if (n >= N) return;
   const Pose P = load_pose(poses + 16 * (size_t)n);
   const int H = cam.H, W = cam.W;
-#define WRITE_ROWS(...) (vec ? write_rows4(__VA_ARGS__) : write_rows(__VA_ARGS__))
   float* xn = xyz + (size_t)n * H * W * 3;
   int* tn = tri ? tri + (size_t)n * H * W : nullptr;
+  if (PART == kRest && __float_as_uint(xn[0]) != kDeferred) return;
   const Rect obj = object_rect(m, P, cam);
-  Rect none;
-  none.x0 = none.x1 = none.y0 = none.y1 = 0;
+  if (PART == kFirst && obj.w() * obj.h() > zcap) {
+    if (threadIdx.x == 0) xn[0] = __uint_as_float(kDeferred);
+    return;
+  }
   if (obj.empty()) {
-    WRITE_ROWS(cam, 0, H, none, zbuf, 0, xn, tn);
+    write_empty_rows<VEC, BS>(W, 0, H, xn, tn);
     return;
   }
   const int band_rows = max(zcap / obj.w(), 1);
@@ -115,11 +122,11 @@ __global__ __launch_bounds__(kBlock, 4) void k_render_batch(MeshDev m, Cam cam, 
     band.y0 = a;
     band.y1 = min(a + band_rows, obj.y1);
     const int nk = band.h() * band.w();
-    for (int k = threadIdx.x; k < nk; k += kBlock) zbuf[k] = kEmptyKey;
-    __syncthreads();
-    raster_mesh_mode<false, RM, kBlock>(m, P, cam, 0u, band, band, zbuf, rl, view);
+    for (int k = threadIdx.x; k < nk; k += BS) zbuf[k] = kEmptyKey;
+    lds_barrier();
+    raster_mesh_mode<false, RM, BS>(m, P, cam, 0u, band, band, zbuf, rl, view);
     // the drawn slots' depths on their triangles' planes
-    wave_compacted<kWaves>(
+    wave_compacted<(BS / 64)>(
         nk, reinterpret_cast<unsigned short*>(smem) + (threadIdx.x >> 6) * kWaveQueue,
         [&](int k) { return zbuf[k] != kEmptyKey; },
         [&](int k, bool act) {
@@ -129,29 +136,49 @@ __global__ __launch_bounds__(kBlock, 4) void k_render_batch(MeshDev m, Cam cam, 
           row_col(k, band.w(), inv_w, r, c);
           zbuf[k] = pack_key(plane_depth(m, *view, id, band.y0 + r, band.x0 + c), id);
         });
-    __syncthreads();
-    WRITE_ROWS(cam, band.y0, band.y1, band, zbuf, 0u, xn, tn);
-    __syncthreads();
+    lds_barrier();
+    write_band_rows<VEC, BS>(cam, band, zbuf, xn, tn);
+    lds_barrier();
   }
-  // the rows the object does not reach, last: their stores drain while the
-  // next workgroup on this CU rasterises (a barrier waits for every store
-  // issued before it)
-  WRITE_ROWS(cam, 0, obj.y0, none, zbuf, 0, xn, tn);
-  WRITE_ROWS(cam, obj.y1, H, none, zbuf, 0, xn, tn);
+  write_empty_rows<VEC, BS>(W, 0, obj.y0, xn, tn);
+  write_empty_rows<VEC, BS>(W, obj.y1, H, xn, tn);
 }
-#undef WRITE_ROWS
+
+template <int BS, int PART = kAlone>
+static void launch_render_bs(const MeshDev& m, const Cam& cam, const float* poses, int N, float* xyz, int* tri,
+                             int zcap, hipStream_t st) {
+  const size_t lds = render_lds_bytes(BS, zcap);
+  // whole 16-byte words: rows of 4 k pixels in 16-byte aligned buffers
+  const bool vec = cam.W % 4 == 0 && (((uintptr_t)xyz | (uintptr_t)tri) & 15) == 0;
+  auto k = m.has_big ? (vec ? k_render_batch<kRasterBig, true, BS, PART> : k_render_batch<kRasterBig, false, BS, PART>)
+                     : (vec ? k_render_batch<kRasterSmall, true, BS, PART>
+                            : k_render_batch<kRasterSmall, false, BS, PART>);
+  hipLaunchKernelGGL(k, dim3(N), dim3(BS), lds, st, m, cam, poses, N, xyz, tri, zcap);
+}
+
+// Depth keys for a block of bs threads: its share of a CU's LDS, no more than
+// the image needs (slots are listed as 16-bit indices).
+static int render_zcap(const Cam& cam, int bs) {
+  const int fit = (int)((kLdsPerCU / (1024 / bs) - render_lds_bytes(bs, 0)) / 8);
+  return min(fit, cam.W * cam.H);
+}
 
 hipError_t launch_render_batch(const MeshDev& m, const Cam& cam, const float* poses, int N, float* xyz, int* tri,
-                               int zcap, hipStream_t st) {
-  const size_t lds = kRasterLdsBytes + sizeof(unsigned long long) * (size_t)zcap + kPlaneViewBytes;
-  // quads of pixels as whole 16-byte words: rows of W % 4 == 0 pixels in 16-byte aligned buffers
-  const int vec = (cam.W % 4 == 0) && ((uintptr_t)xyz & 15) == 0 && ((uintptr_t)tri & 15) == 0;
-  if (m.has_big)
-    hipLaunchKernelGGL(k_render_batch<kRasterBig>, dim3(N), dim3(kBlock), lds, st, m, cam, poses, N, xyz, tri, zcap,
-                       vec);
-  else
-    hipLaunchKernelGGL(k_render_batch<kRasterSmall>, dim3(N), dim3(kBlock), lds, st, m, cam, poses, N, xyz, tri, zcap,
-                       vec);
+                               hipStream_t st) {
+  const int small = max(render_zcap(cam, kBlock), cam.W);
+  if (N <= kCUs) {
+    launch_render_bs<1024>(m, cam, poses, N, xyz, tri, render_zcap(cam, 1024), st);
+  } else if (N <= 2 * kCUs) {
+    launch_render_bs<512>(m, cam, poses, N, xyz, tri, render_zcap(cam, 512), st);
+  } else if (cam.W * cam.H > max(small, kBandedPixels) || (cam.W * cam.H > small && N >= kBandedCount)) {
+    launch_render_bs<kBlock, kFirst>(m, cam, poses, N, xyz, tri, small, st);
+    if (cam.W * cam.H > kWholeCuPixels)
+      launch_render_bs<1024, kRest>(m, cam, poses, N, xyz, tri, render_zcap(cam, 1024), st);
+    else
+      launch_render_bs<512, kRest>(m, cam, poses, N, xyz, tri, render_zcap(cam, 512), st);
+  } else {
+    launch_render_bs<kBlock>(m, cam, poses, N, xyz, tri, small, st);
+  }
   return hipGetLastError();
 }
 

@@ -257,15 +257,6 @@ hipError_t launch_score_backward(const float* obs, const float* rend, int N, int
 // row y sits in slot y mod nrows.  Needs W a multiple of 4 and 16-byte
 // aligned images (rows are then whole 16-byte words); the host checks both.
 
-// A workgroup barrier that orders LDS only: the ring kernels keep global
-// loads (the next rows) and stores (gradients) in flight across it, where
-// __syncthreads would first wait for all of them.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 constexpr int kRingPF = 8;  // float4 words per thread per step, score
 constexpr int kRingPP = 8;  // output pixels per thread per step, score
 

@@ -294,3 +294,29 @@ def test_pose_adjoint_reads_ids_either_way(b3d, H, W):
     buf[1:] = t.reshape(-1)
     odd = b3d.render_backward(b3d.Mesh(verts, tris), dev(P), K, buf[1:].view(t.shape), dev(g)).cpu().numpy()
     assert np.all(np.abs(odd - out) <= 1e-6 * np.abs(out).max())
+
+
+# point images by blocks of each size and by the second launch, rows of whole
+# 16-byte words or not, with and without ids: the same images
+@pytest.mark.parametrize("H,W", [(48, 64), (151, 201), (150, 200), (231, 300)])
+def test_render_block_sizes_and_second_launch_give_the_same(b3d, H, W):
+    rng = np.random.default_rng(W)
+    verts, tris = voxel_mesh(voxel_blob(400, rng))
+    cam = Camera(0.94 * W, 0.94 * W, W / 2 + 0.2, H / 2 - 0.3, H, W)
+    K, mesh = b3d.intrinsics_of(cam), b3d.Mesh(f32(verts), tris)
+    P = f32(random_poses(rng, 530, 0.8, 0.03))
+    P[::7, 2, 3] = 2.5
+    P[5, :3, 3] = 0.0, 0.0, 0.05
+    P[6, 2, 3] = -1.0  # behind the camera
+    P = dev(P)
+    xyz, tri = b3d.render_batch(mesh, P, K)
+    assert bool((tri[6] == -1).all()) and bool((xyz[6] == 0).all()) and bool(torch.isfinite(xyz).all())
+    for n in (1, 256, 257, 512):
+        x, t = b3d.render_batch(mesh, P[:n].contiguous(), K)
+        assert torch.equal(x, xyz[:n]) and torch.equal(t, tri[:n])
+    assert torch.equal(b3d.render_batch(mesh, P, K, want_tri=False)[0], xyz)
+    sel = [0, 1, 5, 7, 300]
+    d, ids = oracle.render([(f32(verts), tris, P[sel].cpu().numpy().astype(np.float64))], cam)
+    same = tri[sel].cpu().numpy() == ids
+    assert same.mean() >= 0.999
+    assert np.abs(xyz[sel][..., 2].cpu().numpy() - d)[same & (ids >= 0)].max() <= 1e-5
