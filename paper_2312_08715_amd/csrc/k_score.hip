@@ -534,6 +534,9 @@ hipError_t launch_score_ring(const float* obs, const float* rend, int N, int H, 
     case 2:
       hipLaunchKernelGGL(k_score_ring<2>, dim3(N), dim3(kBlock), lds, st, rows, list, rend, N, H, W, sc, R, logL);
       break;
+    case 3:
+      hipLaunchKernelGGL(k_score_ring<3>, dim3(N), dim3(kBlock), lds, st, rows, list, rend, N, H, W, sc, R, logL);
+      break;
     default:
       hipLaunchKernelGGL(k_score_ring<0>, dim3(N), dim3(kBlock), lds, st, rows, list, rend, N, H, W, sc, R, logL);
   }

@@ -320,3 +320,72 @@ def test_render_block_sizes_and_second_launch_give_the_same(b3d, H, W):
     same = tri[sel].cpu().numpy() == ids
     assert same.mean() >= 0.999
     assert np.abs(xyz[sel][..., 2].cpu().numpy() - d)[same & (ids >= 0)].max() <= 1e-5
+
+
+# the windows that are unrolled (up to 7 x 7) and looped over (from 9 x 9), of
+# an object across the image border
+@pytest.mark.parametrize("window", [5, 7, 9, 13])
+@pytest.mark.parametrize("H,W", [(24, 32), (61, 75)])
+def test_wide_windows_match_oracle(b3d, H, W, window):
+    rng = np.random.default_rng(H + window)
+    verts, tris = voxel_mesh(voxel_blob(60, rng, radius=0.06))
+    verts = f32(verts)
+    cam = Camera(W, W, W / 2 + 0.03, H / 2 - 0.04, H, W)
+    P = random_poses(rng, 6, 0.5, 0.02)
+    P[::2, 0, 3] += 0.22  # across the right edge
+    P = f32(P)
+    d, _ = oracle.render([(verts, tris, P)], cam)
+    zo = np.where(d[0] > 0, d[0], 0.52) + rng.normal(0, 0.002, (H, W))
+    obs = f32(oracle.unproject(np.where(rng.random((H, W)) < 0.2, 0.0, zo)[None], cam)[0])
+    sg, po = float(np.float32(0.01)), float(np.float32(0.1))
+    scene = b3d.Scene(b3d.Mesh(verts, tris), b3d.intrinsics_of(cam), b3d.score_params(sg, po, 1.0, window))
+    scene.set_observed(dev(obs))
+    L, g = scored(b3d, scene, dev(P), True)
+    L64, l1 = oracle.score(obs, oracle.unproject(d, cam), sg, po, 1.0, window)
+    assert np.all(np.abs(L - L64) <= 1e-4 * l1)
+    assert np.array_equal(scored(b3d, scene, dev(P), False)[0], L)
+    # the same through the point images of the kernels' own render
+    xyz, _ = b3d.render_batch(scene.mesh, dev(P), b3d.intrinsics_of(cam))
+    np.testing.assert_allclose(b3d.score(dev(obs), xyz, scene.params).cpu().numpy(), L, rtol=0, atol=1e-5 * l1.max())
+    _, ds, dp = b3d.score_backward(dev(obs), xyz, scene.params, torch.ones(6, device="cuda"))
+    for k, want in ((6, ds), (7, dp)):
+        want = want.cpu().numpy()
+        inside = np.abs(want).max()
+        assert np.abs(g[:, k] - want).max() <= 1e-4 * inside
+    scene.set_noise_grid(np.array([0.5, 1.0, 2.0]) * sg, [po, 0.4])
+    _, grid = b3d.render_score_marginal(scene, dev(P), grid=True)
+    np.testing.assert_allclose(grid[:, 1, 0].cpu().numpy(), L, rtol=0, atol=1e-5 * l1.max())
+
+
+# observed points that are no points: without depth (whatever x and y hold) they
+# count for nothing; at infinity, where no window reaches the object, logL and
+# the pose's gradient are those of a far point, in every window that skips
+# what is not drawn
+@pytest.mark.parametrize("window", [7, 9])
+def test_points_at_infinity_beside_the_object(b3d, window):
+    H, W = 40, 56
+    rng = np.random.default_rng(window)
+    verts, tris = voxel_mesh(voxel_blob(60, rng, radius=0.04))
+    cam = Camera(W, W, W / 2 + 0.03, H / 2 - 0.04, H, W)
+    K = b3d.intrinsics_of(cam)
+    P = f32(random_poses(rng, 3, 0.5, 0.0))
+    scene = b3d.Scene(b3d.Mesh(f32(verts), tris), K, b3d.score_params(0.01, 0.1, 1.0, window))
+    xyz, _ = b3d.render_batch(scene.mesh, dev(P), K)
+    z = xyz[..., 2].cpu().numpy()
+    near = np.zeros((H, W), bool)  # pixels whose window sees something drawn in any of the images
+    h = window // 2
+    for r, c in zip(*np.nonzero((z > 0).any(0))):
+        near[max(r - h, 0) : r + h + 1, max(c - h, 0) : c + h + 1] = True
+    obs = xyz[0].cpu().numpy().copy()
+    far = obs.copy()
+    hole = (z[0] > 0) & (rng.random((H, W)) < 0.2)
+    far[hole] = 0.0
+    obs[hole] = [np.nan, np.inf, 0.0]
+    far[~near], obs[~near] = [0.0, 0.0, 50.0], [np.nan, np.inf, np.inf]
+    assert near.any() and (~near).any()
+    out = []
+    for image in (far, obs):
+        scene.set_observed(dev(image))
+        out.append(scored(b3d, scene, dev(P), True))
+    np.testing.assert_allclose(out[1][0], out[0][0], rtol=1e-5)
+    np.testing.assert_allclose(out[1][1][:, :6], out[0][1][:, :6], rtol=1e-4, atol=1e-4 * np.abs(out[0][1]).max())
