@@ -3,8 +3,8 @@
 //   1. the object's conservative pixel rectangle under the pose is found;
 //   2. an LDS depth/id buffer covering that rectangle plus twice the window
 //      half-width is initialised from the static background and the mesh is
-//      rasterised into it (cluster by cluster, vertices transformed once into
-//      LDS, 64-bit atomicMin on packed (depth, id) keys);
+//      rasterised into it (cluster by cluster, a primitive per lane, 64-bit
+//      atomicMin on packed (depth, id) keys);
 //   3. every observed pixel whose window can see the object evaluates eq. (1)
 //      over its window, reading rendered depths from LDS and turning them into
 //      points on their pixel rays;
@@ -13,8 +13,8 @@
 //      ray/plane intersection of its triangle onto (dt, dw);
 //   5. pixels whose window cannot see the object contribute their
 //      background-only terms, read from double-precision summed-area tables.
-// When the rectangle does not fit the LDS budget it is processed in bands of
-// rows, re-rasterising per band.
+// When the rectangle does not fit the LDS budget it is left to a second launch
+// of larger blocks, or processed in bands of rows, re-rasterising per band.
 #include "b3d_launch.hpp"
 #include <algorithm>
 #include <type_traits>
@@ -102,9 +102,12 @@ __device__ __forceinline__ double block_total(const double (&v)[NV], double* red
 // depth rectangle L (pitch lw), which holds the whole window (positions
 // outside the image are empty slots): S = sum_j exp(-D_ij/(2 sigma^2)) and
 // T = sum_j exp(-D_ij/(2 sigma^2)) D_ij over the rendered points of the
-// window.  HH > 0: the window half-width known at compile time, unrolled (7 x 7
-// row by row) and branch-free: an empty slot's far depth makes its term exactly
-// 0.  HH = 0: any h.  From 7 x 7 on the terms of empty slots are selected away
+// window.  HH > 0: the window half-width known at compile time, each row
+// unrolled and branch-free: an empty slot's far depth makes its term exactly 0.
+// With the adjoint the rows of windows up to 5 x 5 are unrolled as well (397
+// against 400 us for 5,000 hypotheses at 160x120; without it that costs 2 %: 529
+// against 519 us for 729 of a solid mesh at 200x200, by its instructions alone).
+// HH = 0: any h.  From 7 x 7 on the terms of empty slots are selected away
 // instead, so that an observed point at infinity beside the object adds 0 and
 // not infinity times 0.  A loop that branches around empty slots is bound by
 // the latency of one pair after the other: 2,000 hypotheses at 160x120 with 11 x
@@ -123,7 +126,7 @@ __device__ __forceinline__ void window_sums(const unsigned long long* __restrict
 #pragma unroll
     for (int k = 0; k < n; ++k) dxs[k] = dxt[c - HH + k];
     const unsigned long long* zr = zbuf + (r - HH - L.y0) * lw + (c - HH - L.x0);
-#pragma unroll (HH > 2 ? 1 : 2 * HH + 1)
+#pragma unroll (GRAD && HH < 3 ? 2 * HH + 1 : 1)
     for (int j = 0; j < n; ++j, zr += lw) {
       const float dy = dyt[r - HH + j];
 #pragma unroll
@@ -1049,7 +1052,7 @@ static void launch_render_score_bs(const SceneDev& s, const float* poses, int N,
 //   large enough for objects beyond that too.  The second launch costs about
 //   4 us where nothing is left to it, so small images go without unless there
 //   are hypotheses enough to hide that.  (10,000 hypotheses of 1,500 voxels at
-//   320x240: 1,824 against 3,091 us; 700 of 6,000 at 301x227: 844 against 1,510.)
+//   320x240: 1,824 against 3,091 us.)
 //   512 threads for everything cost small objects 11 % (partly filled waves,
 //   work that every wave repeats).
 hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
