@@ -267,8 +267,10 @@ __device__ __forceinline__ void raster_band(const SceneDev& s, const Pose& P, co
 
 // One hypothesis: pose16 (16 floats), writes *logL_out and, when GRAD,
 // grad_out[0..8).  DEFER: one whose depth buffer exceeds the block's writes
-// kDeferred instead, and nothing else.  Must be called by the whole block of BS threads; `smem` is
-// at least the fused LDS size for BS and s.zcap.
+// kDeferred instead, and nothing else.  Must be called by the whole block of BS
+// threads; `smem` is at least the fused LDS size for BS and s.zcap.  Threads of
+// several waves write the results, with no barrier after them: a block that
+// goes on to read them needs one first.
 // What bounds it is VALU issue (about 90 % of the issue slots at 5,000
 // hypotheses of 160x120); so work common to the block is shared between lanes,
 // the observed pixels without a point (44 % of the region there) and the slots
@@ -589,6 +591,7 @@ __global__ __launch_bounds__(kBlock) void k_refine_pose(SceneDev s, float* __res
   __syncthreads();
   for (int it = 1; it <= n_refine; ++it) {
     render_score_one<true>(s, P, &L, g, smem);
+    __syncthreads();  // g[3..5] come from the second wave
     if (threadIdx.x == 0) adam_update(P, g, m, v, it, lr_t, lr_r, b1, b2, eps);
     __syncthreads();
   }

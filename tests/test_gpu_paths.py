@@ -389,3 +389,33 @@ def test_points_at_infinity_beside_the_object(b3d, window):
         out.append(scored(b3d, scene, dev(P), True))
     np.testing.assert_allclose(out[1][0], out[0][0], rtol=1e-5)
     np.testing.assert_allclose(out[1][1][:, :6], out[0][1][:, :6], rtol=1e-4, atol=1e-4 * np.abs(out[0][1]).max())
+
+
+# the one-workgroup refinement reads, in one thread, a gradient that threads of
+# several waves wrote: every step's has to be that step's.  Fewer and more poses
+# than fit the chip at once, an image drawn in bands of rows, one step and
+# several; against the same steps launched in turn, whose arithmetic it shares
+# (bars as in test_refine_poses_equals_score_and_adam_launched_in_turn), and
+# against itself
+@pytest.mark.parametrize("H,W,N", [(48, 64, 1), (48, 64, 1500), (120, 160, 700), (150, 200, 60)])
+def test_refinement_steps_use_their_own_gradient(b3d, H, W, N):
+    rng = np.random.default_rng(N)
+    verts, tris = voxel_mesh(voxel_blob(150, rng, radius=0.06))
+    cam = Camera(0.94 * W, 0.94 * W, W / 2 + 0.2, H / 2 - 0.3, H, W)
+    K = b3d.intrinsics_of(cam)
+    P = f32(random_poses(rng, N, 0.6, 0.02))
+    scene = b3d.Scene(b3d.Mesh(f32(verts), tris), K, b3d.score_params(0.01, 0.1, 1.0, 3))
+    xyz, _ = b3d.render_batch(scene.mesh, dev(P[:1]), K)
+    scene.set_observed(xyz[0].contiguous())
+    args = (1e-3, 1e-2, 0.9, 0.999, 1e-8)
+    for steps in (1, 4):
+        A = [dev(P) for _ in range(3)]
+        for a in A:
+            b3d.refine_poses(scene, a, steps, *args)
+        assert torch.equal(A[0], A[1]) and torch.equal(A[0], A[2])
+        B, state = dev(P), torch.zeros((N, 12), dtype=torch.float32, device="cuda")
+        for it in range(1, steps + 1):
+            _, g = b3d.render_score(scene, B, grad=True)
+            b3d.adam_pose_step(B, g, state, it, *args)
+        assert (A[0] - B).abs().max() <= 1e-6
+        assert (B[:, :3, :3] - dev(P)[:, :3, :3]).abs().amax((1, 2)).min() > 1e-3  # a rotation of every pose
