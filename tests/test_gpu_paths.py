@@ -419,3 +419,67 @@ def test_refinement_steps_use_their_own_gradient(b3d, H, W, N):
             b3d.adam_pose_step(B, g, state, it, *args)
         assert (A[0] - B).abs().max() <= 1e-6
         assert (B[:, :3, :3] - dev(P)[:, :3, :3]).abs().amax((1, 2)).min() > 1e-3  # a rotation of every pose
+
+
+# pixel centres on the edges of many faces: more of them than the exact test's
+# queue holds, in blocks of each size and in a band of two rows, for a mesh
+# without and with large faces (a shorter queue).  The exact test is the
+# oracle's, so what is covered is the same at every pixel; a centre on a shared
+# edge may go to either face of the same depth
+@pytest.mark.parametrize("px,large", [(2, False), (8, False), (8, True), (12, False)])
+def test_centres_on_many_edges_are_decided_exactly(b3d, px, large):
+    H, W, pitch = 240, 320, 0.01
+    nx, ny = min(280 // px, 100), min(200 // px, 80)
+    c = np.stack(np.meshgrid(np.arange(nx) - nx / 2 + 0.5, np.arange(ny) - ny / 2 + 0.5, [0.0], indexing="ij"), -1)
+    mesh = voxel_mesh(c.reshape(-1, 3) * pitch, pitch)
+    if large:
+        mesh = joined(mesh, box_mesh((nx * pitch * 0.9, ny * pitch * 0.5, 0.02), (0.0, 0.0, -0.015)))
+    verts, tris = f32(mesh[0]), mesh[1]
+    f = px / pitch
+    cam = Camera(f, f, W / 2, H / 2, H, W)
+    P = np.tile(np.eye(4), (3, 1, 1))  # the front faces at depth 1, their edges on the centres, between, on one axis' centres
+    P[:, 2, 3] = 1.0 + pitch / 2
+    P[:, 0, 3], P[:, 1, 3] = np.array([0.5, 0.0, 0.3]) / f, np.array([0.5, 0.0, 0.5]) / f
+    P = f32(P)
+    K, m = b3d.intrinsics_of(cam), b3d.Mesh(verts, tris)
+    d, ids = oracle.render([(verts, tris, P)], cam)
+    images = []
+    for n in (1, 100, 200):
+        xyz, tri = b3d.render_batch(m, dev(np.tile(P, (n, 1, 1))), K)
+        for k in (0, n - 1):
+            z = xyz[3 * k : 3 * k + 3, ..., 2].cpu().numpy()
+            assert np.array_equal(z > 0, d > 0), [int(((z > 0) != (d > 0))[i].sum()) for i in range(3)]
+            assert np.abs(z - d).max() <= 1e-5
+        images.append(tri[:3])
+    assert torch.equal(images[0], images[1]) and torch.equal(images[0], images[2])
+    sg, po = float(np.float32(0.01)), float(np.float32(0.1))
+    scene = b3d.Scene(m, K, b3d.score_params(sg, po, 1.0, 3))
+    obs = f32(oracle.unproject(np.where(d[:1] > 0, 1.002, 0.0), cam)[0])
+    scene.set_observed(dev(obs))
+    L64, l1 = oracle.score(obs, oracle.unproject(d, cam), sg, po, 1.0, 3)
+    for n in (1, 100, 200):
+        L = scored(b3d, scene, dev(np.tile(P, (n, 1, 1))), False)[0]
+        assert np.all(np.abs(L[:3] - L64) <= 1e-4 * l1) and np.array_equal(L, np.tile(L[:3], n))
+    scene.set_tile(scene.tile_limits()[0])
+    L = scored(b3d, scene, dev(np.tile(P, (200, 1, 1))), False)[0]
+    assert np.all(np.abs(L[:3] - L64) <= 1e-4 * l1) and np.array_equal(L, np.tile(L[:3], 200))
+
+
+# more triangles than the queue holds at one pixel: a fan around a vertex that
+# projects onto its centre
+@pytest.mark.parametrize("N", [1, 600])
+def test_more_triangles_at_one_centre_than_the_queue_holds(b3d, N):
+    n, H, W = 2500, 24, 32
+    a = np.arange(n) * (2 * np.pi / n)
+    verts = f32(np.concatenate([[[0.0, 0.0, 0.0]], np.stack([np.cos(a), np.sin(a), 0.0 * a], -1) * 0.25]))
+    k = np.arange(n)
+    tris = np.stack([0 * k, 1 + (k + 1) % n, 1 + k], -1).astype(np.int32)  # seen from -z
+    cam = Camera(32.0, 32.0, W / 2 + 0.5, H / 2 + 0.5, H, W)
+    P = np.eye(4)[None].copy()
+    P[0, 2, 3] = 1.0
+    d, ids = oracle.render([(verts, tris, P)], cam)
+    assert ids[0, H // 2, W // 2] == 0 and (ids >= 0).sum() > 100
+    xyz, tri = b3d.render_batch(b3d.Mesh(verts, tris), dev(np.tile(P, (N, 1, 1))), b3d.intrinsics_of(cam))
+    z = xyz[..., 2].cpu().numpy()
+    assert np.array_equal(z > 0, np.broadcast_to(d > 0, z.shape)) and np.abs(z - d).max() <= 1e-5
+    assert bool((tri[:, H // 2, W // 2] == 0).all()) and bool((tri == tri[:1]).all())
