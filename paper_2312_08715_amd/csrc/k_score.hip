@@ -572,7 +572,8 @@ struct CropLds {
 __host__ __device__ __forceinline__ int crop_row_bytes(int lw, int rw) { return 12 * lw + 4 * rw; }
 
 // Sums over the window of the observed point o at band slot (r, c) (row and
-// column of the crop).
+// column of the crop).  A point at infinity makes infinity times 0 of an empty
+// slot's term: such a pixel's window is gone through again, empty slots skipped.
 template <int HH, bool WANT_T>
 __device__ __forceinline__ void window_crop(const CropLds& L, int lw, int h, int slot0, float ox, float oy, float oz,
                                             float c2, float& S, float& T) {
@@ -595,6 +596,19 @@ __device__ __forceinline__ void window_crop(const CropLds& L, int lw, int h, int
     } else {
       for (int k = 0; k < n; ++k) pair(at + k);
     }
+  }
+  if (WANT_T && T != T) {
+    S = T = 0.0f;
+    at = slot0;
+    for (int j = 0; j < n; ++j, at += lw)
+      for (int i = at; i < at + n; ++i)
+        if (L.pz[i] != kFarPoint) {
+          const float ex = ox - L.px[i], ey = oy - L.py[i], ez = oz - L.pz[i];
+          const float D = ex * ex + ey * ey + ez * ez;
+          const float e = fast_exp2(-D * c2);
+          S += e;
+          T += e * D;
+        }
   }
 }
 
@@ -774,6 +788,7 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
                 gy += e * ey;
                 gz += e * ez;
               };
+              bool done = false;
               if (HH > 0 && r - HH >= wa && r + HH < wb && c - HH >= rx0 && c + HH < rx1) {
                 const float* w = L.w + (r - HH - wa) * rw + (c - HH - rx0);
                 const float* o = obs + 3 * ((size_t)(r - HH) * W + (c - HH));
@@ -781,10 +796,17 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
                 for (int j = 0; j < 2 * HH + 1; ++j, w += rw, o += 3 * (size_t)W)
 #pragma unroll
                   for (int i = 0; i < 2 * HH + 1; ++i) term(w[i], o + 3 * i);
-              } else {
+                // (a pixel without a measurement may hold anything: 0 times that is not 0)
+                const float any = gx + gy + gz;
+                done = any == any;
+              }
+              if (!done) {
+                gx = gy = gz = 0.0f;
                 for (int ri = max(r - h, wa); ri <= min(r + h, wb - 1); ++ri)
-                  for (int ci = max(c - h, rx0); ci <= min(c + h, rx1 - 1); ++ci)
-                    term(L.w[(ri - wa) * rw + (ci - rx0)], obs + 3 * ((size_t)ri * W + ci));
+                  for (int ci = max(c - h, rx0); ci <= min(c + h, rx1 - 1); ++ci) {
+                    const float w = L.w[(ri - wa) * rw + (ci - rx0)];
+                    if (w != 0.0f) term(w, obs + 3 * ((size_t)ri * W + ci));
+                  }
               }
               float* o = dn + 3 * ((size_t)r * W + c);
               o[0] = gx * sc.inv_s2;

@@ -483,3 +483,37 @@ def test_more_triangles_at_one_centre_than_the_queue_holds(b3d, N):
     z = xyz[..., 2].cpu().numpy()
     assert np.array_equal(z > 0, np.broadcast_to(d > 0, z.shape)) and np.abs(z - d).max() <= 1e-5
     assert bool((tri[:, H // 2, W // 2] == 0).all()) and bool((tri == tri[:1]).all())
+
+
+# the split adjoint with observed pixels that hold no measurement (whatever x and
+# y are) and points at infinity where no window sees anything drawn: the same
+# gradients as with zeros and far points there, with and without a workspace
+@pytest.mark.parametrize("workspace", [True, False])
+@pytest.mark.parametrize("window", [1, 3, 5, 7, 9])
+def test_score_adjoint_with_points_that_are_none(b3d, window, workspace):
+    H, W, h = 33, 48, window // 2
+    rng = np.random.default_rng(window)
+    cam = Camera(W, W, W / 2, H / 2, H, W)
+    rays = oracle.unproject(np.ones((1, H, W)), cam)[0]
+    z = np.zeros((2, H, W))
+    z[0, 9:22, 12:30] = 0.8 + rng.normal(0, 0.003, (13, 18))
+    z[1, 12:20, 10:33] = 0.8 + rng.normal(0, 0.003, (8, 23))
+    z[:, ::3, ::4] = 0.0
+    rend = f32(z[..., None] * rays)
+    near = np.zeros((H, W), bool)
+    for r, c in zip(*np.nonzero((z > 0).any(0))):
+        near[max(r - h, 0) : r + h + 1, max(c - h, 0) : c + h + 1] = True
+    plain = f32((0.8 + rng.normal(0, 0.003, (H, W)))[..., None] * rays)
+    odd = plain.copy()
+    hole = rng.random((H, W)) < 0.2
+    plain[hole], odd[hole] = 0.0, [np.nan, np.inf, 0.0]
+    beside = ~near & ~hole
+    plain[beside], odd[beside] = [0.0, 0.0, 50.0], [np.nan, np.inf, np.inf]
+    assert hole[near].any() and beside.any()
+    p, dl = b3d.score_params(0.005, 0.1, 1.0, window), dev([1.0, -0.7])
+    a, b = (b3d.score_backward(dev(o), dev(rend), p, dl, workspace=workspace) for o in (plain, odd))
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+    _, s64, _ = oracle.score_grad(plain, rend, float(np.float32(0.005)), float(np.float32(0.1)), 1.0, window)
+    want = s64 * dl.cpu().numpy()
+    assert np.all(np.abs(b[1].cpu().numpy() - want) <= 1e-5 * np.abs(want).max())
