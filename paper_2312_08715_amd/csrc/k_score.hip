@@ -817,6 +817,8 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
       __syncthreads();
     }
   }
+  // less all observed pixels: whole numbers, exact
+  for (int r = threadIdx.x; r < H; r += kCropBlock) acc[2] -= (double)rows[r + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -829,7 +831,7 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
     for (int w = 0; w < kCropWaves; ++w)
       for (int k = 0; k < 3; ++k) t[k] += sums[3 * w + k];
     // the observed pixels that see nothing
-    t[1] += ((double)rows[H] - t[2]) * (double)(sc.invV / sc.a);
+    t[1] -= t[2] * (double)(sc.invV / sc.a);
     if (d_sigma) d_sigma[n] = (float)((double)g * t[0]);
     if (d_pout) d_pout[n] = (float)((double)g * t[1]);
   }
@@ -851,11 +853,12 @@ static auto crop_kernel(int h) {
 hipError_t launch_score_backward_crop(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc,
                                       void* workspace, const float* dlogL, float* d_rend, float* d_sigma,
                                       float* d_pout, hipStream_t st) {
-  if (hipError_t e = launch_obs_list(obs, H, W, workspace, st)) return e;
+  // the rows' counts of observed pixels alone: the list is not read
+  int* rows = reinterpret_cast<int*>(workspace);
+  hipLaunchKernelGGL(k_obs_count, dim3(H), dim3(kBlock), 0, st, obs, H, W, rows);
   const bool vec = W % 4 == 0 && (((uintptr_t)rend | (uintptr_t)d_rend) & 15) == 0;
   hipLaunchKernelGGL((vec ? crop_kernel<true>(sc.h) : crop_kernel<false>(sc.h)), dim3(N), dim3(kCropBlock), kCropLds,
-                     st, obs, rend, N, H, W, sc, reinterpret_cast<const int*>(workspace), dlogL, d_rend, d_sigma,
-                     d_pout);
+                     st, obs, rend, N, H, W, sc, rows, dlogL, d_rend, d_sigma, d_pout);
   return hipGetLastError();
 }
 

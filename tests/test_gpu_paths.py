@@ -517,3 +517,25 @@ def test_score_adjoint_with_points_that_are_none(b3d, window, workspace):
     _, s64, _ = oracle.score_grad(plain, rend, float(np.float32(0.005)), float(np.float32(0.1)), 1.0, window)
     want = s64 * dl.cpu().numpy()
     assert np.all(np.abs(b[1].cpu().numpy() - want) <= 1e-5 * np.abs(want).max())
+
+
+# observed pixels that see nothing drawn are only counted, by rows: more rows
+# than a workgroup has threads, rows without any, and none at all
+@pytest.mark.parametrize("H,W", [(1, 7), (700, 9), (513, 4)])
+def test_score_adjoint_counts_what_sees_nothing(b3d, H, W):
+    rng = np.random.default_rng(H)
+    cam = Camera(50.0, 50.0, W / 2, H / 2, H, W)
+    rays = oracle.unproject(np.ones((1, H, W)), cam)[0]
+    z = np.zeros((3, H, W))
+    z[1, H // 3 : H // 3 + 3] = 0.8
+    z[2, H - 1, 0] = 0.8
+    rend = f32(z[..., None] * rays)
+    zo = np.where(rng.random((H, W)) < 0.3, 0.0, 0.8 + rng.normal(0, 0.003, (H, W)))
+    zo[H // 2 : H // 2 + 5] = 0.0
+    sg, po = float(np.float32(0.005)), float(np.float32(0.1))
+    for obs in (f32(zo[..., None] * rays), np.zeros((H, W, 3))):
+        dr, ds, dp = b3d.score_backward(dev(obs), dev(rend), b3d.score_params(sg, po, 1.0, 3))
+        r64, s64, p64 = oracle.score_grad(obs, rend, sg, po, 1.0, 3)
+        assert np.abs(dr.cpu().numpy() - r64).max() <= 1e-5 * np.abs(r64).max()
+        for got, want in ((ds, s64), (dp, p64)):
+            assert np.all(np.abs(got.cpu().numpy() - want) <= 1e-5 * np.abs(want).max())
