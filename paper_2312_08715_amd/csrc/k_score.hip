@@ -557,11 +557,12 @@ hipError_t launch_score_ring(const float* obs, const float* rend, int N, int H, 
 //   LDS: points x | y | z of the band's rendered rows [a - 2h, b + 2h) and of
 //   columns [x0 - 2h, x1 + 2h) (an empty or outside slot holds a far point,
 //   whose terms are exactly 0), the weights w_i = g b / L_i of observed rows
-//   [a - h, b + h), the waves' queues.
-constexpr int kCropBlock = 512;
-constexpr int kCropWaves = kCropBlock / 64;
-constexpr size_t kCropLds = 80 * 1024;  // two workgroups per CU
-constexpr size_t kCropFixed = 64 * sizeof(int) + sizeof(double) * 3 * kCropWaves + 2 * kWaveQueue * kCropWaves;
+//   [a - h, b + h), the waves' queues: area_bytes of points and weights, at
+//   least what one row and its halo take at the image's width.
+constexpr size_t kCropLds = 80 * 1024;  // the most: two workgroups per CU
+constexpr size_t crop_fixed_bytes(int bs) {
+  return 64 * sizeof(int) + (sizeof(double) * 3 + 2 * kWaveQueue) * (bs / 64);
+}
 constexpr float kFarPoint = 1.0e15f;
 
 struct CropLds {
@@ -612,15 +613,15 @@ __device__ __forceinline__ void window_crop(const CropLds& L, int lw, int h, int
   }
 }
 
-template <int HH, bool VEC>
-__global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const float* __restrict__ obs,
-                                                                       const float* __restrict__ rend, int N, int H,
-                                                                       int W, ScoreConsts sc,
-                                                                       const int* __restrict__ rows,
-                                                                       const float* __restrict__ dlogL,
-                                                                       float* __restrict__ d_rend,
-                                                                       float* __restrict__ d_sigma,
-                                                                       float* __restrict__ d_pout) {
+template <int HH, bool VEC, int BS>
+__global__ __launch_bounds__(BS, 4) void k_score_backward_crop(const float* __restrict__ obs,
+                                                               const float* __restrict__ rend, int N, int H, int W,
+                                                               ScoreConsts sc, const int* __restrict__ rows,
+                                                               const float* __restrict__ dlogL,
+                                                               float* __restrict__ d_rend, float* __restrict__ d_sigma,
+                                                               float* __restrict__ d_pout, int area_bytes) {
+  constexpr int kCropWaves = BS / 64;
+  constexpr size_t kCropFixed = crop_fixed_bytes(BS);
   extern __shared__ __align__(16) unsigned char smem[];
   int* rect = reinterpret_cast<int*>(smem);  // row and column bounds of the drawn pixels
   double* sums = reinterpret_cast<double*>(rect + 64);
@@ -642,18 +643,18 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
     const f4v* src = reinterpret_cast<const f4v*>(rn);
     f4v* dst = reinterpret_cast<f4v*>(dn);
     constexpr int kTurn = 4;
-    for (int base = threadIdx.x; base < nq; base += kTurn * kCropBlock) {
+    for (int base = threadIdx.x; base < nq; base += kTurn * BS) {
       f4v v[kTurn][3];
 #pragma unroll
       for (int u = 0; u < kTurn; ++u) {
-        const int q = min(base + u * kCropBlock, nq - 1);
+        const int q = min(base + u * BS, nq - 1);
 #pragma unroll
         for (int k = 0; k < 3; ++k) v[u][k] = src[3 * (size_t)q + k];
       }
       if (dn) {
 #pragma unroll
         for (int u = 0; u < kTurn; ++u) {
-          const int q = base + u * kCropBlock;
+          const int q = base + u * BS;
           if (q < nq)
 #pragma unroll
             for (int k = 0; k < 3; ++k) dst[3 * (size_t)q + k] = zero;
@@ -663,7 +664,7 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
       for (int u = 0; u < kTurn; ++u) {
         const bool d0 = v[u][0].z > 0.0f, d1 = v[u][1].y > 0.0f, d2 = v[u][2].x > 0.0f, d3 = v[u][2].w > 0.0f;
         if (d0 || d1 || d2 || d3) {  // (a quad read twice at the end changes nothing)
-          const int q = min(base + u * kCropBlock, nq - 1);
+          const int q = min(base + u * BS, nq - 1);
           const int r = q / qpr, c = 4 * (q - r * qpr);
           r_lo = min(r_lo, r);
           r_hi = max(r_hi, r);
@@ -675,9 +676,9 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
   } else {
     const int np = H * W;
     if (dn)
-      for (size_t k = threadIdx.x; k < 3 * (size_t)np; k += kCropBlock) dn[k] = 0.0f;
+      for (size_t k = threadIdx.x; k < 3 * (size_t)np; k += BS) dn[k] = 0.0f;
 #pragma unroll 8
-    for (int p = threadIdx.x; p < np; p += kCropBlock) {
+    for (int p = threadIdx.x; p < np; p += BS) {
       if (rn[3 * (size_t)p + 2] > 0.0f) {
         const int r = p / W, c = p - r * W;
         r_lo = min(r_lo, r);
@@ -700,7 +701,7 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
   if (y1 > 0) {
     const int ry0 = max(y0 - h, 0), ry1 = min(y1 + h, H), rx0 = max(x0 - h, 0), rx1 = min(x1 + h, W);
     const int lx0 = x0 - 2 * h, lw = x1 - x0 + 4 * h, rw = rx1 - rx0;
-    const int room = (int)(kCropLds - kCropFixed) / crop_row_bytes(lw, rw);
+    const int room = area_bytes / crop_row_bytes(lw, rw);
     const int band = max(room - 4 * h, 1);
     const float inv_lw = 1.0f / (float)lw, inv_rw = 1.0f / (float)rw, inv_ow = 1.0f / (float)(x1 - x0);
     const float gb = g * sc.bn;
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
       L.pz = L.py + nl;
       L.w = L.pz + nl;
       // 2. the band's points
-      for (int k = threadIdx.x; k < nl; k += kCropBlock) {
+      for (int k = threadIdx.x; k < nl; k += BS) {
         int r, c;
         row_col(k, lw, inv_lw, r, c);
         r += ly0;
@@ -818,7 +819,7 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
     }
   }
   // less all observed pixels: whole numbers, exact
-  for (int r = threadIdx.x; r < H; r += kCropBlock) acc[2] -= (double)rows[r + 1];
+  for (int r = threadIdx.x; r < H; r += BS) acc[2] -= (double)rows[r + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -839,17 +840,25 @@ __global__ __launch_bounds__(kCropBlock, 4) void k_score_backward_crop(const flo
 
 // Whether the kernel takes images of width W: one row and its halo in LDS.
 bool score_backward_crop_fits(int W, int h) {
-  return (size_t)(4 * h + 1) * crop_row_bytes(W + 4 * h, W) <= kCropLds - kCropFixed;
+  return (size_t)(4 * h + 1) * crop_row_bytes(W + 4 * h, W) <= kCropLds - crop_fixed_bytes(512);
 }
 
-template <bool VEC>
+template <bool VEC, int BS>
 static auto crop_kernel(int h) {
-  return h == 1   ? k_score_backward_crop<1, VEC>
-         : h == 2 ? k_score_backward_crop<2, VEC>
-         : h == 3 ? k_score_backward_crop<3, VEC>
-                  : k_score_backward_crop<0, VEC>;
+  return h == 1   ? k_score_backward_crop<1, VEC, BS>
+         : h == 2 ? k_score_backward_crop<2, VEC, BS>
+         : h == 3 ? k_score_backward_crop<3, VEC, BS>
+                  : k_score_backward_crop<0, VEC, BS>;
 }
 
+// Threads and LDS by how many workgroups a CU then holds, which is what bounds
+// small images: never more LDS than the whole image needs; 256 threads up to
+// 1,024 pixels (3,000 images of 24x32, 3x3 windows, mostly empty or full: 40 and
+// 87 us against 57 and 108 with 512); and half of the LDS, four workgroups per
+// CU instead of two, where there are hypotheses for them and a band still has
+// more rows of its own than 5/4 of its halo's (3,000 of 48x64, 3x3: 83 and 246 us
+// against 101 and 277; 500 of 120x160, 7x7, a halo of most of the band: 135 and
+// 1,409 against 122 and 713).
 hipError_t launch_score_backward_crop(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc,
                                       void* workspace, const float* dlogL, float* d_rend, float* d_sigma,
                                       float* d_pout, hipStream_t st) {
@@ -857,8 +866,16 @@ hipError_t launch_score_backward_crop(const float* obs, const float* rend, int N
   int* rows = reinterpret_cast<int*>(workspace);
   hipLaunchKernelGGL(k_obs_count, dim3(H), dim3(kBlock), 0, st, obs, H, W, rows);
   const bool vec = W % 4 == 0 && (((uintptr_t)rend | (uintptr_t)d_rend) & 15) == 0;
-  hipLaunchKernelGGL((vec ? crop_kernel<true>(sc.h) : crop_kernel<false>(sc.h)), dim3(N), dim3(kCropBlock), kCropLds,
-                     st, obs, rend, N, H, W, sc, rows, dlogL, d_rend, d_sigma, d_pout);
+  const int h = sc.h, bs = H * W <= 1024 ? 256 : 512, fixed = (int)crop_fixed_bytes(bs);
+  const int row = crop_row_bytes(W + 4 * h, W);
+  int area = (int)kCropLds - fixed;
+  const int half = (int)kCropLds / 2 - fixed;
+  if (N > 2 * kCUs && half / row - 4 * h > 5 * h) area = half;
+  area = (int)std::min<size_t>(area, (size_t)(H + 4 * h) * row);
+  auto k = bs == 256 ? (vec ? crop_kernel<true, 256>(h) : crop_kernel<false, 256>(h))
+                     : (vec ? crop_kernel<true, 512>(h) : crop_kernel<false, 512>(h));
+  hipLaunchKernelGGL(k, dim3(N), dim3(bs), (size_t)(fixed + area), st, obs, rend, N, H, W, sc, rows, dlogL, d_rend,
+                     d_sigma, d_pout, area);
   return hipGetLastError();
 }
 

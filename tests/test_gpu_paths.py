@@ -539,3 +539,31 @@ def test_score_adjoint_counts_what_sees_nothing(b3d, H, W):
         assert np.abs(dr.cpu().numpy() - r64).max() <= 1e-5 * np.abs(r64).max()
         for got, want in ((ds, s64), (dp, p64)):
             assert np.all(np.abs(got.cpu().numpy() - want) <= 1e-5 * np.abs(want).max())
+
+
+# the split adjoint's workgroup and LDS by image size and number of hypotheses:
+# either side of 1,024 pixels, of 512 hypotheses, and of the halo that half of
+# the LDS is worth: the same gradients as the general kernel and the oracle
+@pytest.mark.parametrize("window", [1, 3, 7])
+@pytest.mark.parametrize("H,W", [(24, 32), (25, 31), (32, 32), (33, 32), (48, 64), (60, 90)])
+def test_score_adjoint_by_workgroups_of_either_size(b3d, H, W, window):
+    rng = np.random.default_rng(H * W + window)
+    cam = Camera(0.9 * W, 0.9 * W, W / 2, H / 2, H, W)
+    rays = oracle.unproject(np.ones((1, H, W)), cam)[0]
+    z = 0.8 + rng.normal(0, 0.003, (4, H, W))
+    z[1, : H // 3] = z[2, :, W // 2 :] = 0.0
+    z[3] = 0.0
+    z[3, H // 2 : H // 2 + 9, 3:14] = 0.8
+    rend = f32(z[..., None] * rays)
+    zo = np.where(rng.random((H, W)) < 0.2, 0.0, 0.8 + rng.normal(0, 0.003, (H, W)))
+    obs = f32(zo[..., None] * rays)
+    sg, po = float(np.float32(0.005)), float(np.float32(0.1))
+    p = b3d.score_params(sg, po, 1.0, window)
+    want = oracle.score_grad(obs, rend, sg, po, 1.0, window)
+    general = b3d.score_backward(dev(obs), dev(rend), p, workspace=False)
+    for n in (1, 128, 129):
+        got = b3d.score_backward(dev(obs), dev(np.tile(rend, (n, 1, 1, 1))), p)
+        for k, (g, w, o) in enumerate(zip(got, general, want)):
+            assert bool((g.view(n, *w.shape) == g[:4]).all())
+            bar = 1e-5 * np.abs(o).max()
+            assert np.abs(g[:4].cpu().numpy() - o).max() <= bar and (g[:4] - w).abs().max() <= 2 * bar, k
