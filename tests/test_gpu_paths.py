@@ -567,3 +567,26 @@ def test_score_adjoint_by_workgroups_of_either_size(b3d, H, W, window):
             assert bool((g.view(n, *w.shape) == g[:4]).all())
             bar = 1e-5 * np.abs(o).max()
             assert np.abs(g[:4].cpu().numpy() - o).max() <= bar and (g[:4] - w).abs().max() <= 2 * bar, k
+
+
+# larger images go by 512 threads alone up to 1,024 poses, with a second launch
+# beyond: the same images as few poses at a time
+@pytest.mark.parametrize("H,W", [(150, 161), (150, 200), (240, 320)])
+def test_render_second_launch_beyond_two_rounds_gives_the_same(b3d, H, W):
+    rng = np.random.default_rng(H + W)
+    verts, tris = voxel_mesh(voxel_blob(400, rng))
+    cam = Camera(0.94 * W, 0.94 * W, W / 2 + 0.2, H / 2 - 0.3, H, W)
+    K, mesh = b3d.intrinsics_of(cam), b3d.Mesh(f32(verts), tris)
+    P = f32(random_poses(rng, 1025, 0.8, 0.03))
+    P[::7, 2, 3] = 2.5
+    P[1, :3, 3] = 0.0, 0.0, 0.05
+    P = dev(P)
+    xyz, tri = b3d.render_batch(mesh, P, K)
+    for k, n in ((0, 1024), (0, 100), (1000, 25)):
+        x, t = b3d.render_batch(mesh, P[k : k + n].contiguous(), K)
+        assert torch.equal(x, xyz[k : k + n]) and torch.equal(t, tri[k : k + n])
+    sel = [0, 1, 2, 1024]
+    d, ids = oracle.render([(f32(verts), tris, P[sel].cpu().numpy().astype(np.float64))], cam)
+    same = tri[sel].cpu().numpy() == ids
+    assert same.mean() >= 0.999
+    assert np.abs(xyz[sel][..., 2].cpu().numpy() - d)[same & (ids >= 0)].max() <= 1e-5
