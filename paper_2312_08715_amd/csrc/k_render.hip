@@ -39,11 +39,12 @@ template <bool VEC, int BS>
 __device__ __forceinline__ void write_band_rows(const Cam& cam, const Rect& band, const unsigned long long* zbuf,
                                                 float* __restrict__ xyz, int* __restrict__ tri) {
   constexpr int V = VEC ? 4 : 1;
-  const int W = cam.W, per_row = W / V, n = band.h() * per_row, bw = band.w();
-  const float inv = 1.0f / (float)per_row;
-  for (int q = threadIdx.x; q < n; q += BS) {
-    int dr, qc;
-    row_col(q, per_row, inv, dr, qc);
+  const int W = cam.W, per_row = W / V, n_rows = band.h(), bw = band.w();
+  // row and column stepped, not found from an index: a narrow object's band can
+  // hold more pixels of the image than row_col is exact for
+  const int step_r = BS / per_row, step_c = BS - step_r * per_row;
+  int dr = (int)threadIdx.x / per_row, qc = (int)threadIdx.x - dr * per_row;
+  while (dr < n_rows) {
     const int r = band.y0 + dr, c0 = V * qc;
     float x[V], y[V], z[V];
     int id[V];
@@ -78,6 +79,12 @@ __device__ __forceinline__ void write_band_rows(const Cam& cam, const Rect& band
       xyz[3 * p + 1] = y[0];
       xyz[3 * p + 2] = z[0];
       if (tri) tri[p] = id[0];
+    }
+    dr += step_r;
+    qc += step_c;
+    if (qc >= per_row) {
+      qc -= per_row;
+      ++dr;
     }
   }
 }

@@ -590,3 +590,23 @@ def test_render_second_launch_beyond_two_rounds_gives_the_same(b3d, H, W):
     same = tri[sel].cpu().numpy() == ids
     assert same.mean() >= 0.999
     assert np.abs(xyz[sel][..., 2].cpu().numpy() - d)[same & (ids >= 0)].max() <= 1e-5
+
+
+# a thin, tall object in the first or the last column of an image of several
+# megapixels: its band covers more pixels than an index in single precision holds
+@pytest.mark.parametrize("H,W", [(1200, 4095), (3400, 1921), (3400, 1920)])
+def test_thin_objects_at_the_edges_of_large_images(b3d, H, W):
+    f = 2000.0
+    verts, tris = box_mesh((3.0 / f, (H - 41.0) / f, 0.002))
+    verts = f32(verts)
+    cam = Camera(f, f, W / 2, H / 2, H, W)
+    P = np.tile(np.eye(4), (2, 1, 1))
+    P[:, 2, 3] = 1.0
+    P[:, 0, 3] = (0.8 - W / 2) / f, (W / 2 - 0.8) / f
+    P = f32(P)
+    d, ids = oracle.render([(verts, tris, P)], cam)
+    assert (d[0, :, 0] > 0).sum() > H - 60 and (d[1, :, -1] > 0).sum() > H - 60
+    xyz, tri = b3d.render_batch(b3d.Mesh(verts, tris), dev(P), b3d.intrinsics_of(cam))
+    z = xyz[..., 2].cpu().numpy()
+    assert np.array_equal(z > 0, d > 0), int(((z > 0) != (d > 0)).sum())
+    assert np.abs(z - d).max() <= 1e-5 and np.array_equal(tri.cpu().numpy() >= 0, ids >= 0)
