@@ -49,7 +49,7 @@ struct Pose {
 // normals and the sine of its half-angle plus a margin (above 1: no bound).
 // `alike` clusters hold parallelograms a, a + ab, a + ab + ad, a + ad that
 // share their edge vectors up to the rounding of the vertices: the faces of
-// equal voxels.
+// equal voxels.  ab.w is how far from one of their corners that puts it at most.
 struct ClusterDev {
   int pfirst, np, alike, pad;
   float4 sphere;
@@ -498,7 +498,8 @@ constexpr int kStepBox = 16;
 // 160x120 with the adjoint, 3,086 against 4,177 us for 10,000 of 1,500 voxels at
 // 320x240.
 // Returns false, for the whole wave, when the general path has to take the
-// cluster: a corner behind the near plane or a box beyond kStepBox.
+// cluster: a corner behind the near plane (or so near that 1/z is in doubt) or a
+// box beyond kStepBox.
 template <bool COUNT>
 __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev& m, const Pose& P, const Cam& cam,
                                              uint32_t id_base, const Rect& buf, int pitch, float bx0, float bx1,
@@ -517,7 +518,7 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
   const float aX = cam.fx * oa.x, aY = cam.fy * oa.y;
   const float Bz = oa.z + rb.z, Dz = oa.z + rd.z, Cz = Bz + rd.z;
   const float zmin = fminf(fminf(oa.z, Bz), fminf(Cz, Dz));
-  if (__ballot(in && !(zmin > cam.znear)) != 0ull) return false;
+  if (__ballot(in && !(zmin > fmaxf(cam.znear, 256.0f * cl.ab.w))) != 0ull) return false;
   const float iA = __builtin_amdgcn_rcpf(oa.z), iB = __builtin_amdgcn_rcpf(Bz);
   const float iC = __builtin_amdgcn_rcpf(Cz), iD = __builtin_amdgcn_rcpf(Dz);
   const float Au = __builtin_fmaf(aX, iA, cu), Av = __builtin_fmaf(aY, iA, cv);
@@ -530,7 +531,11 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
   const float area1 = e1x * e2y - e2x * e1y, area2 = e1x * f1y - f1x * e1y;
   const float mag = fmaxf(fmaxf(fmaxf(fabsf(Au), fabsf(Av)), fmaxf(fabsf(Bu), fabsf(Bv))),
                           fmaxf(fmaxf(fabsf(Cu), fabsf(Cv)), fmaxf(fabsf(Du), fabsf(Dv))));
-  const float tau = 2e-6f * fmaxf(mag + 0.5f, 256.0f);
+  // rounding, and what a corner ab.w away from its place moves on the screen
+  // (the projection's slopes are f/z and (u - cx)/z)
+  const float wide = fmaxf(cam.fx, cam.fy) + fmaxf(fabsf(cam.cx), fabsf(cam.cy)) + 1.0f;
+  const float off = 1.01f * cl.ab.w * fmaxf(fmaxf(iA, iB), fmaxf(iC, iD));
+  const float tau = __builtin_fmaf(off, mag + wide, 2e-6f * fmaxf(mag + 0.5f, 256.0f));
   const float len = fmaxf(fmaxf(fmaxf(fabsf(e0x) + fabsf(e0y), fabsf(e1x) + fabsf(e1y)),
                                 fmaxf(fabsf(e2x) + fabsf(e2y), fabsf(f0x) + fabsf(f0y))),
                           fabsf(f1x) + fabsf(f1y));

@@ -405,6 +405,7 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
       double axis[3] = {0, 0, 0};
       double blo[3] = {1e300, 1e300, 1e300}, bhi[3] = {-1e300, -1e300, -1e300};
       size_t j = i;
+      double off = 0.0;
       c.alike = ps[i].alike ? 1 : 0;
       if (c.alike) {
         const Edges& e = common[cls_dir];
@@ -414,6 +415,16 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
       for (; j < ps.size() && c.np < kClusterPrims && (ps[j].key >> 32) == cls_dir && ps[j].alike == ps[i].alike;
            ++j) {
         const Prim& pr = ps[j];
+        if (c.alike)  // how far the shared edges put a corner from its place
+          for (int k = 1; k < 4; ++k) {
+            double d2 = 0.0;
+            for (int x = 0; x < 3; ++x) {
+              const double ab = (&c.ab.x)[x], ad = (&c.ad.x)[x];
+              const double e = pos(pr.p[k], x) - pos(pr.p[0], x) - (k < 3 ? ab : 0.0) - (k > 1 ? ad : 0.0);
+              d2 += e * e;
+            }
+            off = std::max(off, std::sqrt(d2));
+          }
         for (int k = 0; k < 4; ++k) {
           L.pverts.push_back(make_float4((float)pos(pr.p[k], 0), (float)pos(pr.p[k], 1), (float)pos(pr.p[k], 2), 0.0f));
           for (int a2 = 0; a2 < 3; ++a2) {
@@ -425,6 +436,7 @@ MeshLayout build_mesh_layout(const float* verts, int V, const int* tris, int T) 
         for (int a2 = 0; a2 < 3; ++a2) axis[a2] += unit[3 * pr.id1 + a2] + (pr.id2 >= 0 ? unit[3 * pr.id2 + a2] : 0.0);
         ++c.np;
       }
+      c.ab.w = (float)(off * (1.0 + 1e-6));
       double ctr[3], rad = 0.0;
       for (int a2 = 0; a2 < 3; ++a2) ctr[a2] = 0.5 * (blo[a2] + bhi[a2]);
       for (int v = 0; v < 4 * c.np; ++v) {

@@ -610,3 +610,30 @@ def test_thin_objects_at_the_edges_of_large_images(b3d, H, W):
     z = xyz[..., 2].cpu().numpy()
     assert np.array_equal(z > 0, d > 0), int(((z > 0) != (d > 0)).sum())
     assert np.abs(z - d).max() <= 1e-5 and np.array_equal(tri.cpu().numpy() >= 0, ids >= 0)
+
+
+# faces that share their edges only up to the rounding of the largest coordinate
+# (here 60 m away): what that moves a corner by on the screen is part of the margin
+# of the exact test, so coverage is the oracle's at every pixel
+@pytest.mark.parametrize("N", [1, 600])
+def test_nearly_equal_faces_of_a_large_mesh_are_decided_exactly(b3d, N):
+    H, W, f = 120, 160, 1200.0
+    k = np.arange(10)
+    c = np.stack(np.meshgrid(k, k, [0.0], indexing="ij"), -1).reshape(-1, 3) * 0.01
+    small, large = voxel_mesh(c, 0.01), voxel_mesh(c, 0.01)
+    large = large[0] * (1.0 + 1e-3) + [0.0, 0.11, 0.0], large[1]  # 1e-5 m an edge
+    mesh = turned(joined(small, large, box_mesh((0.01, 0.01, 0.01), (60.0, 0.0, 0.0))), 0.3)
+    verts, tris = f32(mesh[0]), mesh[1]
+    cam = Camera(f, f, 20.0, 30.0, H, W)
+    P = np.tile(np.eye(4), (4, 1, 1))
+    P[:, 2, 3] = 1.0
+    P[:, 0, 3], P[:, 1, 3] = [0.003, -0.02, 0.011, 0.03], [0.004, -0.1, 0.0, -0.13]
+    P = f32(P)
+    d, ids = oracle.render([(verts, tris, P)], cam)
+    assert (ids >= 0).mean() > 0.3
+    xyz, tri = b3d.render_batch(b3d.Mesh(verts, tris), dev(np.tile(P, (N, 1, 1))), b3d.intrinsics_of(cam))
+    for n in (0, N - 1):
+        z, i = xyz[4 * n : 4 * n + 4, ..., 2].cpu().numpy(), tri[4 * n : 4 * n + 4].cpu().numpy()
+        assert np.array_equal(z > 0, d > 0), int(((z > 0) != (d > 0)).sum())
+        assert np.abs(z - d).max() <= 1e-5
+        assert (i == ids).mean() >= 0.9999, int((i != ids).sum())
