@@ -246,14 +246,17 @@ b3d_status b3d_render_score_marginal(const b3d_scene* scene, const float* poses,
  * each candidate size of the LDS depth buffer (the sizes that leave room for
  * 2..6 resident workgroups per CU, down to the smallest that still holds one
  * row band), keeps the fastest in the scene and returns its depth-buffer
- * capacity (keys) in *zcap_out (may be NULL).  Synchronises the device.
+ * capacity (keys) in *zcap_out (may be NULL).  Calls of up to 512 hypotheses
+ * take larger workgroups with depth buffers of their own whatever the tile: a
+ * sample that small keeps the default.  Synchronises the device.
  * poses: device float[N][16], a representative sample (N >= 1). */
 b3d_status b3d_scene_autotune(b3d_scene* scene, const float* poses, int32_t N, int32_t grad, int32_t* zcap_out,
                               void* stream);
 /* The depth-buffer capacities (keys) b3d_scene_set_tile accepts for this
  * scene, and the current one.  Any pointer may be NULL. */
 b3d_status b3d_scene_tile_limits(const b3d_scene* scene, int32_t* min_keys, int32_t* max_keys, int32_t* current);
-/* Set the depth-buffer capacity directly (e.g. from a cached tuning result);
+/* Set the depth-buffer capacity directly (e.g. from a cached tuning result:
+ * the scene is then as b3d_scene_autotune left the one it came from);
  * zcap <= 0 restores the default.  Fails with B3D_ESHAPE when it does not fit
  * the LDS or cannot hold one band of rows. */
 b3d_status b3d_scene_set_tile(b3d_scene* scene, int32_t zcap);

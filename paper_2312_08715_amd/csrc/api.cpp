@@ -107,8 +107,8 @@ int max_zcap(const SceneDev& d) {
   SceneDev t = d;
   t.zcap = 0;
   const size_t rest = fused_lds_bytes(t);
-  // also bounded by the drawn-slot list, which lives in the raster scratch
-  return (int)std::min<size_t>((kLdsMax > rest ? kLdsMax - rest : 0) / kFusedBytesPerKey, kRasterLdsBytes / 2);
+  // (far below the 65,536 slots that the waves' 16-bit queues can index)
+  return (int)((kLdsMax > rest ? kLdsMax - rest : 0) / kFusedBytesPerKey);
 }
 
 b3d_status make_noise_grid(const b3d_score_params& base, int H, int W, const float* sigma, int A, const float* p_out,
@@ -722,6 +722,57 @@ b3d_status run_batch(const BatchPlan& plan, hipStream_t st, hipStream_t side, hi
   return B3D_OK;
 }
 
+b3d_status tune_tile(const SceneDev& d, const float* poses, int N, bool grad, bool batch, hipStream_t st, int* zcap) {
+  *zcap = std::max(default_zcap(d, 4), min_zcap(d));
+  if (!batch && !launch_uses_tile(d, N, grad)) return B3D_OK;  // every candidate would be the same launch
+  float* out = nullptr;
+  if (hipMalloc((void**)&out, sizeof(float) * 9 * (size_t)N) != hipSuccess)
+    return fail(B3D_ENOMEM, "scene_autotune: scratch allocation failed");
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  (void)hipEventCreate(&e0);
+  (void)hipEventCreate(&e1);
+  float best_ms = 3.0e38f;
+  std::vector<int> cands;
+  for (int b = 2; b <= 6; ++b) {
+    const int z = std::min(default_zcap(d, b), max_zcap(d));
+    if (cands.empty() || cands.back() != z) cands.push_back(z);
+  }
+  if (cands.back() != min_zcap(d)) cands.push_back(min_zcap(d));
+  auto launch = [&](const SceneDev& t) {
+    float* g = grad ? out + N : nullptr;
+    if (!batch) return launch_render_score(t, poses, N, out, g, st);
+    BatchGroupDev G{};
+    G.S = 1;
+    G.s[0] = t;
+    G.poses[0] = poses;
+    G.logL[0] = out;
+    G.grad[0] = g;
+    G.first[1] = N;
+    return launch_batch(G, grad, fused_lds_bytes(t), st);
+  };
+  b3d_status status = B3D_OK;
+  for (int z : cands) {
+    SceneDev t = d;
+    t.zcap = z;
+    if (z < min_zcap(d) || fused_lds_bytes(t) > kLdsMax) continue;
+    float ms = 0.0f;
+    for (int rep = 0; rep < 3 && status == B3D_OK; ++rep) {
+      if (hipEventRecord(e0, st) != hipSuccess || launch(t) != hipSuccess || hipEventRecord(e1, st) != hipSuccess ||
+          hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+        status = fail(B3D_EHIP, "scene_autotune: timing launch failed");
+    }
+    if (status != B3D_OK) break;
+    if (ms < best_ms) {
+      best_ms = ms;
+      *zcap = z;
+    }
+  }
+  (void)hipEventDestroy(e0);
+  (void)hipEventDestroy(e1);
+  (void)hipFree(out);
+  return status;
+}
+
 }  // namespace b3d_api
 
 extern "C" {
@@ -787,7 +838,6 @@ b3d_status b3d_scene_set_tile(b3d_scene* S, int32_t zcap) {
   if (t.zcap < min_zcap(S->dev) || t.zcap > max_zcap(S->dev) || fused_lds_bytes(t) > kLdsMax)
     return fail(B3D_ESHAPE, "scene_set_tile: %d keys outside [%d, LDS limit]", zcap, min_zcap(S->dev));
   S->dev.zcap = t.zcap;
-  S->dev.fixed_tile = zcap > 0;
   return B3D_OK;
 }
 
@@ -796,47 +846,9 @@ b3d_status b3d_scene_autotune(b3d_scene* S, const float* poses, int32_t N, int32
   if (!S || !poses) return fail(B3D_EINVAL, "scene_autotune: NULL pointer");
   if (!S->observed) return fail(B3D_EINVAL, "scene_autotune: call b3d_scene_set_observed first");
   if (N < 1) return fail(B3D_ESHAPE, "scene_autotune: need N >= 1");
-  hipStream_t st = (hipStream_t)stream;
-  float* out = nullptr;
-  if (hipMalloc((void**)&out, sizeof(float) * 9 * (size_t)N) != hipSuccess)
-    return fail(B3D_ENOMEM, "scene_autotune: scratch allocation failed");
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  (void)hipEventCreate(&e0);
-  (void)hipEventCreate(&e1);
-  const int keep = S->dev.zcap;
-  int best = keep;
-  float best_ms = 3.0e38f;
-  std::vector<int> cands;
-  for (int b = 2; b <= 6; ++b) {
-    const int z = std::min(default_zcap(S->dev, b), max_zcap(S->dev));
-    if (cands.empty() || cands.back() != z) cands.push_back(z);
-  }
-  if (cands.back() != min_zcap(S->dev)) cands.push_back(min_zcap(S->dev));
-  b3d_status status = B3D_OK;
-  for (int z : cands) {
-    SceneDev t = S->dev;
-    t.zcap = z;
-    if (z < min_zcap(S->dev) || fused_lds_bytes(t) > kLdsMax) continue;
-    float ms = 0.0f;
-    for (int rep = 0; rep < 3 && status == B3D_OK; ++rep) {
-      if (hipEventRecord(e0, st) != hipSuccess ||
-          launch_render_score(t, poses, N, out, grad ? out + N : nullptr, st) != hipSuccess ||
-          hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-          hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
-        status = fail(B3D_EHIP, "scene_autotune: timing launch failed");
-    }
-    if (status != B3D_OK) break;
-    if (ms < best_ms) {
-      best_ms = ms;
-      best = z;
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  (void)hipFree(out);
-  if (status != B3D_OK) return status;
+  int best = 0;
+  if (b3d_status s = tune_tile(S->dev, poses, N, grad != 0, false, (hipStream_t)stream, &best)) return s;
   S->dev.zcap = best;
-  S->dev.fixed_tile = 0;
   if (zcap_out) *zcap_out = best;
   return B3D_OK;
 }

@@ -61,6 +61,11 @@ b3d_status plan_batch(const std::vector<BatchItemDev>& items, bool grad, BatchPl
 // that one launch's tail overlaps the next one's start.
 b3d_status run_batch(const BatchPlan& plan, hipStream_t st, hipStream_t side = nullptr, hipEvent_t fork = nullptr,
                      hipEvent_t join = nullptr);
+// The tile (see b3d_scene_autotune) under which N hypotheses of d are scored
+// fastest, by a launch of their own or by a batch's; the default where the
+// launch does not take the tile.  Synchronises st.
+b3d_status tune_tile(const SceneDev& d, const float* poses, int N, bool grad, bool batch, hipStream_t st, int* zcap);
+
 }  // namespace b3d_api
 
 #define B3D_CHECK_HIP(expr, where)                                   \

@@ -32,8 +32,7 @@ struct SceneDev {
   const float* obs;                // [H][W][3]
   const unsigned long long* bg;    // [H][W] background keys, or nullptr
   const double* sat;               // 3 summed-area tables [(H+1)(W+1)]: l, dl/dp, dl/dsigma of the background
-  int zcap;                        // LDS capacity of the depth buffer in keys
-  int fixed_tile;                  // zcap is the caller's: launches keep it whatever their size
+  int zcap;                        // depth keys of a 256-thread workgroup (the scene's tile)
 };
 
 // A grid of noise parameters for the hierarchical likelihood: A standard
@@ -212,6 +211,9 @@ hipError_t launch_score(const float* obs, const float* rend, int N, int H, int W
 hipError_t launch_score_backward(const float* obs, const float* rend, int N, int H, int W, const ScoreConsts& sc,
                                  const float* dlogL, float* d_rend, float* d_sigma, float* d_pout, int cap,
                                  hipStream_t st);
+// Whether launch_render_score of N hypotheses takes the scene's tile, or
+// workgroups of a size and depth buffer of their own.
+bool launch_uses_tile(const SceneDev& s, int N, bool grad);
 hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, float* logL, float* grad, hipStream_t st);
 hipError_t launch_render_score_count(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                      unsigned long long* work, hipStream_t st);

@@ -482,21 +482,19 @@ __global__ __launch_bounds__(BS, 4) void k_render_score(SceneDev s, const float*
 
 static bool defers(const SceneDev& s, long long N) {
   const long long whole = (long long)(s.cam.W + 4 * s.sc.h) * (s.cam.H + 4 * s.sc.h);
-  return !s.fixed_tile && whole > s.zcap && (s.cam.W * s.cam.H > kBandedPixels || N >= kBandedCount);
+  return whole > s.zcap && (s.cam.W * s.cam.H > kBandedPixels || N >= kBandedCount);
 }
 static int rest_block(const SceneDev& s) { return s.cam.W * s.cam.H > kWholeCuPixels ? 1024 : 512; }
 
-// The scene with the depth buffer that a block of bs threads has room for: its
-// share of a CU's LDS, no more than the image needs.  The caller's own tile
-// stays.  False when even that does not fit (the widest images).
+// The scene with the depth buffer that a block of bs > kBlock threads has room
+// for, whatever the scene's tile: its share of a CU's LDS, no more than the image
+// needs.  False when not even one band fits (the widest images).
 static bool roomy_scene(const SceneDev& s, int bs, bool grad, SceneDev* t) {
   *t = s;
-  if (!s.fixed_tile) {
-    const size_t share = kLdsPerCU / (1024 / bs), rest = fused_lds_bytes(s, bs, 0);
-    const int fit = share > rest ? (int)((share - rest) / (kFusedBytesPerKey + (grad ? 4 : 0))) : 0;
-    const int whole = (s.cam.W + 4 * s.sc.h) * (s.cam.H + 4 * s.sc.h);
-    t->zcap = std::max(s.zcap, std::min(fit, whole));
-  }
+  const size_t share = kLdsPerCU / (1024 / bs), rest = fused_lds_bytes(s, bs, 0);
+  const int fit = share > rest ? (int)((share - rest) / (kFusedBytesPerKey + (grad ? 4 : 0))) : 0;
+  const int whole = (s.cam.W + 4 * s.sc.h) * (s.cam.H + 4 * s.sc.h);
+  t->zcap = std::max(min_zcap(s), std::min(fit, whole));
   return launch_lds_bytes(*t, bs, t->zcap, grad) <= kLdsPerCU;
 }
 
@@ -557,7 +555,6 @@ hipError_t launch_batch(const BatchGroupDev& g, bool grad, size_t lds, hipStream
   BatchGroupDev rest = g;
   size_t rest_lds = 0;
   for (int k = 0; k < g.S && defer; ++k) {
-    // a scene with a tile of the caller's has nothing left to it, or bands
     fits = fits && roomy_scene(g.s[k], bs, grad, &rest.s[k]);
     rest_lds = std::max(rest_lds, launch_lds_bytes(rest.s[k], bs, rest.s[k].zcap, grad));
   }
@@ -1058,6 +1055,11 @@ static void launch_render_score_bs(const SceneDev& s, const float* poses, int N,
 //   320x240: 1,824 against 3,091 us.)
 //   512 threads for everything cost small objects 11 % (partly filled waves,
 //   work that every wave repeats).
+bool launch_uses_tile(const SceneDev& s, int N, bool grad) {
+  SceneDev t;
+  return !(N <= kCUs && roomy_scene(s, 1024, grad, &t)) && !(N <= 2 * kCUs && roomy_scene(s, 512, grad, &t));
+}
+
 hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                hipStream_t st) {
   const bool g = grad != nullptr;

@@ -458,14 +458,12 @@ b3d_status b3d_smc_step(b3d_smc* S, void* stream) {
     int big = 0;
     for (int o = 0; o < n_types; ++o)
       if (S->types[o]->T > S->types[big]->T) big = o;
-    b3d_scene* sc = S->scenes[rep[0]];
-    SceneDev keep = sc->dev;
-    sc->dev.mesh = S->types[big]->dev;
-    int z = 0;
-    const b3d_status s = b3d_scene_autotune(sc, S->stage0_poses + 16 * (size_t)big * 6 * n0, 6 * n0, 0, &z, st);
-    sc->dev.mesh = keep.mesh;
-    if (s) return s;
-    S->zcap = z;
+    SceneDev d = S->scenes[rep[0]]->dev;
+    d.mesh = S->types[big]->dev;
+    if (b3d_status s = tune_tile(d, S->stage0_poses + 16 * (size_t)big * 6 * n0, 6 * n0, false, true, st, &S->zcap)) {
+      S->zcap = 0;
+      return s;
+    }
   }
   auto scene_of = [&](int m, int o) {
     SceneDev d = S->scenes[rep[m]]->dev;

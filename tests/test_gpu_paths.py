@@ -2,6 +2,8 @@
 it changes: against the FP64 oracle, or against another route that has to give
 the same.  Bars as in test_gpu_parity.py."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -637,3 +639,100 @@ def test_nearly_equal_faces_of_a_large_mesh_are_decided_exactly(b3d, N):
         assert np.array_equal(z > 0, d > 0), int(((z > 0) != (d > 0)).sum())
         assert np.abs(z - d).max() <= 1e-5
         assert (i == ids).mean() >= 0.9999, int((i != ids).sum())
+
+
+def kernels_of(call):
+    """Kernels that a call launches on the current stream, from a captured graph."""
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)
+    st, graph, n = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        assert hip.hipStreamBeginCapture(ctypes.c_void_p(st.cuda_stream), 0) == 0
+        try:
+            call()
+        finally:
+            rc = hip.hipStreamEndCapture(ctypes.c_void_p(st.cuda_stream), ctypes.byref(graph))
+    assert rc == 0 and hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+# a tuned tile, the same tile from the cache and the same tile set: the scene's
+# launches are the same; a sample too small to take the tile leaves the default
+@pytest.mark.parametrize("grad", [False, True])
+def test_a_cached_tile_takes_the_route_of_a_tuned_one(b3d, tmp_path, grad):
+    rng = np.random.default_rng(5)
+    H, W = 180, 240
+    verts, tris = voxel_mesh(voxel_blob(300, rng))
+    cam = Camera(0.94 * W, 0.94 * W, W / 2, H / 2, H, W)
+    K, mesh = b3d.intrinsics_of(cam), b3d.Mesh(f32(verts), tris)
+    P = dev(f32(random_poses(rng, 700, 0.7, 0.03)))
+    xyz, _ = b3d.render_batch(mesh, P[:1].contiguous(), K)
+    obs, cache, p = xyz[0].contiguous(), str(tmp_path / "tiles.json"), b3d.score_params(0.004, 0.05, 1.0, 5)
+    L, g = torch.empty(700, device="cuda"), torch.empty((700, 8), device="cuda")
+
+    def fresh():
+        scene = b3d.Scene(mesh, K, p)
+        scene.set_observed(obs)
+        return scene
+
+    def call(scene):
+        b3d._call("b3d_render_score", scene._h, P.data_ptr(), 700, L.data_ptr(), g.data_ptr() if grad else None,
+                  b3d._stream())
+
+    default = fresh()
+    want = kernels_of(lambda: call(default))
+    assert want == 2
+    results = []
+    for how in ("tuned", "cached", "set", "tuned after set"):
+        scene = fresh()
+        if how == "set":
+            scene.set_tile(tile)
+        elif how == "tuned after set":
+            scene.set_tile(scene.tile_limits()[0])
+            scene.autotune(P, grad=grad)
+        else:
+            tile = scene.autotune(P, grad=grad, cache=cache)
+        if how != "tuned after set":
+            assert scene.tile_limits()[2] == tile
+        assert kernels_of(lambda: call(scene)) == want, how
+        call(scene)
+        results.append((L.clone(), g.clone() if grad else None))
+    for x, y in results[1:]:
+        assert torch.equal(x, results[0][0]) and (not grad or torch.equal(y, results[0][1]))
+    scene = fresh()
+    size = scene.tile_limits()[2]
+    for n in (1, 256, 512):
+        scene.set_tile(scene.tile_limits()[0])
+        assert scene.autotune(P[:n].contiguous(), grad=grad) == size == scene.tile_limits()[2]
+
+
+# bands of rows in 256-thread workgroups (images below 24,000 pixels, tiles of two
+# rows) give what one band gives, with the adjoint and for noise grids in registers and in LDS
+@pytest.mark.parametrize("window", [3, 5, 7, 9])
+def test_bands_of_small_tiles_give_the_same(b3d, window):
+    rng = np.random.default_rng(window)
+    H, W = 90, 120
+    verts, tris = voxel_mesh(voxel_blob(300, rng, radius=0.08))
+    cam = Camera(0.94 * W, 0.94 * W, W / 2 + 0.2, H / 2 - 0.3, H, W)
+    K = b3d.intrinsics_of(cam)
+    P = dev(f32(random_poses(rng, 600, 0.6, 0.03)))
+    scene = b3d.Scene(b3d.Mesh(f32(verts), tris), K, b3d.score_params(0.004, 0.05, 1.0, window))
+    xyz, _ = b3d.render_batch(scene.mesh, P[1:2].contiguous(), K)
+    scene.set_observed(xyz[0].contiguous())
+    few = P[:200].contiguous()  # one large workgroup each, in one band
+    want = [scored(b3d, scene, few, grad) for grad in (False, True)]
+    grids = []
+    for A, B in ((3, 5), (5, 3)):
+        scene.set_noise_grid(*b3d.noise_grid_midpoints(0.012, A, B))
+        grids.append(b3d.render_score_marginal(scene, few, grid=True))
+    scene.set_tile(scene.tile_limits()[0])
+    for grad in (False, True):
+        for a, b in zip(scored(b3d, scene, P, grad), want[grad]):
+            np.testing.assert_array_equal(a[:200], b)
+    for (A, B), ref in zip(((3, 5), (5, 3)), grids):
+        scene.set_noise_grid(*b3d.noise_grid_midpoints(0.012, A, B))
+        for a, b in zip(b3d.render_score_marginal(scene, P, grid=True), ref):
+            assert torch.equal(a[:200], b)
