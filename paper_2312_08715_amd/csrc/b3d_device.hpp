@@ -150,9 +150,6 @@ __device__ __forceinline__ float max8(float v) {
   v = fmaxf(v, lane_swap<0x4E>(v));
   return fmaxf(v, lane_swap<0x141>(v));
 }
-__device__ __forceinline__ float uniform(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
 
 // Range of x/z over a sphere (centre c, radius r) in front of the camera:
 // the planes x = k z through the camera that touch the sphere have
@@ -610,10 +607,9 @@ __device__ __forceinline__ bool raster_alike(const ClusterDev& cl, const MeshDev
 // buf.w(); band inside buf).  Triangle ids written are
 // id_base + the caller's triangle index.  Clusters are tested for drawing,
 // one per thread at a time, and the drawable ones compacted into a list; the
-// waves then take clusters from the list independently: a wave transforms
-// its cluster's vertices into its own LDS buffer and each lane takes one
-// primitive (a quad or a triangle), walking the pixel centres of its screen
-// box; with BIG, up to kBigSlots boxes of more than kBigCentres centres per
+// waves then take clusters from the list independently: each lane takes one
+// primitive (a quad or a triangle), projects its corners and walks the pixel
+// centres of its screen box (alike clusters: see raster_alike); with BIG, up to kBigSlots boxes of more than kBigCentres centres per
 // wave and cluster are walked by the whole wave instead (with the same
 // coverage tests from the same values).  A centre that single
 // precision places clearly inside all three edges is written at once (64-bit

@@ -173,7 +173,9 @@ __device__ __forceinline__ void window_sums(const unsigned long long* __restrict
 // 1/sigma^2 factor.  HH > 0: the half-width known at compile time, for windows
 // inside the weights' rows and the region's columns (every pixel away from the
 // image border), each row unrolled; the rest, and HH = 0, in a loop over the
-// clipped window.  A weight of 0 adds nothing, whatever the point it belongs to.
+// clipped window.  A weight of 0 adds nothing, whatever the point it belongs to,
+// but in 3 x 3 and 5 x 5 windows off the border, whose terms are not selected: x
+// and y of a pixel without a measurement have to be finite there.
 // Border rows unrolled with clamped columns took 96 bytes of spilled registers
 // a thread against 28, and 408 us against 398 us for 5,000 hypotheses at 160x120
 // with 5 x 5 windows.
@@ -1040,11 +1042,16 @@ static void launch_render_score_bs(const SceneDev& s, const float* poses, int N,
   hipLaunchKernelGGL(k, dim3(N), dim3(BS), lds, st, s, poses, N, logL, grad);
 }
 
+bool launch_uses_tile(const SceneDev& s, int N, bool grad) {
+  SceneDev t;
+  return !(N <= kCUs && roomy_scene(s, 1024, grad, &t)) && !(N <= 2 * kCUs && roomy_scene(s, 512, grad, &t));
+}
+
 // One workgroup scores one hypothesis; how large a one is chosen for two
 // reasons, and no result depends on it.
 // * A launch of fewer hypotheses than the chip has slots lasts as long as one
 //   workgroup: up to one hypothesis per CU, each gets all of a CU's sixteen
-//   waves and its LDS (256 hypotheses at 64x48: 13.6 against 17.5 us), up to two,
+//   waves and its LDS (256 hypotheses at 64x48: 13.7 against 17.5 us), up to two,
 //   half of them.
 // * An object beyond the 256-thread block's depth buffer is drawn in bands of
 //   rows, each setting the mesh up again.  Such hypotheses are left to a second
@@ -1052,14 +1059,9 @@ static void launch_render_score_bs(const SceneDev& s, const float* poses, int N,
 //   large enough for objects beyond that too.  The second launch costs about
 //   4 us where nothing is left to it, so small images go without unless there
 //   are hypotheses enough to hide that.  (10,000 hypotheses of 1,500 voxels at
-//   320x240: 1,824 against 3,091 us.)
+//   320x240: 1,835 against 3,091 us.)
 //   512 threads for everything cost small objects 11 % (partly filled waves,
 //   work that every wave repeats).
-bool launch_uses_tile(const SceneDev& s, int N, bool grad) {
-  SceneDev t;
-  return !(N <= kCUs && roomy_scene(s, 1024, grad, &t)) && !(N <= 2 * kCUs && roomy_scene(s, 512, grad, &t));
-}
-
 hipError_t launch_render_score(const SceneDev& s, const float* poses, int N, float* logL, float* grad,
                                hipStream_t st) {
   const bool g = grad != nullptr;
