@@ -46,7 +46,7 @@ HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E, published
 # what the same counters read for a plain 256 MiB device copy (FETCH_SIZE x 2.0,
 # WRITE_SIZE x 1.0).  Valid only for the kernel sources with this digest:
 # after any change to them the figure is reported as null until re-measured.
-TRAFFIC = {"sources_sha256": "269efe6930b11a3dd9df6a73c0ddb74e3f46555747f96450e2a3b1fc5d562d63", "fetch_KiB": 9205.0, "write_KiB": 21240.3, "fetch_scale": 2.0, "write_scale": 1.0}
+TRAFFIC = {"sources_sha256": "ecd69a3aacec87de9d3a7f192bd9427328b76ec74b0817baea5098f07c20206e", "fetch_KiB": 9027.4, "write_KiB": 8738.4, "fetch_scale": 2.0, "write_scale": 1.0}
 KERNEL_SOURCES = ["k_fused.hip", "b3d_device.hpp", "b3d_launch.hpp"]
 
 
@@ -718,10 +718,10 @@ SPLIT_BYTES_PER_DRAWN = {"render_backward": 12}
 # dispatch, mean over the run's dispatches); valid for the sources with this
 # digest only.
 SPLIT_SOURCES = ["k_render.hip", "k_score.hip", "b3d_device.hpp", "b3d_launch.hpp"]
-SPLIT_TRAFFIC = {"sources_sha256": "51cdec12678880161b9d0f0d91215c96cd6f0dc7a18707156aa11a0948cfc40d",
-                 "KiB": {"render_batch": [38806.7, 1125717.1], "render_batch_ids": [42261.7, 1501541.9],
-                         "score": [563812.9, 166.1], "score_backward": [624505.3, 1202365.1],
-                         "render_backward": [258313.9, 234.4]}}
+SPLIT_TRAFFIC = {"sources_sha256": "d85f4e9d697d611c3ffba22ab4daafcb0aa8fc3ec8fc88863d6aa374ff13fef7",
+                 "KiB": {"render_batch": [39138.2, 1125609.5], "render_batch_ids": [42763.2, 1501480.2],
+                         "score": [563819.3, 167.0], "score_backward": [624491.5, 1202282.3],
+                         "render_backward": [258303.4, 234.4]}}
 
 
 def split_sources_digest() -> str:
